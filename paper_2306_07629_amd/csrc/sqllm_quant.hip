@@ -10,13 +10,14 @@
 //   3. Per output row, weighted 1-D k-means over the remaining weights (Eq. 4: minimise sum_j s_j (w_j - Q(w_j))^2
 //      over 2^b values) by Lloyd iterations: equal-count start, nearest-centroid assignment, sensitivity-weighted
 //      means.  Every integer decision is taken in fp32 exactly as written below and the weighted sums are exact
-//      64-bit integers, so the result does not depend on the order of the additions.  The row is sorted once and
+//      integers, so the result does not depend on the order of the additions.  The row is sorted into buckets once and
 //      the iterations move the K - 1 cluster boundaries (see quant_kmeans_kernel).
 //   4. fp16 tables, final indices (nearest table entry in exact arithmetic, ties to the lower index; an extracted
 //      position gets the entry nearest to zero) and the packed index stream in the layout the matvec reads.
 #include <hip/hip_runtime.h>
 #include <atomic>
 #include <stdint.h>
+#include <type_traits>
 
 #include "sqllm_kernels.h"
 
@@ -186,335 +187,420 @@ __global__ void __launch_bounds__(1024) quant_scan_kernel(int M, int* __restrict
     for (int i = b; i < e; ++i) { run += rowptr[i + 1]; rowptr[i + 1] = run; }
 }
 
-// Sum of a 32-bit integer over the 64 lanes with DPP moves (no LDS traffic), returned as a uniform value.
-template <int CTRL, int ROW_MASK = 0xF>
-__device__ __forceinline__ int dpp_add(int v) { return v + __builtin_amdgcn_update_dpp(0, v, CTRL, ROW_MASK, 0xF, false); }
-__device__ __forceinline__ int wave_sum_i32(int v) {
-    v = dpp_add<0xB1>(v);            // quad_perm [1,0,3,2]
-    v = dpp_add<0x4E>(v);            // quad_perm [2,3,0,1]
-    v = dpp_add<0x141>(v);           // row_half_mirror
-    v = dpp_add<0x140>(v);           // row_mirror: every lane holds the sum of its row of 16
-    v = dpp_add<0x142, 0xA>(v);      // row_bcast:15 into rows 1 and 3
-    v = dpp_add<0x143, 0xC>(v);      // row_bcast:31 into rows 2 and 3: lane 63 holds the total
-    return __builtin_amdgcn_readlane(v, 63);
-}
-// The three sums a boundary needs over the lanes' (sensitivity, product) pairs -- sum s, sum of the low words and sum of
-// the high words of the products p = s * w * 2^24 -- from four 32-bit reductions: s < 2^16 and |p| < 2^57, so the 16-bit
-// halves of the low word and the (signed) high word all add up over 64 lanes without overflow.
-__device__ __forceinline__ void wave_sums(u32 sv, i64 p, u64& s0, u64& lo, u64& hi) {
-    const u32 plo = (u32)((u64)p & 0xFFFFFFFFull);
-    const int phi = (int)(p >> 32);
-    const u32 a = (u32)wave_sum_i32((int)(plo & 0xFFFFu)), b = (u32)wave_sum_i32((int)(plo >> 16));
-    s0 = (u64)(u32)wave_sum_i32((int)sv);
-    lo = (u64)a + ((u64)b << 16);
-    hi = (u64)(i64)wave_sum_i32(phi);
-}
-
 __device__ __forceinline__ u32 umin(u32 a, u32 b) { return a < b ? a : b; }
 __device__ __forceinline__ u32 umax(u32 a, u32 b) { return a < b ? b : a; }
 
-// The sort is a bitonic network in its all-ascending form: the merge of size k first compares word i of the lower half
-// with its MIRROR image k - 1 - i in the upper half, then runs the usual half-cleaners of distance k/4, k/8, ... 1.  Every
-// comparator puts the smaller word at the lower index, so words past the end of the row, thought of as +infinity, never
-// move and comparators reaching past the end are simply skipped: the cost follows N, not the next power of two.
-// Steps with distances below 16 stay inside aligned blocks of 16 words; a thread runs them in registers:
-// FULL: the whole merges k = 2, 4, 8, 16 (start of the sort);  otherwise the half-cleaners 8, 4, 2, 1 of a later merge.
-template <bool FULL>
-__device__ __forceinline__ void sort_block_steps(u32* __restrict__ A, int blk) {
-    u32 v[16];
-    u32x4* src = reinterpret_cast<u32x4*>(A + 16 * blk);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) { const u32x4 t4 = src[i]; v[4 * i] = t4.x; v[4 * i + 1] = t4.y; v[4 * i + 2] = t4.z; v[4 * i + 3] = t4.w; }
-    auto cx = [&](int a, int b) { const u32 lo = umin(v[a], v[b]), hi = umax(v[a], v[b]); v[a] = lo; v[b] = hi; };
-    if constexpr (FULL) {
-#pragma unroll
-        for (int k = 2; k <= 16; k <<= 1) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {                                // mirror step of merge k
-                const int base = (i / (k / 2)) * k, off = i % (k / 2);
-                cx(base + off, base + k - 1 - off);
-            }
-#pragma unroll
-            for (int j = k >> 2; j > 0; j >>= 1) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) cx(2 * i - (i & (j - 1)), 2 * i - (i & (j - 1)) + j);
-            }
-        }
-    } else {
-#pragma unroll
-        for (int j = 8; j > 0; j >>= 1) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) cx(2 * i - (i & (j - 1)), 2 * i - (i & (j - 1)) + j);
-        }
+// ---------------------------------------------------------------------------------------------- k-means of one row
+template <int CTRL, int ROW_MASK = 0xF>
+__device__ __forceinline__ u32 dpp_u32(u32 old, u32 v) { return (u32)__builtin_amdgcn_update_dpp((int)old, (int)v, CTRL, ROW_MASK, 0xF, false); }
+constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kRowHalfMirror = 0x141, kRowMirror = 0x140;
+constexpr int kRowShl1 = 0x101, kRowShr1 = 0x111, kRowShr2 = 0x112, kRowShr4 = 0x114, kRowShr8 = 0x118, kRowBcast15 = 0x142, kRowBcast31 = 0x143;
+
+// Exact sum of products s * w * 2^24.  |w| < 128 in the whole row: a product is below 2^47 and a row's sum below 2^63; else the low and
+// the high words of the products are summed apart.
+template <bool WIDE>
+struct Moment {
+    i64 v;
+    __device__ __forceinline__ static Moment zero() { return {0}; }
+    __device__ __forceinline__ static Moment product(u32 word) {     // word: key << 16 | sensitivity
+        const int fixed = (int)(half_bits_to_f32(key_half(word >> 16)) * 16777216.0f);   // exact
+        return {(i64)fixed * (i64)(int)(word & 0xFFFFu)};
     }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) src[i] = u32x4{v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]};
+    __device__ __forceinline__ Moment operator+(const Moment& o) const { return {v + o.v}; }
+    __device__ __forceinline__ Moment operator-(const Moment& o) const { return {v - o.v}; }
+    __device__ __forceinline__ double value() const { return (double)v; }
+    template <int CTRL, int ROW_MASK = 0xF>
+    __device__ __forceinline__ Moment moved() const {
+        const u32 lo = dpp_u32<CTRL, ROW_MASK>(0, (u32)(u64)v), hi = dpp_u32<CTRL, ROW_MASK>(0, (u32)((u64)v >> 32));
+        return {(i64)((u64)lo | ((u64)hi << 32))};
+    }
+};
+template <>
+struct Moment<true> {
+    i64 lo, hi;
+    __device__ __forceinline__ static Moment zero() { return {0, 0}; }
+    __device__ __forceinline__ static Moment product(u32 word) {
+        const i64 p = half_to_fixed(key_half(word >> 16)) * (i64)(word & 0xFFFFu);
+        return {(i64)((u64)p & 0xFFFFFFFFull), p >> 32};
+    }
+    __device__ __forceinline__ Moment operator+(const Moment& o) const { return {lo + o.lo, hi + o.hi}; }
+    __device__ __forceinline__ Moment operator-(const Moment& o) const { return {lo - o.lo, hi - o.hi}; }
+    __device__ __forceinline__ double value() const { return (double)hi * 4294967296.0 + (double)lo; }   // both exact: one rounding
+    template <int CTRL, int ROW_MASK = 0xF>
+    __device__ __forceinline__ Moment moved() const {
+        const Moment<false> a = Moment<false>{lo}.template moved<CTRL, ROW_MASK>(), b = Moment<false>{hi}.template moved<CTRL, ROW_MASK>();
+        return {a.v, b.v};
+    }
+};
+struct Plain {                                                       // a 32-bit count or sum with the same interface
+    u32 v;
+    __device__ __forceinline__ Plain operator+(const Plain& o) const { return {v + o.v}; }
+    template <int CTRL, int ROW_MASK = 0xF>
+    __device__ __forceinline__ Plain moved() const { return {dpp_u32<CTRL, ROW_MASK>(0, v)}; }
+};
+// sum over each row of 16 lanes, in all its lanes
+template <class T>
+__device__ __forceinline__ T row16_sum(T v) {
+    v = v + v.template moved<kQuadXor1>();
+    v = v + v.template moved<kQuadXor2>();
+    v = v + v.template moved<kRowHalfMirror>();
+    v = v + v.template moved<kRowMirror>();
+    return v;
+}
+// inclusive prefix sum over the 64 lanes
+template <class T>
+__device__ __forceinline__ T wave_scan(T v) {
+    v = v + v.template moved<kRowShr1>();
+    v = v + v.template moved<kRowShr2>();
+    v = v + v.template moved<kRowShr4>();
+    v = v + v.template moved<kRowShr8>();
+    v = v + v.template moved<kRowBcast15, 0xA>();
+    v = v + v.template moved<kRowBcast31, 0xC>();
+    return v;
+}
+// Largest key k with 2 w(k) <= t, t between the smallest and the largest fp16 value doubled (the correction steps make it exact whatever
+// the conversion rounds to).
+__device__ __forceinline__ u32 key_below(float t) {
+    typedef __fp16 fp16x2 __attribute__((ext_vector_type(2)));
+    const fp16x2 h = __builtin_amdgcn_cvt_pkrtz(0.5f * t, 0.f);
+    u32 k = half_key(__builtin_bit_cast(u32, h) & 0xFFFFu);
+    if (t < 2.0f * half_bits_to_f32(key_half(k))) --k;
+    if (!(t < 2.0f * half_bits_to_f32(key_half(k + 1)))) ++k;
+    return k;
 }
 
-// One block of 256 threads per row.  In one dimension the clusters of Lloyd's method are intervals of the sorted
-// weights, so the row is sorted once and every iteration only moves K - 1 boundaries:
-//   * LDS holds the row's dense weights as (key << 16 | sensitivity), sorted ascending by a bitonic network
-//     (extracted positions are 0xFFFFFFFF and end up behind the dense ones; the network skips what lies past the row),
-//     and the running sums (sum s, low and high words of sum s w 2^24) in front of every chunk of 64 sorted weights.
-//   * A boundary position p_k = #{ j : fp32(2 w_j) <= fp32(c_k + c_{k+1}) } is found by a 64-way search (every lane
-//     probes one position per round, three rounds cover 2^18 weights); the sums in front of p_k are the chunk's running
-//     sums plus a wave reduction over the part of the chunk before p_k; cluster sums are differences of neighbours.
-//     These are the same decisions and the same exact integer sums as a pass over all weights, hence the same result.
-//   * "No weight changed its cluster" is "no boundary position moved".
-// The final indices and the packed stream are produced from the row as it lies in memory.
+// One block of T threads per row.  In one dimension the clusters of Lloyd's method are intervals of the sorted weights, so an update
+// only needs, for each of the K - 1 boundaries, how many weights lie below it and their exact sums.  The row is not sorted for that:
+//   * it is read once; every thread keeps its weights as words (key << 16 | sensitivity) in registers until the indices are written;
+//   * a counting sort puts the words into NB buckets of 2^shift consecutive keys (shift from the row's smallest and largest key); the
+//     atomic that counts a word also gives its place in the bucket; the order inside a bucket does not matter, all sums are integers;
+//   * C0 / C1 hold the sums in front of every chunk of 16 words;
+//   * 16 lanes evaluate a boundary: the key below it names the bucket, and the sums are those in front of the chunk in which the
+//     bucket starts plus the words up to the end of the bucket that precede the bucket or have a key within the boundary.  A bucket
+//     holds a handful of words, so that is one round of two words per lane.  A wave takes four boundaries, K / 4 waves work on an
+//     iteration, which costs one barrier.
+// The decisions and integers are those of a pass over all weights per update, hence the same result.
+// Bound by the latency of that chain (boundary -> bucket -> words -> reduction -> division) and, beyond two rows per unit, by the vector
+// ALU.  Against a bitonic sort of the row in LDS and a 64-way search per boundary with reductions over 64 lanes: 4096x4096 at 3 bits
+// 409 -> 134 us (22 updates per row, 3.6 us each over the matrix), 4096x11008 at 4 bits 1164 -> 447 us (32 updates, 8.0 us each).  All
+// boundaries of an iteration in one wave, without a barrier: 160 and 968 us.
 template <int BITS, int T>
-__global__ void __launch_bounds__(T) quant_kmeans_kernel(int M, int N, int NP, int max_iter, const uint16_t* __restrict__ w, const uint16_t* __restrict__ sens,
+struct KmeansShape {
+    static constexpr int V = T == 256 ? 2 : 4;                       // units of eight weights per thread: N <= 8 T V
+    static constexpr int NB = T == 256 ? 1024 : 2048;                // buckets
+    static constexpr int kMinLog = T == 256 ? 10 : 11;               // log2(NB)
+    static constexpr int kMaxN = T == 256 ? 4096 : (T == 512 ? 16384 : 28672);
+};
+__host__ __device__ constexpr size_t kmeans_lds(int N, int NB) { return (size_t)N * 4 + (size_t)(N / 16 + 1) * 20 + (size_t)(NB + 4) * 4; }
+
+template <int BITS, int T>
+__global__ void __launch_bounds__(T) quant_kmeans_kernel(int M, int N, int max_iter, const uint16_t* __restrict__ w, const uint16_t* __restrict__ sens,
                                                          const u32* __restrict__ ws, const int* __restrict__ rowptr, void* __restrict__ qidx,
                                                          uint16_t* __restrict__ lut, int* __restrict__ cols, uint16_t* __restrict__ vals, int* __restrict__ iters) {
-    constexpr int K = 1 << BITS;
+    constexpr int K = 1 << BITS, SETS = K / 4;                       // boundaries are evaluated four at a time
+    constexpr int V = KmeansShape<BITS, T>::V, NB = KmeansShape<BITS, T>::NB, NBT = NB / T, NWAVES = T / 64;
     extern __shared__ __align__(16) char smem[];
-    u32* A = reinterpret_cast<u32*>(smem);                           // [N]; NP (the next power of two) only bounds the sort's merges
-    const int NC = N / 64;
-    u64* c0 = reinterpret_cast<u64*>(A + N);                        // [NC + 1] running sum of s in front of chunk c
-    u64* clo = c0 + (NC + 1);                                        // low words of s * w * 2^24
-    u64* chi = clo + (NC + 1);                                       // high words (two's complement)
-    __shared__ u64 F0[K + 1], Flo[K + 1], Fhi[K + 1];
-    __shared__ float cen[K], thr2[K];
-    __shared__ i64 cfix[K];
-    __shared__ int scan[T], pos[K + 1], prevpos[K + 1], flag;
+    const int NC = N / 16;
+    u32* A = reinterpret_cast<u32*>(smem);                           // [N] words by bucket
+    i64* C1 = reinterpret_cast<i64*>(A + N);                         // [NC + 1] (narrow) or [2 (NC + 1)] (wide): sum of s w 2^24 in front of chunk c
+    u32* C0 = reinterpret_cast<u32*>(C1 + 2 * (NC + 1));             // [NC + 1] sum of s in front of chunk c
+    u32* start = C0 + (NC + 1);                                      // [NB + 1] first place of every bucket; counts before the scan
+    start += (4 - ((reinterpret_cast<size_t>(start) >> 2) & 3)) & 3;
+    u32* emask = A;                                                  // bit j: weight j is extracted (A is filled after its last use)
+    __shared__ u32 wsum[NWAVES];
+    __shared__ i64 wmom[2 * NWAVES];
+    __shared__ u32 kmm[2];
+    __shared__ u32 Fs0[2][K + 1];
+    __shared__ i64 Fs1[4 * (K + 1)];
+    __shared__ int moved[2][SETS];
+    __shared__ float cen_s[K];
+    __shared__ u32 kt[K];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, row = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), row = blockIdx.x;
+    const int n = lane & 15, q = lane >> 4;
     const u32 key_min = ws[kWsThr], key_max = ws[kWsThr + 1], s_thr = ws[kWsThr + 2];
     const uint16_t* __restrict__ wrow = w + (size_t)row * N;
-    const uint16_t* __restrict__ srow = sens + (size_t)row * N;
+    const int units = N / 8;
 
-    // ---- 1. the row into LDS as sortable words; extracted positions become 0xFFFFFFFF
+    // ---- 1. the row into registers; extracted weights become 0xFFFFFFFF
+    u32 word[V][8];
     {
         const u32x4* wr = reinterpret_cast<const u32x4*>(wrow);
-        const u32x4* sr = reinterpret_cast<const u32x4*>(srow);
-        for (int i = tid; i < N / 8; i += T) {
-            u32 out[8];
-            {
-                const u32x4 wv = wr[i], sv = sr[i];
-                const u32 wd[4] = {wv.x, wv.y, wv.z, wv.w}, sd[4] = {sv.x, sv.y, sv.z, sv.w};
+        const u32x4* sr = reinterpret_cast<const u32x4*>(sens + (size_t)row * N);
+        u32x4 wv[V], sv[V];
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const u32 w0 = wd[k] & 0xFFFFu, w1 = wd[k] >> 16, s0 = sd[k] & 0xFFFFu, s1 = sd[k] >> 16;
-                    out[2 * k] = is_extracted(w0, s0, key_min, key_max, s_thr) ? 0xFFFFFFFFu : (half_key(w0) << 16) | s0;
-                    out[2 * k + 1] = is_extracted(w1, s1, key_min, key_max, s_thr) ? 0xFFFFFFFFu : (half_key(w1) << 16) | s1;
-                }
-            }
-            reinterpret_cast<u32x4*>(A)[2 * i] = u32x4{out[0], out[1], out[2], out[3]};
-            reinterpret_cast<u32x4*>(A)[2 * i + 1] = u32x4{out[4], out[5], out[6], out[7]};
+        for (int v = 0; v < V; ++v) {
+            const int i = min(tid + T * v, units - 1);
+            wv[v] = wr[i]; sv[v] = sr[i];
         }
+        for (int b = tid; b < NB; b += T) start[b] = 0;
+        if (tid == 0) { kmm[0] = 0xFFFFu; kmm[1] = 0; start[NB] = 0; }
+        u32 kmin = 0xFFFFu, kmax = 0;
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            const bool live = tid + T * v < units;
+            const u32 wd[4] = {wv[v].x, wv[v].y, wv[v].z, wv[v].w}, sd[4] = {sv[v].x, sv[v].y, sv[v].z, sv[v].w};
+            u32 mask = 0;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const u32 wb = (e & 1) ? wd[e >> 1] >> 16 : wd[e >> 1] & 0xFFFFu, sb = (e & 1) ? sd[e >> 1] >> 16 : sd[e >> 1] & 0xFFFFu;
+                const u32 key = half_key(wb);
+                const bool out = !live || key < key_min || key > key_max || sb > s_thr;
+                word[v][e] = out ? 0xFFFFFFFFu : (key << 16) | sb;
+                mask |= (out ? 1u : 0u) << e;
+                kmin = umin(kmin, out ? 0xFFFFu : key);
+                kmax = umax(kmax, out ? 0u : key);
+            }
+            if (live) reinterpret_cast<uint8_t*>(emask)[tid + T * v] = (uint8_t)mask;
+        }
+        __syncthreads();
+#define SQ_MINMAX(CTRL, MASK) { kmin = umin(kmin, dpp_u32<CTRL, MASK>(0xFFFFu, kmin)); kmax = umax(kmax, dpp_u32<CTRL, MASK>(0u, kmax)); }
+        SQ_MINMAX(kQuadXor1, 0xF) SQ_MINMAX(kQuadXor2, 0xF) SQ_MINMAX(kRowHalfMirror, 0xF) SQ_MINMAX(kRowMirror, 0xF)
+        SQ_MINMAX(kRowBcast15, 0xA) SQ_MINMAX(kRowBcast31, 0xC)
+#undef SQ_MINMAX
+        if (lane == 63) { atomicMin(&kmm[0], kmin); atomicMax(&kmm[1], kmax); }
     }
     __syncthreads();
+    const u32 kmin = (u32)__builtin_amdgcn_readfirstlane((int)kmm[0]), kmax = (u32)__builtin_amdgcn_readfirstlane((int)kmm[1]);   // kmax < kmin: no dense weight
+    const u32 range = kmax >= kmin ? kmax - kmin : 0u;
+    const int shift = max(0, 32 - __builtin_clz(range | 1u) - KmeansShape<BITS, T>::kMinLog);
 
-    // ---- 2. CSR entries of the row, columns ascending: thread t owns the columns [t C, (t + 1) C)
-    const int C = (N + T - 1) / T;
-    const int jb = min(tid * C, N), je = min(jb + C, N);
-    int mine = 0;
-    for (int j = jb; j < je; ++j) mine += A[j] == 0xFFFFFFFFu;
-    scan[tid] = mine;
+    // ---- 2. count the buckets; the count before gives a word its place
+    uint16_t rank[V][8];
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (word[v][e] != 0xFFFFFFFFu) rank[v][e] = (uint16_t)atomicAdd(&start[((word[v][e] >> 16) - kmin) >> shift], 1u);
+    const u32 ext = tid < N / 32 ? emask[tid] : 0u;
     __syncthreads();
-    for (int off = 1; off < T; off <<= 1) {
-        const int v = tid >= off ? scan[tid - off] : 0;
-        __syncthreads();
-        scan[tid] += v;
-        __syncthreads();
-    }
-    const int n_dense = N - scan[T - 1];
+    // ---- 3. one scan over the threads for the places of the buckets (low half) and of the CSR entries (high half); both are below 2^15
+    int n_dense;
     {
-        int o = rowptr[row] + scan[tid] - mine;
-        for (int j = jb; j < je; ++j)
-            if (A[j] == 0xFFFFFFFFu) { cols[o] = j; vals[o] = wrow[j]; ++o; }
-    }
-    __syncthreads();
-
-    // ---- 3. sort, ascending (see sort_block_steps): only the first N words take part; distances >= 16 go through LDS,
-    //         one step per barrier
-    for (int blk = tid; blk < N / 16; blk += T) sort_block_steps<true>(A, blk);       // merges k = 2 .. 16
-    __syncthreads();
-    // Steps with distances >= 16 through LDS.  A thread takes four NEIGHBOURING comparators at a time -- their lower words
-    // are one 16-byte chunk and so are their upper words (in reverse order for the mirror step) -- and kSortBatch such
-    // quads per round: all loads, then all stores.  Index arithmetic, LDS instructions and round trips are shared by four
-    // comparators, and the 16-byte accesses of neighbouring lanes are conflict-free.
-    constexpr int kSortBatch = 2;
-    auto lds_step = [&](auto quad_of, bool mirror) {
-        for (int g0 = tid; g0 < NP / 8; g0 += kSortBatch * T) {
-            int a[kSortBatch], b[kSortBatch];
-            u32x4 va[kSortBatch], vb[kSortBatch];
-            bool live[kSortBatch];
+        u32 cnt[NBT], mine = 0;
 #pragma unroll
-            for (int u = 0; u < kSortBatch; ++u) {
-                quad_of(4 * (g0 + u * T), a[u], b[u]);                   // first words of the two chunks (multiples of 4)
-                live[u] = g0 + u * T < NP / 8 && b[u] < N;               // a < b always; N is a multiple of 4
-                if (live[u]) { va[u] = *reinterpret_cast<const u32x4*>(A + a[u]); vb[u] = *reinterpret_cast<const u32x4*>(A + b[u]); }
-            }
+        for (int k = 0; k < NBT; ++k) { cnt[k] = start[tid * NBT + k]; mine += cnt[k]; }
+        mine |= (u32)__builtin_popcount(ext) << 16;
+        const Plain inc = wave_scan(Plain{mine});
+        if (lane == 63) wsum[wave] = inc.v;
+        __syncthreads();
+        u32 before = inc.v - mine, total = 0;
 #pragma unroll
-            for (int u = 0; u < kSortBatch; ++u) {
-                if (live[u]) {
-                    const u32x4 x = va[u];
-                    const u32x4 y = mirror ? u32x4{vb[u].w, vb[u].z, vb[u].y, vb[u].x} : vb[u];
-                    const u32x4 lo = {umin(x.x, y.x), umin(x.y, y.y), umin(x.z, y.z), umin(x.w, y.w)};
-                    const u32x4 hi = {umax(x.x, y.x), umax(x.y, y.y), umax(x.z, y.z), umax(x.w, y.w)};
-                    *reinterpret_cast<u32x4*>(A + a[u]) = lo;
-                    *reinterpret_cast<u32x4*>(A + b[u]) = mirror ? u32x4{hi.w, hi.z, hi.y, hi.x} : hi;
-                }
-            }
-            if (a[0] >= N) break;                                        // a grows with the quad index
+        for (int k = 0; k < NWAVES; ++k) {
+            const u32 t = wsum[k];
+            before += k < wave ? t : 0u;
+            total += t;
         }
-        __syncthreads();
-    };
-    for (int k = 32; k <= NP; k <<= 1) {
-        const int hk = k >> 1;
-        // mirror step: word off of the lower half against word k - 1 - off of the upper half of every group of k; the four
-        // partners of the words off .. off + 3 are the chunk that starts at k - 4 - off, read backwards
-        lds_step([&](int i, int& a, int& b) { const int base = (i / hk) * k, off = i & (hk - 1); a = base + off; b = base + k - 4 - off; }, true);
-        for (int j = k >> 2; j >= 16; j >>= 1)
-            lds_step([&](int i, int& a, int& b) { a = 2 * i - (i & (j - 1)); b = a + j; }, false);
-        for (int blk = tid; blk < N / 16; blk += T) sort_block_steps<false>(A, blk);  // half-cleaners 8, 4, 2, 1
-        __syncthreads();
-    }
-
-    // ---- 4. running sums in front of every chunk of 64 sorted weights
-    const int nchunks = (n_dense + 63) / 64;
-    for (int c = wave; c < nchunks; c += T / 64) {
-        const int j = c * 64 + lane;
-        u32 sv = 0;
-        i64 p = 0;
-        if (j < n_dense) {
-            const u32 v = A[j];
-            sv = v & 0xFFFFu;
-            p = (i64)sv * half_to_fixed(key_half(v >> 16));
+        n_dense = (int)(total & 0xFFFFu);
+        u32 run = before & 0xFFFFu;
+#pragma unroll
+        for (int k = 0; k < NBT; ++k) { start[tid * NBT + k] = run; run += cnt[k]; }
+        if (tid == 0) start[NB] = (u32)n_dense;
+        // CSR entries of the row, columns ascending
+        int o = rowptr[row] + (int)(before >> 16);
+        for (u32 m = ext; m; m &= m - 1) {
+            const int j = 32 * tid + __builtin_ctz(m);
+            cols[o] = j;
+            vals[o] = wrow[j];
+            ++o;
         }
-        u64 s0, lo, hi;
-        wave_sums(sv, p, s0, lo, hi);
-        if (lane == 0) { c0[c + 1] = s0; clo[c + 1] = lo; chi[c + 1] = hi; }
     }
     __syncthreads();
-    if (wave == 0) {
-        // running sums over the chunks: every lane of wave 0 takes a run of consecutive chunks, the runs are chained with
-        // a prefix sum across the lanes
-        const int per = (nchunks + 63) / 64;
-        const int cb = min(1 + lane * per, nchunks + 1), ce = min(cb + per, nchunks + 1);
-        u64 t0 = 0, tl = 0, th = 0;
-        for (int c = cb; c < ce; ++c) { t0 += c0[c]; tl += clo[c]; th += chi[c]; }
-        u64 p0 = t0, pl = tl, ph = th;
-        for (int off = 1; off < 64; off <<= 1) {
-            const u64 u0 = (u64)__shfl_up((long long)p0, off, 64), ul = (u64)__shfl_up((long long)pl, off, 64), uh = (u64)__shfl_up((long long)ph, off, 64);
-            if (lane >= off) { p0 += u0; pl += ul; ph += uh; }
-        }
-        u64 r0 = p0 - t0, rl = pl - tl, rh = ph - th;                    // sums in front of the lane's run
-        for (int c = cb; c < ce; ++c) { r0 += c0[c]; rl += clo[c]; rh += chi[c]; c0[c] = r0; clo[c] = rl; chi[c] = rh; }
-        if (lane == 0) { c0[0] = 0; clo[0] = 0; chi[0] = 0; }
-    }
-    // ---- 5. equal-count start
-    if (tid < K) {
-        const u64 rank = ((u64)(2 * tid + 1) * (u64)n_dense) / (u64)(2 * K);
-        cen[tid] = n_dense > 0 ? half_bits_to_f32(key_half(A[rank] >> 16)) : 0.f;
-    }
-    if (tid <= K) prevpos[tid] = -1;
+    // ---- 4. the words by bucket
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (word[v][e] != 0xFFFFFFFFu) A[start[((word[v][e] >> 16) - kmin) >> shift] + rank[v][e]] = word[v][e];
     __syncthreads();
 
-    // ---- 6. Lloyd iterations on the boundaries
     int it = 0;
-    if (n_dense > 0) {
-        for (;;) {
-            if (tid < K - 1) thr2[tid] = __fadd_rn(cen[tid], cen[tid + 1]);
-            if (tid == 0) flag = 0;
-            __syncthreads();
-            for (int k = wave; k < K - 1; k += T / 64) {                 // uniform per wave
-                const float t = thr2[k];
-                // p = #{ j < n_dense : 2 w_j <= t }: rounds of 64 probes; invariant: the answer lies in [lo, lo + len]
-                int lo = 0, len = n_dense;
-                while (len > 0) {
-                    const int step = (len + 63) / 64;                    // probe positions lo + step (l + 1) - 1
-                    const int j = lo + step * (lane + 1) - 1;
-                    bool le = false;
-                    if (j < lo + len) le = !(t < 2.0f * half_bits_to_f32(key_half(A[j] >> 16)));
-                    const int cnt = __builtin_popcountll(__ballot(le));  // probes with 2 w <= t form a prefix
-                    lo += cnt * step;
-                    len = min(step - 1, n_dense - lo);                   // the next probe after the prefix is > t (or past the end)
-                    if (len < 0) len = 0;
+    auto solve = [&](auto wide) {
+        constexpr bool WIDE = decltype(wide)::value;
+        typedef Moment<WIDE> Mom;
+        Mom* C = reinterpret_cast<Mom*>(C1);
+        Mom* F1 = reinterpret_cast<Mom*>(Fs1);
+        Mom* wm = reinterpret_cast<Mom*>(wmom);
+        // ---- 5. sums in front of every chunk of 16 words; thread t owns the chunks t CT ..
+        constexpr int CT = V == 2 ? 1 : 2;
+        const int nchunks = (n_dense + 15) >> 4;
+        {
+            u32 s0[CT];
+            Mom s1[CT];
+            u32 t0 = 0;
+            Mom t1 = Mom::zero();
+#pragma unroll
+            for (int k = 0; k < CT; ++k) {
+                const int c = tid * CT + k;
+                s0[k] = 0; s1[k] = Mom::zero();
+                if (c < nchunks) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int j = 16 * c + 4 * ((i + tid) & 3);  // a rotated order: neighbouring threads read different banks
+                        const u32x4 v4 = *reinterpret_cast<const u32x4*>(A + j);
+                        const u32 vv[4] = {v4.x, v4.y, v4.z, v4.w};
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (j + e < n_dense) { s0[k] += vv[e] & 0xFFFFu; s1[k] = s1[k] + Mom::product(vv[e]); }
+                    }
                 }
-                const int p = lo;
-                const int c = p >> 6, inside = p & 63;
-                u32 sv = 0;
-                i64 pr = 0;
-                if (lane < inside) {
-                    const u32 v = A[c * 64 + lane];
-                    sv = v & 0xFFFFu;
-                    pr = (i64)sv * half_to_fixed(key_half(v >> 16));
-                }
-                u64 s0, l, h;
-                wave_sums(sv, pr, s0, l, h);
-                if (lane == 0) {
-                    pos[k + 1] = p; F0[k + 1] = c0[c] + s0; Flo[k + 1] = clo[c] + l; Fhi[k + 1] = chi[c] + h;
-                    if (p != prevpos[k + 1]) flag = 1;
-                }
+                t0 += s0[k]; t1 = t1 + s1[k];
             }
-            if (tid == 0) {
-                pos[0] = 0; F0[0] = 0; Flo[0] = 0; Fhi[0] = 0;
-                pos[K] = n_dense; F0[K] = c0[nchunks]; Flo[K] = clo[nchunks]; Fhi[K] = chi[nchunks];
-            }
+            const Plain i0 = wave_scan(Plain{t0});
+            const Mom i1 = wave_scan(t1);
+            if (lane == 63) { wsum[wave] = i0.v; wm[wave] = i1; }
             __syncthreads();
-            const bool stop = flag == 0 || it == max_iter;
-            if (!stop && tid < K) {
-                const u64 s0 = F0[tid + 1] - F0[tid];
-                if (s0 > 0) {
-                    const double s1 = (double)(i64)(Fhi[tid + 1] - Fhi[tid]) * 4294967296.0 + (double)(Flo[tid + 1] - Flo[tid]);
-                    cen[tid] = (float)(s1 * 5.9604644775390625e-08 / (double)s0);
+            u32 b0 = i0.v - t0;
+            Mom b1 = i1 - t1;
+            for (int k = 0; k < wave; ++k) { b0 += wsum[k]; b1 = b1 + wm[k]; }   // uniform
+#pragma unroll
+            for (int k = 0; k < CT; ++k) {
+                const int c = tid * CT + k;
+                if (c <= NC) { C0[c] = b0; C[c] = b1; }
+                b0 += s0[k]; b1 = b1 + s1[k];
+            }
+            if (tid == T - 1 && CT * T == NC) { C0[NC] = b0; C[NC] = b1; }
+        }
+        __syncthreads();
+        // ---- 6. equal-count start: the weight of rank r lies in the last bucket that starts at or before r; its key is found bit by bit.
+        //         Wave s < SETS finds the centroids 4 s .. 4 s + 3, one per group of 16 lanes.
+        const int k0 = 4 * wave + q;
+        if (wave < SETS) {
+            const int r = (int)(((u64)(2 * k0 + 1) * (u64)n_dense) / (u64)(2 * K));
+            int lo = 0, hi = NB;                                     // start[lo] <= r < start[hi]
+            while (hi - lo > 1) {                                    // the same number of rounds in every lane
+                const int mid = (lo + hi) >> 1;
+                if ((int)start[mid] <= r) lo = mid; else hi = mid;
+            }
+            const int p0 = (int)start[lo], p1 = (int)start[lo + 1];
+            u32 key = kmin + ((u32)lo << shift);
+            for (int b = shift - 1; b >= 0; --b) {
+                const u32 cand = key + (1u << b);                    // no more than r - p0 words below cand: the key is cand or above
+                int below = 0;
+                for (int j0 = p0; __any(j0 < p1); j0 += 16) {
+                    const int j = j0 + n;
+                    const bool in = j < p1 && (A[min(j, N - 1)] >> 16) < cand;
+                    const u64 m = __ballot(in);
+                    below += __builtin_popcount((u32)(m >> (16 * q)) & 0xFFFFu);
                 }
+                if (below <= r - p0) key = cand;
             }
-            if (tid <= K) prevpos[tid] = pos[tid];
+            if (n == 0) cen_s[k0] = half_bits_to_f32(key_half(key));
+        }
+        if (tid < 2) {
+            Fs0[tid][0] = 0; F1[tid * (K + 1)] = Mom::zero();
+            Fs0[tid][K] = C0[nchunks]; F1[tid * (K + 1) + K] = C[nchunks];
+        }
+        __syncthreads();
+        // ---- 7. Lloyd iterations: wave s < SETS evaluates the boundaries 4 s .. 4 s + 3; every such wave then forms all centroids.
+        //         The sums of two successive iterations use different arrays, so one barrier per iteration is enough.
+        float cen = n < K ? cen_s[n] : 0.f;                          // lane (n, q): centroid n
+        int prev = -1;
+        for (int par = 0;; par ^= 1) {
+            if (wave < SETS) {                                       // uniform
+                const float next = __builtin_bit_cast(float, dpp_u32<kRowShl1>(0u, __builtin_bit_cast(u32, cen)));
+                const float thr = __fadd_rn(cen, next);              // lane n: twice the boundary above centroid n
+                const float t = __shfl(thr, 16 * q + min(k0, K - 2));
+                const u32 kk = key_below(t);
+                const int b = kk < kmin ? -1 : (int)min((kk - kmin) >> shift, (u32)(NB - 1));
+                const int p0 = b < 0 ? 0 : (int)start[max(b, 0)], p1 = b < 0 ? 0 : (int)start[max(b, 0) + 1];
+                const u32 kkw = (kk << 16) | 0xFFFFu;
+                const int j0 = p0 & ~15;
+                const u32 c0 = C0[j0 >> 4];
+                const Mom c1 = C[j0 >> 4];
+                int pos = j0;
+                u32 s0 = 0;
+                Mom s1 = Mom::zero();
+                for (int j1 = j0; __any(j1 < p1); j1 += 32) {
+                    const int ja = j1 + n, jb = ja + 16;
+                    const u32 va = A[min(ja, N - 1)], vb = A[min(jb, N - 1)];
+                    const bool ina = ja < p1 && (ja < p0 || va <= kkw), inb = jb < p1 && vb <= kkw;   // jb >= p0
+                    const u64 ma = __ballot(ina), mb = __ballot(inb);
+                    pos += __builtin_popcount((u32)(ma >> (16 * q)) & 0xFFFFu) + __builtin_popcount((u32)(mb >> (16 * q)) & 0xFFFFu);
+                    const u32 za = ina ? va : 0x80000000u, zb = inb ? vb : 0x80000000u;   // +0 with sensitivity 0
+                    s0 += (za & 0xFFFFu) + (zb & 0xFFFFu);
+                    s1 = s1 + Mom::product(za) + Mom::product(zb);
+                }
+                s0 = row16_sum(Plain{s0}).v + c0;
+                s1 = row16_sum(s1) + c1;
+                if (n == 0 && k0 < K - 1) { Fs0[par][k0 + 1] = s0; F1[par * (K + 1) + k0 + 1] = s1; }
+                const bool any = __any(k0 < K - 1 && pos != prev);
+                if (lane == 0) moved[par][wave] = any ? 1 : 0;
+                prev = pos;
+            }
             __syncthreads();
-            if (stop) break;
+            int any = 0;
+#pragma unroll
+            for (int k = 0; k < SETS; ++k) any |= moved[par][k];
+            if (any == 0 || it == max_iter) break;                   // uniform
+            if (wave < SETS && n < K) {
+                const u32 m0 = Fs0[par][n + 1] - Fs0[par][n];
+                const Mom m1 = F1[par * (K + 1) + n + 1] - F1[par * (K + 1) + n];
+                if (m0 > 0) cen = (float)(m1.value() * 5.9604644775390625e-08 / (double)m0);
+            }
             ++it;
         }
+        if (tid < K) cen_s[tid] = cen;
+    };
+    if (n_dense > 0) {
+        if (kmax >= 0xD800u || kmin <= 0x27FFu) solve(std::integral_constant<bool, true>{});    // |w| >= 128 somewhere
+        else solve(std::integral_constant<bool, false>{});
+    } else if (tid < K) {
+        cen_s[tid] = 0.f;
     }
-
-    // ---- 7. fp16 tables; final indices from the row as it lies in memory, packed 32 per thread
+    // ---- 8. fp16 tables; an index is the number of boundaries between table entries below the weight, as keys
+    __syncthreads();
     if (tid < K) {
-        const uint16_t hb = __builtin_bit_cast(uint16_t, (_Float16)cen[tid]);
+        const uint16_t hb = __builtin_bit_cast(uint16_t, (_Float16)cen_s[tid]);
         lut[(size_t)row * K + tid] = hb;
-        cfix[tid] = half_to_fixed(hb);
+        if (tid < K - 1) {
+            const uint16_t hn = __builtin_bit_cast(uint16_t, (_Float16)cen_s[tid + 1]);
+            const i64 t = half_to_fixed(hb) + half_to_fixed(hn);     // largest key with 2 w 2^24 <= t
+            typedef __fp16 fp16x2 __attribute__((ext_vector_type(2)));
+            const fp16x2 h = __builtin_amdgcn_cvt_pkrtz((float)((double)t * 2.98023223876953125e-08), 0.f);
+            u32 k = half_key(__builtin_bit_cast(u32, h) & 0xFFFFu);
+            if (2 * half_to_fixed(key_half(k)) > t) --k;
+            if (k < 0xFBFFu && 2 * half_to_fixed(key_half(k + 1)) <= t) ++k;
+            kt[tid] = k;
+        }
     }
-    if (tid == 0 && iters) iters[row] = it;
+    if (tid == 0 && iters) iters[row] = it;                          // thread 0 is in the wave that iterated
     __syncthreads();
     {
-        i64 tf[K - 1];
+        u32 bound[K - 1];
 #pragma unroll
-        for (int k = 0; k < K - 1; ++k) tf[k] = cfix[k] + cfix[k + 1];
+        for (int k = 0; k < K - 1; ++k) bound[k] = ((u32)__builtin_amdgcn_readfirstlane((int)kt[k]) << 16) | 0xFFFFu;
         u32 zero = 0;
-        i64 best = cfix[0] < 0 ? -cfix[0] : cfix[0];
+        i64 best = 0;
 #pragma unroll
-        for (int k = 1; k < K; ++k) {
-            const i64 a = cfix[k] < 0 ? -cfix[k] : cfix[k];
-            if (a < best) { best = a; zero = k; }
+        for (int k = 0; k < K; ++k) {
+            const i64 f = half_to_fixed((u32)__builtin_bit_cast(uint16_t, (_Float16)cen_s[k]));
+            const i64 a = f < 0 ? -f : f;
+            if (k == 0 || a < best) { best = a; zero = k; }
         }
-        u32* out = static_cast<u32*>(qidx) + (size_t)row * ((size_t)N * BITS / 32);
-        for (int ch = tid; ch < N / 32; ch += T) {
-            u32 q[BITS];
 #pragma unroll
-            for (int k = 0; k < BITS; ++k) q[k] = 0;
+        for (int v = 0; v < V; ++v) {
+            const int i = tid + T * v;
+            if (i >= units) continue;                                // whole quads of lanes
+            u32 packed = 0;
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const u32x4 wv = reinterpret_cast<const u32x4*>(wrow + ch * 32)[g], sv = reinterpret_cast<const u32x4*>(srow + ch * 32)[g];
-                const u32 wd[4] = {wv.x, wv.y, wv.z, wv.w}, sd[4] = {sv.x, sv.y, sv.z, sv.w};
+            for (int e = 0; e < 8; ++e) {
+                u32 a = 0;
 #pragma unroll
-                for (int e8 = 0; e8 < 8; ++e8) {
-                    const u32 wb = (e8 & 1) ? wd[e8 >> 1] >> 16 : wd[e8 >> 1] & 0xFFFFu;
-                    const u32 sb = (e8 & 1) ? sd[e8 >> 1] >> 16 : sd[e8 >> 1] & 0xFFFFu;
-                    u32 a = zero;
-                    if (!is_extracted(wb, sb, key_min, key_max, s_thr)) {
-                        const i64 w2 = 2 * half_to_fixed(wb);
-                        a = 0;
-#pragma unroll
-                        for (int k = 0; k < K - 1; ++k) a += tf[k] < w2;
-                    }
-                    const int e = g * 8 + e8, bitpos = e * BITS;
-                    q[bitpos >> 5] |= a << (bitpos & 31);
-                    if ((bitpos & 31) + BITS > 32) q[(bitpos >> 5) + 1] |= a >> (32 - (bitpos & 31));
-                }
+                for (int k = 0; k < K - 1; ++k) a += word[v][e] > bound[k] ? 1u : 0u;
+                packed |= (word[v][e] == 0xFFFFFFFFu ? zero : a) << (BITS * e);
             }
-#pragma unroll
-            for (int k = 0; k < BITS; ++k) out[(size_t)ch * BITS + k] = q[k];
+            if constexpr (BITS == 2) {
+                static_cast<uint16_t*>(qidx)[(size_t)row * units + i] = (uint16_t)packed;
+            } else if constexpr (BITS == 4) {
+                static_cast<u32*>(qidx)[(size_t)row * units + i] = packed;
+            } else {
+                // four lanes hold 24 bits each: lane l of the quad writes dword l of the three
+                const u32 up = dpp_u32<0x39>(0u, packed);            // quad_perm [1,2,3,0]
+                const int l = lane & 3;
+                const u32 d = (packed >> (8 * l)) | (up << (24 - 8 * l));
+                if (l < 3) static_cast<u32*>(qidx)[((size_t)row * units + (i & ~3)) / 4 * 3 + l] = d;
+            }
         }
     }
 }
@@ -558,20 +644,15 @@ hipError_t launch_quantize(const QuantArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(quant_select2_kernel, dim3(1), dim3(256), 0, s, ws);
     hipLaunchKernelGGL(quant_count_kernel, dim3((a.M + 3) / 4), dim3(256), 0, s, a.M, a.N, static_cast<const uint16_t*>(a.w), static_cast<const uint16_t*>(a.sens), ws, a.rowptr);
     hipLaunchKernelGGL(quant_scan_kernel, dim3(1), dim3(1024), 0, s, a.M, a.rowptr);
-    int NP = 128;
-    while (NP < a.N) NP <<= 1;
-    const size_t lds = (size_t)a.N * 4 + (size_t)(a.N / 64 + 1) * 24;
-    // Threads per row by the row's LDS footprint (the kernel is bound by LDS and barrier latency, so it wants 16 or more
-    // waves per compute unit): 256 up to 4096 weights (eight workgroups per unit), 512 up to 16384 (2-4 workgroups), 1024
-    // beyond (one).  Measured: 4096x11008 2.24 -> 1.79 ms and 8192x8192 2.30 -> 2.08 ms with 512 instead of 256 threads,
-    // 8192x22016 9.95 -> 8.39 ms with 1024 instead of 512; 4096x4096 0.61 -> 0.67 ms with 512 (so 256 there).
-    auto go = [](auto kernel) { return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024); };
+    // Threads per row by the row's LDS footprint (26 KB at 4096 weights, 66 KB at 11008, 159 KB at 28672, so six, two and one row per
+    // compute unit at a time): the iterations of a row are one chain of dependent steps, the other waves of the unit fill the gaps.
+    auto go = [](auto kernel, size_t lds) { return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); };
     const int threads = a.N > 16384 ? 1024 : (a.N > 4096 ? 512 : 256);
 #define SQ_LAUNCH_KMEANS(B_, T_)                                                                                                     \
     {                                                                                                                                \
-        static bool enabled = false;                                                                                                 \
-        if (!enabled) { const hipError_t e = go(&quant_kmeans_kernel<B_, T_>); if (e != hipSuccess) return e; enabled = true; }      \
-        hipLaunchKernelGGL((quant_kmeans_kernel<B_, T_>), dim3(a.M), dim3(T_), lds, s, a.M, a.N, NP, a.max_iter,                       \
+        const hipError_t e = go(&quant_kmeans_kernel<B_, T_>, kmeans_lds(KmeansShape<B_, T_>::kMaxN, KmeansShape<B_, T_>::NB));      \
+        if (e != hipSuccess) return e;                                                                                               \
+        hipLaunchKernelGGL((quant_kmeans_kernel<B_, T_>), dim3(a.M), dim3(T_), kmeans_lds(a.N, KmeansShape<B_, T_>::NB), s, a.M, a.N, a.max_iter, \
                            static_cast<const uint16_t*>(a.w), static_cast<const uint16_t*>(a.sens), ws, a.rowptr, a.qidx,           \
                            static_cast<uint16_t*>(a.lut), a.cols, static_cast<uint16_t*>(a.vals), a.iters);                         \
     }
