@@ -39,107 +39,164 @@ __device__ __forceinline__ i64 half_to_fixed(u32 h) {
     return (h & 0x8000u) ? -mag : mag;
 }
 
-// Workspace layout (32-bit words)
-constexpr int kWsHist1W = 0, kWsHist1S = 256, kWsHist2 = 512 /* 3 x 256 */, kWsSel = 1280 /* 3 x (bin, residual lo, residual hi) + pad */,
-              kWsThr = 1296 /* key_min, key_max, s_thr */, kWsWords = 1312;
+__device__ __forceinline__ u32 umin(u32 a, u32 b) { return a < b ? a : b; }
+__device__ __forceinline__ u32 umax(u32 a, u32 b) { return a < b ? b : a; }
+template <int CTRL, int ROW_MASK = 0xF>
+__device__ __forceinline__ u32 dpp_u32(u32 old, u32 v) { return (u32)__builtin_amdgcn_update_dpp((int)old, (int)v, CTRL, ROW_MASK, 0xF, false); }
+constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kRowHalfMirror = 0x141, kRowMirror = 0x140;
+constexpr int kRowShl1 = 0x101, kRowShr1 = 0x111, kRowShr2 = 0x112, kRowShr4 = 0x114, kRowShr8 = 0x118, kRowBcast15 = 0x142, kRowBcast31 = 0x143;
+struct Plain {                                                       // a 32-bit count or sum
+    u32 v;
+    __device__ __forceinline__ Plain operator+(const Plain& o) const { return {v + o.v}; }
+    template <int CTRL, int ROW_MASK = 0xF>
+    __device__ __forceinline__ Plain moved() const { return {dpp_u32<CTRL, ROW_MASK>(0, v)}; }
+};
+// sum over each row of 16 lanes, in all its lanes
+template <class T>
+__device__ __forceinline__ T row16_sum(T v) {
+    v = v + v.template moved<kQuadXor1>();
+    v = v + v.template moved<kQuadXor2>();
+    v = v + v.template moved<kRowHalfMirror>();
+    v = v + v.template moved<kRowMirror>();
+    return v;
+}
+// inclusive prefix sum over the 64 lanes
+template <class T>
+__device__ __forceinline__ T wave_scan(T v) {
+    v = v + v.template moved<kRowShr1>();
+    v = v + v.template moved<kRowShr2>();
+    v = v + v.template moved<kRowShr4>();
+    v = v + v.template moved<kRowShr8>();
+    v = v + v.template moved<kRowBcast15, 0xA>();
+    v = v + v.template moved<kRowBcast31, 0xC>();
+    return v;
+}
+
+// ---------------------------------------------------------------------------------------------- thresholds and row pointers
+// Workspace layout (32-bit words).  Bins are the RAW bytes of the fp16 patterns and of the sensitivities; the order of the keys is
+// applied when a rank is looked up.
+constexpr int kWsHist1W = 0, kWsHist1S = 256, kWsHist2 = 512 /* 3 x 256 */, kWsSel = 1280 /* 3 x (raw bin, residual rank) */,
+              kWsThr = 1296 /* key_min, key_max, s_thr */, kWsDone = 1300 /* blocks finished: hist1, hist2, count */, kWsWords = 1312;
+constexpr int kPassThreads = 1024, kPassBlocks = 256;                // a pass over the matrix: one block per compute unit
 
 __global__ void __launch_bounds__(256) quant_clear_kernel(u32* ws) {
     for (int i = threadIdx.x + blockIdx.x * blockDim.x; i < kWsWords; i += blockDim.x * gridDim.x) ws[i] = 0;
 }
 
-// pass 1: histograms of the high bytes of all weight keys and of all sensitivities
-__global__ void __launch_bounds__(256) quant_hist1_kernel(long long units, const u32x4* __restrict__ w, const u32x4* __restrict__ s, u32* __restrict__ ws) {
-    // eight copies of each histogram, picked by the lane, so that the lanes of a wave seldom add to one address
-    __shared__ u32 hw8[8][256], hs8[8][256];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) { hw8[c][threadIdx.x] = 0; hs8[c][threadIdx.x] = 0; }
-    u32* hw = hw8[threadIdx.x & 7];
-    u32* hs = hs8[threadIdx.x & 7];
+__device__ __forceinline__ u32 load_shared(const u32* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// The last block of a launch to come here.  What the blocks hand over is written with agent-scope atomics only, so waiting for them to
+// complete before the block is counted is enough: a release at agent scope would write back the caches as well (7 us of a 4096x4096
+// pass).  Called by all threads of the block.
+__device__ __forceinline__ bool last_block(u32* done, u32* flag /* LDS */) {
+    __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < units; i += (long long)gridDim.x * blockDim.x) {
-        const u32x4 wv = w[i], sv = s[i];
-        const u32 wd[4] = {wv.x, wv.y, wv.z, wv.w}, sd[4] = {sv.x, sv.y, sv.z, sv.w};
+    if (threadIdx.x == 0) *flag = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == gridDim.x ? 1u : 0u;
+    __syncthreads();
+    const bool last = *flag != 0;
+    if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    return last;
+}
+// Of 256 bins whose counts the threads 0 .. 255 hold: the bin in which rank r falls and the rank inside it, written by the thread of that
+// bin.  All threads of the block call this; wsum: 4 words of LDS.
+__device__ __forceinline__ void select_bin(u32 mine, u32 r, u32* wsum, u32* bin_out, u32* residual_out, u32 bin) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const u32 inc = wave_scan(Plain{threadIdx.x < 256 ? mine : 0u}).v;
+    if (wave < 4 && lane == 63) wsum[wave] = inc;
+    __syncthreads();
+    u32 before = inc - mine;
+    for (int k = 0; k < wave && k < 4; ++k) before += wsum[k];
+    if (threadIdx.x < 256 && r >= before && r - before < mine) { *bin_out = bin; *residual_out = r - before; }
+    __syncthreads();
+}
+// raw high byte of the weights whose key has high byte t, and back
+__device__ __forceinline__ u32 raw_high(u32 t) { return t & 0x80u ? t & 0x7Fu : ~t & 0xFFu; }
+__device__ __forceinline__ u32 key_high(u32 raw) { return raw & 0x80u ? ~raw & 0xFFu : raw | 0x80u; }
+
+// pass 1: histograms of the high bytes of all weights and of all sensitivities, then the bins that hold the three ranks (by the block
+// that finishes last, instead of in a launch of its own).  Bound by the read of the matrix (67 MB at 4096x4096: 13 us of the 17.5).
+__global__ void __launch_bounds__(kPassThreads) quant_hist1_kernel(long long units, const u32x4* __restrict__ w, const u32x4* __restrict__ s, u32* __restrict__ ws,
+                                                                   u32 r_min, u32 r_max, u32 r_sens) {
+    // 32 copies of each histogram, one per lane of half a wave and each in a bank of its own: counting never waits for a bank, whatever
+    // the data.  256 blocks end with 512 global atomics each.  (Eight copies one after the other, 1024 blocks of 256 threads and a select
+    // kernel behind it: 36 + 4.7 us at 4096x4096, 81 + 4.6 at 4096x11008, against 17.5 and 43.)
+    extern __shared__ __align__(16) u32 h[];                         // [2][256][32]
+    for (int i = threadIdx.x; i < 2 * 256 * 32 / 4; i += kPassThreads) reinterpret_cast<u32x4*>(h)[i] = u32x4{0, 0, 0, 0};
+    __syncthreads();
+    const u32 lane4 = 4u * (threadIdx.x & 31);
+    auto count = [&](const u32x4& v, u32 base) {
+        const u32 d[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            atomicAdd(&hw[half_key(wd[k] & 0xFFFFu) >> 8], 1u); atomicAdd(&hw[half_key(wd[k] >> 16) >> 8], 1u);
-            atomicAdd(&hs[(sd[k] & 0xFFFFu) >> 8], 1u); atomicAdd(&hs[sd[k] >> 24], 1u);
+            // bin * 128 + base from bytes 1 and 3 of the dword
+            atomicAdd(reinterpret_cast<u32*>(reinterpret_cast<char*>(h) + __builtin_amdgcn_udot4(d[k], 128u << 8, base, false)), 1u);
+            atomicAdd(reinterpret_cast<u32*>(reinterpret_cast<char*>(h) + __builtin_amdgcn_udot4(d[k], 128u << 24, base, false)), 1u);
         }
+    };
+    const long long stride = (long long)gridDim.x * kPassThreads;
+    long long i = (long long)blockIdx.x * kPassThreads + threadIdx.x;
+    for (; i + stride < units; i += 2 * stride) {
+        const u32x4 w0 = w[i], s0 = s[i], w1 = w[i + stride], s1 = s[i + stride];
+        count(w0, lane4); count(s0, 256 * 128 + lane4);
+        count(w1, lane4); count(s1, 256 * 128 + lane4);
     }
+    if (i < units) { count(w[i], lane4); count(s[i], 256 * 128 + lane4); }
     __syncthreads();
-    u32 tw = 0, ts = 0;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) { tw += hw8[c][threadIdx.x]; ts += hs8[c][threadIdx.x]; }
-    if (tw) atomicAdd(&ws[kWsHist1W + threadIdx.x], tw);
-    if (ts) atomicAdd(&ws[kWsHist1S + threadIdx.x], ts);
+    if (threadIdx.x < 512) {
+        u32 t = 0;
+#pragma unroll 8
+        for (int c = 0; c < 32; ++c) t += h[threadIdx.x * 32 + ((c + threadIdx.x) & 31)];
+        if (t) __hip_atomic_fetch_add(&ws[kWsHist1W + threadIdx.x], t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (!last_block(&ws[kWsDone], h)) return;
+    __syncthreads();
+    const u32 t = threadIdx.x & 255;
+    const u32 hw = load_shared(&ws[kWsHist1W + raw_high(t)]), hs = load_shared(&ws[kWsHist1S + t]);
+    select_bin(hw, r_min, h, &ws[kWsSel], &ws[kWsSel + 1], raw_high(t));
+    select_bin(hw, r_max, h, &ws[kWsSel + 4], &ws[kWsSel + 5], raw_high(t));
+    select_bin(hs, r_sens, h, &ws[kWsSel + 8], &ws[kWsSel + 9], t);
 }
 
-// Bin holding the element of rank r (0-based) in a 256-bin histogram, and the rank inside that bin; called by all 256
-// threads of the block, thread t owning bin t.  The bin is the one whose running count first exceeds r.
-__device__ __forceinline__ void select_bin(u32 mine, u64 r, u64* scan /* [256] in LDS */, u32& bin, u64& residual) {
-    const int t = threadIdx.x;
-    scan[t] = mine;
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-        const u64 v = t >= off ? scan[t - off] : 0;
-        __syncthreads();
-        scan[t] += v;
-        __syncthreads();
-    }
-    const u64 incl = scan[t], excl = incl - mine;
-    __shared__ u32 sel_bin;
-    __shared__ u64 sel_res;
-    if (t == 0) { sel_bin = 255; sel_res = 0; }                      // rank past the end (cannot happen for valid counts)
-    __syncthreads();
-    if (r >= excl && r < incl) { sel_bin = (u32)t; sel_res = r - excl; }
-    __syncthreads();
-    bin = sel_bin; residual = sel_res;
-    __syncthreads();
-}
-
-__global__ void __launch_bounds__(256) quant_select1_kernel(u64 total, u64 n_lo, u64 n_hi, u64 n_sens, u32* ws) {
-    __shared__ u64 scan[256];
-    const u32 hw = ws[kWsHist1W + threadIdx.x], hs = ws[kWsHist1S + threadIdx.x];
-    for (int t = 0; t < 3; ++t) {
-        const u64 rank = t == 0 ? n_lo : (t == 1 ? total - 1 - n_hi : total - 1 - n_sens);
-        u32 bin; u64 res;
-        select_bin(t < 2 ? hw : hs, rank, scan, bin, res);
-        if (threadIdx.x == 0) { ws[kWsSel + 4 * t] = bin; ws[kWsSel + 4 * t + 1] = (u32)res; ws[kWsSel + 4 * t + 2] = (u32)(res >> 32); }
-    }
-}
-
-// pass 2: histograms of the low bytes inside the three selected bins
-__global__ void __launch_bounds__(256) quant_hist2_kernel(long long units, const u32x4* __restrict__ w, const u32x4* __restrict__ s, u32* __restrict__ ws) {
+// pass 2: histograms of the low bytes inside the three selected bins, then the thresholds (23 + 4.9 us at 4096x4096 with 1024 blocks and a
+// select kernel of its own, against 18)
+__global__ void __launch_bounds__(kPassThreads) quant_hist2_kernel(long long units, const u32x4* __restrict__ w, const u32x4* __restrict__ s, u32* __restrict__ ws) {
     __shared__ u32 h[3][256];
-    h[0][threadIdx.x] = 0; h[1][threadIdx.x] = 0; h[2][threadIdx.x] = 0;
+    __shared__ u32 flag;
+    if (threadIdx.x < 768) h[threadIdx.x >> 8][threadIdx.x & 255] = 0;
     const u32 bin_min = ws[kWsSel], bin_max = ws[kWsSel + 4], bin_s = ws[kWsSel + 8];
     __syncthreads();
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < units; i += (long long)gridDim.x * blockDim.x) {
-        const u32x4 wv = w[i], sv = s[i];
+    auto count = [&](const u32x4& wv, const u32x4& sv) {
         const u32 wd[4] = {wv.x, wv.y, wv.z, wv.w}, sd[4] = {sv.x, sv.y, sv.z, sv.w};
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
 #pragma unroll
-            for (int hh = 0; hh < 2; ++hh) {
-                const u32 key = half_key(hh ? wd[k] >> 16 : wd[k] & 0xFFFFu), sv16 = hh ? sd[k] >> 16 : sd[k] & 0xFFFFu;
-                if ((key >> 8) == bin_min) atomicAdd(&h[0][key & 255u], 1u);
-                if ((key >> 8) == bin_max) atomicAdd(&h[1][key & 255u], 1u);
-                if ((sv16 >> 8) == bin_s) atomicAdd(&h[2][sv16 & 255u], 1u);
+            for (int e = 0; e < 2; ++e) {
+                const u32 wb = e ? wd[k] >> 24 : (wd[k] >> 8) & 255u, sb = e ? sd[k] >> 24 : (sd[k] >> 8) & 255u;
+                if (wb == bin_min) atomicAdd(&h[0][(wd[k] >> (16 * e)) & 255u], 1u);
+                if (wb == bin_max) atomicAdd(&h[1][(wd[k] >> (16 * e)) & 255u], 1u);
+                if (sb == bin_s) atomicAdd(&h[2][(sd[k] >> (16 * e)) & 255u], 1u);
             }
         }
+    };
+    const long long stride = (long long)gridDim.x * kPassThreads;
+    long long i = (long long)blockIdx.x * kPassThreads + threadIdx.x;
+    for (; i + stride < units; i += 2 * stride) {
+        const u32x4 w0 = w[i], s0 = s[i], w1 = w[i + stride], s1 = s[i + stride];
+        count(w0, s0);
+        count(w1, s1);
     }
+    if (i < units) count(w[i], s[i]);
     __syncthreads();
-#pragma unroll
-    for (int t = 0; t < 3; ++t)
-        if (h[t][threadIdx.x]) atomicAdd(&ws[kWsHist2 + 256 * t + threadIdx.x], h[t][threadIdx.x]);
-}
-
-__global__ void __launch_bounds__(256) quant_select2_kernel(u32* ws) {
-    __shared__ u64 scan[256];
-    for (int t = 0; t < 3; ++t) {
-        const u64 r = (u64)ws[kWsSel + 4 * t + 1] | ((u64)ws[kWsSel + 4 * t + 2] << 32);
-        u32 lo; u64 res;
-        select_bin(ws[kWsHist2 + 256 * t + threadIdx.x], r, scan, lo, res);
-        if (threadIdx.x == 0) ws[kWsThr + t] = (ws[kWsSel + 4 * t] << 8) | lo;
+    if (threadIdx.x < 768 && h[threadIdx.x >> 8][threadIdx.x & 255])
+        __hip_atomic_fetch_add(&ws[kWsHist2 + threadIdx.x], h[threadIdx.x >> 8][threadIdx.x & 255], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!last_block(&ws[kWsDone + 1], &flag)) return;
+    __syncthreads();
+    const u32 t = threadIdx.x & 255;
+    for (int k = 0; k < 3; ++k) {
+        const u32 bin = k == 0 ? bin_min : (k == 1 ? bin_max : bin_s);
+        const bool down = k < 2 && (bin & 0x80u);                    // negative weights: the key's low byte is the complement
+        const u32 high = k < 2 ? key_high(bin) : bin;
+        u32* tmp = &h[0][0];
+        select_bin(load_shared(&ws[kWsHist2 + 256 * k + (down ? 255u - t : t)]), ws[kWsSel + 4 * k + 1], tmp, &ws[kWsThr + k], tmp + 8, (high << 8) | t);
     }
 }
 
@@ -148,54 +205,51 @@ __device__ __forceinline__ bool is_extracted(u32 wbits, u32 sv, u32 key_min, u32
     return key < key_min || key > key_max || sv > s_thr;
 }
 
-// extracted entries per row -> rowptr[row + 1]; one wave per row
-__global__ void __launch_bounds__(256) quant_count_kernel(int M, int N, const uint16_t* __restrict__ w, const uint16_t* __restrict__ s, const u32* __restrict__ ws, int* __restrict__ rowptr) {
-    const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= M) return;
+// pass 3: extracted entries per row, one wave per row; the last block turns the counts into row pointers
+__global__ void __launch_bounds__(kPassThreads) quant_count_kernel(int M, int N, const uint16_t* __restrict__ w, const uint16_t* __restrict__ s, u32* __restrict__ ws, int* __restrict__ rowptr) {
+    __shared__ u32 flag, wsum[kPassThreads / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, row = blockIdx.x * (kPassThreads / 64) + wave;
     const u32 key_min = ws[kWsThr], key_max = ws[kWsThr + 1], s_thr = ws[kWsThr + 2];
-    const u32x4* wr = reinterpret_cast<const u32x4*>(w + (size_t)row * N);
-    const u32x4* sr = reinterpret_cast<const u32x4*>(s + (size_t)row * N);
-    int cnt = 0;
-    for (int i = lane; i < N / 8; i += 64) {
-        const u32x4 wv = wr[i], sv = sr[i];
-        const u32 wd[4] = {wv.x, wv.y, wv.z, wv.w}, sd[4] = {sv.x, sv.y, sv.z, sv.w};
+    if (row < M) {
+        const u32x4* wr = reinterpret_cast<const u32x4*>(w + (size_t)row * N);
+        const u32x4* sr = reinterpret_cast<const u32x4*>(s + (size_t)row * N);
+        u32 cnt = 0;
+        for (int i = lane; i < N / 8; i += 64) {
+            const u32x4 wv = wr[i], sv = sr[i];
+            const u32 wd[4] = {wv.x, wv.y, wv.z, wv.w}, sd[4] = {sv.x, sv.y, sv.z, sv.w};
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-            cnt += (int)is_extracted(wd[k] & 0xFFFFu, sd[k] & 0xFFFFu, key_min, key_max, s_thr) + (int)is_extracted(wd[k] >> 16, sd[k] >> 16, key_min, key_max, s_thr);
+            for (int k = 0; k < 4; ++k)
+                cnt += (u32)is_extracted(wd[k] & 0xFFFFu, sd[k] & 0xFFFFu, key_min, key_max, s_thr) + (u32)is_extracted(wd[k] >> 16, sd[k] >> 16, key_min, key_max, s_thr);
+        }
+        cnt = wave_scan(Plain{cnt}).v;
+        if (lane == 63) __hip_atomic_store(reinterpret_cast<u32*>(&rowptr[row + 1]), cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    for (int off = 32; off > 0; off >>= 1) cnt += __shfl_down(cnt, off, 64);
-    if (lane == 0) rowptr[row + 1] = cnt;
-    if (row == 0 && lane == 0) rowptr[0] = 0;
-}
-
-// in-place inclusive scan of rowptr[1 .. M]; one block of 1024 threads
-__global__ void __launch_bounds__(1024) quant_scan_kernel(int M, int* __restrict__ rowptr) {
-    __shared__ int sums[1024];
-    const int per = (M + 1023) / 1024;
-    const int b = threadIdx.x * per, e = min(b + per, M);
-    int local = 0;
-    for (int i = b; i < e; ++i) local += rowptr[i + 1];
-    sums[threadIdx.x] = local;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {                       // Hillis-Steele inclusive scan
-        const int v = threadIdx.x >= off ? sums[threadIdx.x - off] : 0;
+    if (!last_block(&ws[kWsDone + 2], &flag)) return;
+    u32 carry = 0;
+    for (int t0 = 0; t0 < M; t0 += 4 * kPassThreads) {               // four rows per thread and round
+        const int r = t0 + 4 * threadIdx.x;
+        u32 c[4], mine = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) { c[k] = r + k < M ? load_shared(reinterpret_cast<const u32*>(&rowptr[r + k + 1])) : 0u; mine += c[k]; }
+        const u32 inc = wave_scan(Plain{mine}).v;
         __syncthreads();
-        sums[threadIdx.x] += v;
+        if (lane == 63) wsum[wave] = inc;
         __syncthreads();
+        u32 run = carry + inc - mine;
+        for (int k = 0; k < kPassThreads / 64; ++k) {
+            run += k < wave ? wsum[k] : 0u;
+            carry += wsum[k];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            run += c[k];
+            if (r + k < M) rowptr[r + k + 1] = (int)run;
+        }
     }
-    int run = sums[threadIdx.x] - local;
-    for (int i = b; i < e; ++i) { run += rowptr[i + 1]; rowptr[i + 1] = run; }
+    if (threadIdx.x == 0) rowptr[0] = 0;
 }
-
-__device__ __forceinline__ u32 umin(u32 a, u32 b) { return a < b ? a : b; }
-__device__ __forceinline__ u32 umax(u32 a, u32 b) { return a < b ? b : a; }
 
 // ---------------------------------------------------------------------------------------------- k-means of one row
-template <int CTRL, int ROW_MASK = 0xF>
-__device__ __forceinline__ u32 dpp_u32(u32 old, u32 v) { return (u32)__builtin_amdgcn_update_dpp((int)old, (int)v, CTRL, ROW_MASK, 0xF, false); }
-constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kRowHalfMirror = 0x141, kRowMirror = 0x140;
-constexpr int kRowShl1 = 0x101, kRowShr1 = 0x111, kRowShr2 = 0x112, kRowShr4 = 0x114, kRowShr8 = 0x118, kRowBcast15 = 0x142, kRowBcast31 = 0x143;
-
 // Exact sum of products s * w * 2^24.  |w| < 128 in the whole row: a product is below 2^47 and a row's sum below 2^63; else the low and
 // the high words of the products are summed apart.
 template <bool WIDE>
@@ -232,32 +286,6 @@ struct Moment<true> {
         return {a.v, b.v};
     }
 };
-struct Plain {                                                       // a 32-bit count or sum with the same interface
-    u32 v;
-    __device__ __forceinline__ Plain operator+(const Plain& o) const { return {v + o.v}; }
-    template <int CTRL, int ROW_MASK = 0xF>
-    __device__ __forceinline__ Plain moved() const { return {dpp_u32<CTRL, ROW_MASK>(0, v)}; }
-};
-// sum over each row of 16 lanes, in all its lanes
-template <class T>
-__device__ __forceinline__ T row16_sum(T v) {
-    v = v + v.template moved<kQuadXor1>();
-    v = v + v.template moved<kQuadXor2>();
-    v = v + v.template moved<kRowHalfMirror>();
-    v = v + v.template moved<kRowMirror>();
-    return v;
-}
-// inclusive prefix sum over the 64 lanes
-template <class T>
-__device__ __forceinline__ T wave_scan(T v) {
-    v = v + v.template moved<kRowShr1>();
-    v = v + v.template moved<kRowShr2>();
-    v = v + v.template moved<kRowShr4>();
-    v = v + v.template moved<kRowShr8>();
-    v = v + v.template moved<kRowBcast15, 0xA>();
-    v = v + v.template moved<kRowBcast31, 0xC>();
-    return v;
-}
 // Largest key k with 2 w(k) <= t, t between the smallest and the largest fp16 value doubled (the correction steps make it exact whatever
 // the conversion rounds to).
 __device__ __forceinline__ u32 key_below(float t) {
@@ -634,16 +662,15 @@ hipError_t launch_quantize(const QuantArgs& a, hipStream_t s) {
     u32* ws = static_cast<u32*>(a.workspace);
     const long long units = (long long)a.M * a.N / 8;
     const u64 total = (u64)a.M * (u64)a.N;
-    // every block ends with up to 512 global atomic adds to the same 512 counters: 1024 blocks rather than 2048
-    // (4096x4096: the two histogram kernels 47 + 27 -> 36 + 23 us)
-    const int hist_blocks = (int)min((long long)1024, (units + 255) / 256);
-    hipLaunchKernelGGL(quant_clear_kernel, dim3(4), dim3(256), 0, s, ws);
-    hipLaunchKernelGGL(quant_hist1_kernel, dim3(hist_blocks), dim3(256), 0, s, units, static_cast<const u32x4*>(a.w), static_cast<const u32x4*>(a.sens), ws);
-    hipLaunchKernelGGL(quant_select1_kernel, dim3(1), dim3(256), 0, s, total, (u64)a.n_lo, (u64)a.n_hi, (u64)a.n_sens, ws);
-    hipLaunchKernelGGL(quant_hist2_kernel, dim3(hist_blocks), dim3(256), 0, s, units, static_cast<const u32x4*>(a.w), static_cast<const u32x4*>(a.sens), ws);
-    hipLaunchKernelGGL(quant_select2_kernel, dim3(1), dim3(256), 0, s, ws);
-    hipLaunchKernelGGL(quant_count_kernel, dim3((a.M + 3) / 4), dim3(256), 0, s, a.M, a.N, static_cast<const uint16_t*>(a.w), static_cast<const uint16_t*>(a.sens), ws, a.rowptr);
-    hipLaunchKernelGGL(quant_scan_kernel, dim3(1), dim3(1024), 0, s, a.M, a.rowptr);
+    const int blocks = (int)min((long long)kPassBlocks, (units + kPassThreads - 1) / kPassThreads);
+    const u32x4* w4 = static_cast<const u32x4*>(a.w);
+    const u32x4* s4 = static_cast<const u32x4*>(a.sens);
+    constexpr int kHist1Lds = 2 * 256 * 32 * 4;
+    hipLaunchKernelGGL(quant_clear_kernel, dim3(2), dim3(256), 0, s, ws);
+    hipLaunchKernelGGL(quant_hist1_kernel, dim3(blocks), dim3(kPassThreads), kHist1Lds, s, units, w4, s4, ws, (u32)a.n_lo, (u32)(total - 1 - (u64)a.n_hi), (u32)(total - 1 - (u64)a.n_sens));
+    hipLaunchKernelGGL(quant_hist2_kernel, dim3(blocks), dim3(kPassThreads), 0, s, units, w4, s4, ws);
+    hipLaunchKernelGGL(quant_count_kernel, dim3((a.M + kPassThreads / 64 - 1) / (kPassThreads / 64)), dim3(kPassThreads), 0, s, a.M, a.N,
+                       static_cast<const uint16_t*>(a.w), static_cast<const uint16_t*>(a.sens), ws, a.rowptr);
     // Threads per row by the row's LDS footprint (26 KB at 4096 weights, 66 KB at 11008, 159 KB at 28672, so six, two and one row per
     // compute unit at a time): the iterations of a row are one chain of dependent steps, the other waves of the unit fill the gaps.
     auto go = [](auto kernel, size_t lds) { return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); };
