@@ -44,20 +44,19 @@ __device__ __forceinline__ u32 umax(u32 a, u32 b) { return a < b ? b : a; }
 template <int CTRL, int ROW_MASK = 0xF>
 __device__ __forceinline__ u32 dpp_u32(u32 old, u32 v) { return (u32)__builtin_amdgcn_update_dpp((int)old, (int)v, CTRL, ROW_MASK, 0xF, false); }
 constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kRowHalfMirror = 0x141, kRowMirror = 0x140;
-constexpr int kRowShl1 = 0x101, kRowShr1 = 0x111, kRowShr2 = 0x112, kRowShr4 = 0x114, kRowShr8 = 0x118, kRowBcast15 = 0x142, kRowBcast31 = 0x143;
+constexpr int kRowShr1 = 0x111, kRowShr2 = 0x112, kRowShr4 = 0x114, kRowShr8 = 0x118, kRowBcast15 = 0x142, kRowBcast31 = 0x143;
 struct Plain {                                                       // a 32-bit count or sum
     u32 v;
     __device__ __forceinline__ Plain operator+(const Plain& o) const { return {v + o.v}; }
     template <int CTRL, int ROW_MASK = 0xF>
     __device__ __forceinline__ Plain moved() const { return {dpp_u32<CTRL, ROW_MASK>(0, v)}; }
 };
-// sum over each row of 16 lanes, in all its lanes
+// sum over each group of eight lanes, in all its lanes
 template <class T>
-__device__ __forceinline__ T row16_sum(T v) {
+__device__ __forceinline__ T group_sum(T v) {
     v = v + v.template moved<kQuadXor1>();
     v = v + v.template moved<kQuadXor2>();
     v = v + v.template moved<kRowHalfMirror>();
-    v = v + v.template moved<kRowMirror>();
     return v;
 }
 // inclusive prefix sum over the 64 lanes
@@ -286,6 +285,13 @@ struct Moment<true> {
         return {a.v, b.v};
     }
 };
+// Orders the LDS accesses of one wave (they execute in order; this keeps the compiler from reordering them).
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Largest key k with 2 w(k) <= t, t between the smallest and the largest fp16 value doubled (the correction steps make it exact whatever
 // the conversion rounds to).
 __device__ __forceinline__ u32 key_below(float t) {
@@ -302,38 +308,44 @@ __device__ __forceinline__ u32 key_below(float t) {
 //   * it is read once; every thread keeps its weights as words (key << 16 | sensitivity) in registers until the indices are written;
 //   * a counting sort puts the words into NB buckets of 2^shift consecutive keys (shift from the row's smallest and largest key); the
 //     atomic that counts a word also gives its place in the bucket; the order inside a bucket does not matter, all sums are integers;
-//   * C0 / C1 hold the sums in front of every chunk of 16 words;
-//   * 16 lanes evaluate a boundary: the key below it names the bucket, and the sums are those in front of the chunk in which the
+//   * C0 / C1 hold the sums in front of every chunk of eight words;
+//   * eight lanes evaluate a boundary: the key below it names the bucket, and the sums are those in front of the chunk in which the
 //     bucket starts plus the words up to the end of the bucket that precede the bucket or have a key within the boundary.  A bucket
-//     holds a handful of words, so that is one round of two words per lane.  A wave takes four boundaries, K / 4 waves work on an
-//     iteration, which costs one barrier.
+//     holds a handful of words, so that is one round of two words per lane.  A wave takes eight boundaries: tables of up to eight
+//     entries iterate inside one wave without a barrier, larger ones in two waves with one barrier.
 // The decisions and integers are those of a pass over all weights per update, hence the same result.
-// Bound by the latency of that chain (boundary -> bucket -> words -> reduction -> division) and, beyond two rows per unit, by the vector
-// ALU.  Against a bitonic sort of the row in LDS and a 64-way search per boundary with reductions over 64 lanes: 4096x4096 at 3 bits
-// 409 -> 134 us (22 updates per row, 3.6 us each over the matrix), 4096x11008 at 4 bits 1164 -> 447 us (32 updates, 8.0 us each).  All
-// boundaries of an iteration in one wave, without a barrier: 160 and 968 us.
-template <int BITS, int T>
+// Bound by the vector ALU (62 % busy at 4096x4096, 51 % at 4096x11008) and by the latency of the chain boundary -> bucket -> words ->
+// reduction -> division, which the other rows on the unit cover only in part (six at 4096 weights, two at 11008).  Against a bitonic sort of the
+// row in LDS and a 64-way search per boundary with reductions over 64 lanes: 4096x4096 at 3 bits 409 -> 112 us (22 updates per row, 2.6 us
+// each over the matrix), 4096x11008 at 4 bits 1164 -> 377 us (32 updates, 7.5 us each).  16 lanes per boundary and chunks of 16 words:
+// 134 and 447 us (vector ALU 84 % busy).
+// Threads T, units of eight weights per thread V, buckets, words per chunk of running sums (twice as many in wide rows), and the waves per
+// SIMD the registers are held down for.
+template <int T_, int V_, int LOG_NB, int CHUNK, int WAVES>
 struct KmeansShape {
-    static constexpr int V = T == 256 ? 2 : 4;                       // units of eight weights per thread: N <= 8 T V
-    static constexpr int NB = T == 256 ? 1024 : 2048;                // buckets
-    static constexpr int kMinLog = T == 256 ? 10 : 11;               // log2(NB)
-    static constexpr int kMaxN = T == 256 ? 4096 : (T == 512 ? 16384 : 28672);
+    static constexpr int T = T_, V = V_, kWavesPerSimd = WAVES, kChunk = CHUNK;
+    static constexpr int kMaxN = 8 * T_ * V_ < 28672 ? 8 * T_ * V_ : 28672;
+    static constexpr int kLogNB = LOG_NB, NB = 1 << LOG_NB;
+    static constexpr int kChunksPerThread = (kMaxN / CHUNK + T_ - 1) / T_;
+    static constexpr size_t sum_bytes(int N) { return (size_t)(N / CHUNK + 1) * 12 + 32; }           // also holds (N / (2 CHUNK) + 1) * 20
+    static constexpr size_t lds(int N) { return (size_t)N * 4 + sum_bytes(N) + (size_t)(NB + 2) * 2; }
 };
-__host__ __device__ constexpr size_t kmeans_lds(int N, int NB) { return (size_t)N * 4 + (size_t)(N / 16 + 1) * 20 + (size_t)(NB + 4) * 4; }
+typedef KmeansShape<256, 2, 11, 8, 6> KmeansUpTo4096;                // 26 KB of LDS at 4096 weights: six rows per compute unit
+typedef KmeansShape<512, 3, 12, 8, 4> KmeansUpTo12288;               // 69 KB at 11008: two
+typedef KmeansShape<512, 4, 12, 8, 4> KmeansUpTo16384;
+typedef KmeansShape<1024, 4, 12, 16, 4> KmeansBeyond;                // 145 KB at 28672: one
 
-template <int BITS, int T>
-__global__ void __launch_bounds__(T) quant_kmeans_kernel(int M, int N, int max_iter, const uint16_t* __restrict__ w, const uint16_t* __restrict__ sens,
+template <int BITS, class S>
+__global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(int M, int N, int max_iter, const uint16_t* __restrict__ w, const uint16_t* __restrict__ sens,
                                                          const u32* __restrict__ ws, const int* __restrict__ rowptr, void* __restrict__ qidx,
                                                          uint16_t* __restrict__ lut, int* __restrict__ cols, uint16_t* __restrict__ vals, int* __restrict__ iters) {
-    constexpr int K = 1 << BITS, SETS = K / 4;                       // boundaries are evaluated four at a time
-    constexpr int V = KmeansShape<BITS, T>::V, NB = KmeansShape<BITS, T>::NB, NBT = NB / T, NWAVES = T / 64;
+    constexpr int K = 1 << BITS, SETS = K > 8 ? K / 8 : 1;           // eight boundaries per wave
+    constexpr int T = S::T, V = S::V, NB = S::NB, NBT = NB / T, NWAVES = T / 64;
     extern __shared__ __align__(16) char smem[];
-    const int NC = N / 16;
-    u32* A = reinterpret_cast<u32*>(smem);                           // [N] words by bucket
-    i64* C1 = reinterpret_cast<i64*>(A + N);                         // [NC + 1] (narrow) or [2 (NC + 1)] (wide): sum of s w 2^24 in front of chunk c
-    u32* C0 = reinterpret_cast<u32*>(C1 + 2 * (NC + 1));             // [NC + 1] sum of s in front of chunk c
-    u32* start = C0 + (NC + 1);                                      // [NB + 1] first place of every bucket; counts before the scan
-    start += (4 - ((reinterpret_cast<size_t>(start) >> 2) & 3)) & 3;
+    u32* A = reinterpret_cast<u32*>(smem);                           // words by bucket
+    char* sums = smem + (size_t)N * 4;                               // sums in front of every chunk: moments, then sensitivities
+    u32* start32 = reinterpret_cast<u32*>(sums + S::sum_bytes(N));   // first place of every bucket, two to a word; counts before the scan
+    const uint16_t* start = reinterpret_cast<const uint16_t*>(start32);
     u32* emask = A;                                                  // bit j: weight j is extracted (A is filled after its last use)
     __shared__ u32 wsum[NWAVES];
     __shared__ i64 wmom[2 * NWAVES];
@@ -342,10 +354,10 @@ __global__ void __launch_bounds__(T) quant_kmeans_kernel(int M, int N, int max_i
     __shared__ i64 Fs1[4 * (K + 1)];
     __shared__ int moved[2][SETS];
     __shared__ float cen_s[K];
-    __shared__ u32 kt[K];
+    __shared__ u32 bound[K], rank_bucket[K], nearest;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), row = blockIdx.x;
-    const int n = lane & 15, q = lane >> 4;
+    const int n = lane & 7, q = lane >> 3;                           // eight lanes per boundary
     const u32 key_min = ws[kWsThr], key_max = ws[kWsThr + 1], s_thr = ws[kWsThr + 2];
     const uint16_t* __restrict__ wrow = w + (size_t)row * N;
     const int units = N / 8;
@@ -361,8 +373,8 @@ __global__ void __launch_bounds__(T) quant_kmeans_kernel(int M, int N, int max_i
             const int i = min(tid + T * v, units - 1);
             wv[v] = wr[i]; sv[v] = sr[i];
         }
-        for (int b = tid; b < NB; b += T) start[b] = 0;
-        if (tid == 0) { kmm[0] = 0xFFFFu; kmm[1] = 0; start[NB] = 0; }
+        for (int b = tid; b < NB / 2 + 1; b += T) start32[b] = 0;
+        if (tid == 0) { kmm[0] = 0xFFFFu; kmm[1] = 0; nearest = 0xFFFFFFFFu; }
         u32 kmin = 0xFFFFu, kmax = 0;
 #pragma unroll
         for (int v = 0; v < V; ++v) {
@@ -391,23 +403,31 @@ __global__ void __launch_bounds__(T) quant_kmeans_kernel(int M, int N, int max_i
     __syncthreads();
     const u32 kmin = (u32)__builtin_amdgcn_readfirstlane((int)kmm[0]), kmax = (u32)__builtin_amdgcn_readfirstlane((int)kmm[1]);   // kmax < kmin: no dense weight
     const u32 range = kmax >= kmin ? kmax - kmin : 0u;
-    const int shift = max(0, 32 - __builtin_clz(range | 1u) - KmeansShape<BITS, T>::kMinLog);
+    const int shift = max(0, 32 - __builtin_clz(range | 1u) - S::kLogNB);
+    auto bucket_of = [&](u32 wd) { return ((wd >> 16) - kmin) >> shift; };
 
     // ---- 2. count the buckets; the count before gives a word its place
-    uint16_t rank[V][8];
+    u32 rank[V][4];                                                  // two to a word
 #pragma unroll
     for (int v = 0; v < V; ++v)
 #pragma unroll
-        for (int e = 0; e < 8; ++e)
-            if (word[v][e] != 0xFFFFFFFFu) rank[v][e] = (uint16_t)atomicAdd(&start[((word[v][e] >> 16) - kmin) >> shift], 1u);
+        for (int e = 0; e < 8; ++e) {
+            u32 r = 0;
+            if (word[v][e] != 0xFFFFFFFFu) {
+                const u32 b = bucket_of(word[v][e]), sh = 16 * (b & 1);
+                r = (atomicAdd(&start32[b >> 1], 1u << sh) >> sh) & 0xFFFFu;   // a bucket holds fewer than 2^15 words
+            }
+            rank[v][e >> 1] = (e & 1) ? rank[v][e >> 1] | (r << 16) : r;
+        }
     const u32 ext = tid < N / 32 ? emask[tid] : 0u;
     __syncthreads();
     // ---- 3. one scan over the threads for the places of the buckets (low half) and of the CSR entries (high half); both are below 2^15
     int n_dense;
     {
-        u32 cnt[NBT], mine = 0;
+        u32 pair[NBT / 2], mine = 0;
 #pragma unroll
-        for (int k = 0; k < NBT; ++k) { cnt[k] = start[tid * NBT + k]; mine += cnt[k]; }
+        for (int k = 0; k < NBT / 2; ++k) { pair[k] = start32[tid * (NBT / 2) + k]; mine += (pair[k] & 0xFFFFu) + (pair[k] >> 16); }
+        const u32 dense = mine;
         mine |= (u32)__builtin_popcount(ext) << 16;
         const Plain inc = wave_scan(Plain{mine});
         if (lane == 63) wsum[wave] = inc.v;
@@ -419,11 +439,29 @@ __global__ void __launch_bounds__(T) quant_kmeans_kernel(int M, int N, int max_i
             before += k < wave ? t : 0u;
             total += t;
         }
-        n_dense = (int)(total & 0xFFFFu);
+        n_dense = __builtin_amdgcn_readfirstlane((int)(total & 0xFFFFu));
         u32 run = before & 0xFFFFu;
+        // the buckets of the ranks the k-means starts from
 #pragma unroll
-        for (int k = 0; k < NBT; ++k) { start[tid * NBT + k] = run; run += cnt[k]; }
-        if (tid == 0) start[NB] = (u32)n_dense;
+        for (int k = 0; k < K; ++k) {
+            const u32 r = (u32)(((u64)(2 * k + 1) * (u64)n_dense) / (u64)(2 * K));
+            if (r - run < dense) {                                   // a bucket of this thread (run <= r < run + dense)
+                u32 at = run, b = 0;
+#pragma unroll
+                for (int i = 0; i < NBT - 1; ++i) {
+                    at += (i & 1) ? pair[i >> 1] >> 16 : pair[i >> 1] & 0xFFFFu;
+                    b += r >= at ? 1u : 0u;
+                }
+                rank_bucket[k] = tid * NBT + b;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < NBT / 2; ++k) {
+            const u32 second = run + (pair[k] & 0xFFFFu);
+            start32[tid * (NBT / 2) + k] = run | (second << 16);
+            run = second + (pair[k] >> 16);
+        }
+        if (tid == 0) start32[NB / 2] = (u32)n_dense;
         // CSR entries of the row, columns ascending
         int o = rowptr[row] + (int)(before >> 16);
         for (u32 m = ext; m; m &= m - 1) {
@@ -439,37 +477,40 @@ __global__ void __launch_bounds__(T) quant_kmeans_kernel(int M, int N, int max_i
     for (int v = 0; v < V; ++v)
 #pragma unroll
         for (int e = 0; e < 8; ++e)
-            if (word[v][e] != 0xFFFFFFFFu) A[start[((word[v][e] >> 16) - kmin) >> shift] + rank[v][e]] = word[v][e];
+            if (word[v][e] != 0xFFFFFFFFu) A[start[bucket_of(word[v][e])] + ((e & 1) ? rank[v][e >> 1] >> 16 : rank[v][e >> 1] & 0xFFFFu)] = word[v][e];
     __syncthreads();
 
     int it = 0;
     auto solve = [&](auto wide) {
         constexpr bool WIDE = decltype(wide)::value;
+        constexpr int CW = WIDE ? 2 * S::kChunk : S::kChunk, CT = S::kChunksPerThread;
         typedef Moment<WIDE> Mom;
-        Mom* C = reinterpret_cast<Mom*>(C1);
+        const int NC = N / CW;                                       // whole chunks: N is a multiple of 128
+        Mom* C1 = reinterpret_cast<Mom*>(sums);                      // [NC + 1] sum of s w 2^24 in front of chunk c
+        u32* C0 = reinterpret_cast<u32*>(C1 + NC + 1);               // [NC + 1] sum of s
         Mom* F1 = reinterpret_cast<Mom*>(Fs1);
         Mom* wm = reinterpret_cast<Mom*>(wmom);
-        // ---- 5. sums in front of every chunk of 16 words; thread t owns the chunks t CT ..
-        constexpr int CT = V == 2 ? 1 : 2;
-        const int nchunks = (n_dense + 15) >> 4;
+        // ---- 5. sums in front of every chunk; thread t owns the chunks CT t ..
+        const int nchunks = (n_dense + CW - 1) / CW;
         {
-            u32 s0[CT];
-            Mom s1[CT];
-            u32 t0 = 0;
-            Mom t1 = Mom::zero();
+            u32 s0[CT], t0 = 0;
+            Mom s1[CT], t1 = Mom::zero();
 #pragma unroll
             for (int k = 0; k < CT; ++k) {
-                const int c = tid * CT + k;
+                const int c = CT * tid + k;
                 s0[k] = 0; s1[k] = Mom::zero();
                 if (c < nchunks) {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int j = 16 * c + 4 * ((i + tid) & 3);  // a rotated order: neighbouring threads read different banks
+                    for (int i = 0; i < CW / 4; ++i) {
+                        const int j = CW * c + 4 * ((i + tid) & (CW / 4 - 1));   // a rotated order: neighbouring threads read different banks
                         const u32x4 v4 = *reinterpret_cast<const u32x4*>(A + j);
                         const u32 vv[4] = {v4.x, v4.y, v4.z, v4.w};
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (j + e < n_dense) { s0[k] += vv[e] & 0xFFFFu; s1[k] = s1[k] + Mom::product(vv[e]); }
+                        for (int e = 0; e < 4; ++e) {
+                            const u32 z = j + e < n_dense ? vv[e] : 0x80000000u;   // +0 with sensitivity 0
+                            s0[k] += z & 0xFFFFu;
+                            s1[k] = s1[k] + Mom::product(z);
+                        }
                     }
                 }
                 t0 += s0[k]; t1 = t1 + s1[k];
@@ -483,92 +524,91 @@ __global__ void __launch_bounds__(T) quant_kmeans_kernel(int M, int N, int max_i
             for (int k = 0; k < wave; ++k) { b0 += wsum[k]; b1 = b1 + wm[k]; }   // uniform
 #pragma unroll
             for (int k = 0; k < CT; ++k) {
-                const int c = tid * CT + k;
-                if (c <= NC) { C0[c] = b0; C[c] = b1; }
+                const int c = CT * tid + k;
+                if (c <= NC) { C0[c] = b0; C1[c] = b1; }
                 b0 += s0[k]; b1 = b1 + s1[k];
             }
-            if (tid == T - 1 && CT * T == NC) { C0[NC] = b0; C[NC] = b1; }
+            if (tid == T - 1 && CT * T == NC) { C0[NC] = b0; C1[NC] = b1; }
         }
         __syncthreads();
-        // ---- 6. equal-count start: the weight of rank r lies in the last bucket that starts at or before r; its key is found bit by bit.
-        //         Wave s < SETS finds the centroids 4 s .. 4 s + 3, one per group of 16 lanes.
-        const int k0 = 4 * wave + q;
+        // ---- 6. equal-count start: the key of the weight of rank r, found bit by bit inside its bucket, by the eight lanes that will work on
+        //         the boundary above that centroid
+        const int k0 = 8 * wave + q;
         if (wave < SETS) {
-            const int r = (int)(((u64)(2 * k0 + 1) * (u64)n_dense) / (u64)(2 * K));
-            int lo = 0, hi = NB;                                     // start[lo] <= r < start[hi]
-            while (hi - lo > 1) {                                    // the same number of rounds in every lane
-                const int mid = (lo + hi) >> 1;
-                if ((int)start[mid] <= r) lo = mid; else hi = mid;
-            }
-            const int p0 = (int)start[lo], p1 = (int)start[lo + 1];
-            u32 key = kmin + ((u32)lo << shift);
+            const int kr = min(k0, K - 1);
+            const int r = (int)(((u64)(2 * kr + 1) * (u64)n_dense) / (u64)(2 * K));
+            const int b0 = (int)rank_bucket[kr], p0 = (int)start[b0], p1 = (int)start[b0 + 1];
+            const u32 first = A[min(p0 + n, N - 1)] >> 16;
+            u32 key = kmin + ((u32)b0 << shift);
             for (int b = shift - 1; b >= 0; --b) {
                 const u32 cand = key + (1u << b);                    // no more than r - p0 words below cand: the key is cand or above
-                int below = 0;
-                for (int j0 = p0; __any(j0 < p1); j0 += 16) {
+                u32 below = 0, v = first;
+                for (int j0 = p0; __any(j0 < p1); j0 += 8) {
                     const int j = j0 + n;
-                    const bool in = j < p1 && (A[min(j, N - 1)] >> 16) < cand;
-                    const u64 m = __ballot(in);
-                    below += __builtin_popcount((u32)(m >> (16 * q)) & 0xFFFFu);
+                    if (j0 != p0) v = A[min(j, N - 1)] >> 16;
+                    below += j < p1 && v < cand ? 1u : 0u;
                 }
-                if (below <= r - p0) key = cand;
+                if ((int)group_sum(Plain{below}).v <= r - p0) key = cand;
             }
-            if (n == 0) cen_s[k0] = half_bits_to_f32(key_half(key));
+            if (n == 0 && k0 < K) cen_s[k0] = half_bits_to_f32(key_half(key));
         }
         if (tid < 2) {
             Fs0[tid][0] = 0; F1[tid * (K + 1)] = Mom::zero();
-            Fs0[tid][K] = C0[nchunks]; F1[tid * (K + 1) + K] = C[nchunks];
+            Fs0[tid][K] = C0[nchunks]; F1[tid * (K + 1) + K] = C1[nchunks];
         }
         __syncthreads();
-        // ---- 7. Lloyd iterations: wave s < SETS evaluates the boundaries 4 s .. 4 s + 3; every such wave then forms all centroids.
-        //         The sums of two successive iterations use different arrays, so one barrier per iteration is enough.
-        float cen = n < K ? cen_s[n] : 0.f;                          // lane (n, q): centroid n
-        int prev = -1;
+        if (SETS == 1 && wave != 0) return;                          // uniform
+        // ---- 7. Lloyd iterations: group q of wave s < SETS evaluates boundary k0 = 8 s + q; its even lanes hold centroid k0, its odd ones
+        //         k0 + 1.  The sums of two successive iterations use different arrays, so one barrier per iteration is enough.
+        const int kc = min(k0 + (n & 1), K - 1);
+        float cen = wave < SETS ? cen_s[kc] : 0.f;
+        u32 prev = 0xFFFFFFFFu;
         for (int par = 0;; par ^= 1) {
+            bool any = false;
             if (wave < SETS) {                                       // uniform
-                const float next = __builtin_bit_cast(float, dpp_u32<kRowShl1>(0u, __builtin_bit_cast(u32, cen)));
-                const float thr = __fadd_rn(cen, next);              // lane n: twice the boundary above centroid n
-                const float t = __shfl(thr, 16 * q + min(k0, K - 2));
-                const u32 kk = key_below(t);
-                const int b = kk < kmin ? -1 : (int)min((kk - kmin) >> shift, (u32)(NB - 1));
-                const int p0 = b < 0 ? 0 : (int)start[max(b, 0)], p1 = b < 0 ? 0 : (int)start[max(b, 0) + 1];
+                const u32 kk = key_below(__fadd_rn(cen, __builtin_bit_cast(float, dpp_u32<kQuadXor1>(0u, __builtin_bit_cast(u32, cen)))));
+                const u32 b = (umin(umax(kk, kmin), kmax) - kmin) >> shift;
+                u32 p0 = start[b], p1 = start[b + 1];
+                if (kk < kmin) { p0 = 0; p1 = 0; }
                 const u32 kkw = (kk << 16) | 0xFFFFu;
-                const int j0 = p0 & ~15;
-                const u32 c0 = C0[j0 >> 4];
-                const Mom c1 = C[j0 >> 4];
-                int pos = j0;
-                u32 s0 = 0;
+                const u32 j0 = p0 & ~(u32)(CW - 1);
+                const u32 c0 = C0[j0 / CW];
+                const Mom c1 = C1[j0 / CW];
+                u32 pos = 0, s0 = 0;
                 Mom s1 = Mom::zero();
-                for (int j1 = j0; __any(j1 < p1); j1 += 32) {
-                    const int ja = j1 + n, jb = ja + 16;
-                    const u32 va = A[min(ja, N - 1)], vb = A[min(jb, N - 1)];
-                    const bool ina = ja < p1 && (ja < p0 || va <= kkw), inb = jb < p1 && vb <= kkw;   // jb >= p0
-                    const u64 ma = __ballot(ina), mb = __ballot(inb);
-                    pos += __builtin_popcount((u32)(ma >> (16 * q)) & 0xFFFFu) + __builtin_popcount((u32)(mb >> (16 * q)) & 0xFFFFu);
-                    const u32 za = ina ? va : 0x80000000u, zb = inb ? vb : 0x80000000u;   // +0 with sensitivity 0
+                for (u32 j1 = j0; __any(j1 < p1); j1 += 16) {
+                    const u32 ja = j1 + n, jb = ja + 8;
+                    const u32 va = A[umin(ja, N - 1)], vb = A[umin(jb, N - 1)];
+                    const bool ina = ja < p1 && (ja < p0 || va <= kkw), inb = jb < p1 && (jb < p0 || vb <= kkw);
+                    pos += (ina ? 1u : 0u) + (inb ? 1u : 0u);
+                    const u32 za = ina ? va : 0x80000000u, zb = inb ? vb : 0x80000000u;
                     s0 += (za & 0xFFFFu) + (zb & 0xFFFFu);
                     s1 = s1 + Mom::product(za) + Mom::product(zb);
                 }
-                s0 = row16_sum(Plain{s0}).v + c0;
-                s1 = row16_sum(s1) + c1;
+                pos = group_sum(Plain{pos}).v + j0;
+                s0 = group_sum(Plain{s0}).v + c0;
+                s1 = group_sum(s1) + c1;
                 if (n == 0 && k0 < K - 1) { Fs0[par][k0 + 1] = s0; F1[par * (K + 1) + k0 + 1] = s1; }
-                const bool any = __any(k0 < K - 1 && pos != prev);
-                if (lane == 0) moved[par][wave] = any ? 1 : 0;
+                any = __any(k0 < K - 1 && pos != prev);
+                if (SETS > 1 && lane == 0) moved[par][wave] = any ? 1 : 0;
                 prev = pos;
             }
-            __syncthreads();
-            int any = 0;
+            if constexpr (SETS > 1) {
+                __syncthreads();
 #pragma unroll
-            for (int k = 0; k < SETS; ++k) any |= moved[par][k];
-            if (any == 0 || it == max_iter) break;                   // uniform
-            if (wave < SETS && n < K) {
-                const u32 m0 = Fs0[par][n + 1] - Fs0[par][n];
-                const Mom m1 = F1[par * (K + 1) + n + 1] - F1[par * (K + 1) + n];
+                for (int k = 0; k < SETS; ++k) any = any || moved[par][k] != 0;
+            } else {
+                wave_fence();
+            }
+            if (!any || it == max_iter) break;                       // uniform
+            if (wave < SETS) {
+                const u32 m0 = Fs0[par][kc + 1] - Fs0[par][kc];
+                const Mom m1 = F1[par * (K + 1) + kc + 1] - F1[par * (K + 1) + kc];
                 if (m0 > 0) cen = (float)(m1.value() * 5.9604644775390625e-08 / (double)m0);
             }
             ++it;
         }
-        if (tid < K) cen_s[tid] = cen;
+        if (wave < SETS && n == 0 && k0 < K) cen_s[k0] = cen;
     };
     if (n_dense > 0) {
         if (kmax >= 0xD800u || kmin <= 0x27FFu) solve(std::integral_constant<bool, true>{});    // |w| >= 128 somewhere
@@ -581,54 +621,47 @@ __global__ void __launch_bounds__(T) quant_kmeans_kernel(int M, int N, int max_i
     if (tid < K) {
         const uint16_t hb = __builtin_bit_cast(uint16_t, (_Float16)cen_s[tid]);
         lut[(size_t)row * K + tid] = hb;
+        u32 k = 0xFFFFu;                                             // the last one: above every key
         if (tid < K - 1) {
             const uint16_t hn = __builtin_bit_cast(uint16_t, (_Float16)cen_s[tid + 1]);
             const i64 t = half_to_fixed(hb) + half_to_fixed(hn);     // largest key with 2 w 2^24 <= t
             typedef __fp16 fp16x2 __attribute__((ext_vector_type(2)));
             const fp16x2 h = __builtin_amdgcn_cvt_pkrtz((float)((double)t * 2.98023223876953125e-08), 0.f);
-            u32 k = half_key(__builtin_bit_cast(u32, h) & 0xFFFFu);
+            k = half_key(__builtin_bit_cast(u32, h) & 0xFFFFu);
             if (2 * half_to_fixed(key_half(k)) > t) --k;
             if (k < 0xFBFFu && 2 * half_to_fixed(key_half(k + 1)) <= t) ++k;
-            kt[tid] = k;
         }
+        bound[tid] = (k << 16) | 0xFFFFu;
+        atomicMin(&nearest, ((u32)(hb & 0x7FFFu) << 4) | tid);       // the entry nearest to zero, the first of several
     }
-    if (tid == 0 && iters) iters[row] = it;                          // thread 0 is in the wave that iterated
+    if (tid == 0 && iters) iters[row] = it;
     __syncthreads();
-    {
-        u32 bound[K - 1];
+    const u32 zero = nearest & 15u;
+    const char* bounds = reinterpret_cast<const char*>(bound);
 #pragma unroll
-        for (int k = 0; k < K - 1; ++k) bound[k] = ((u32)__builtin_amdgcn_readfirstlane((int)kt[k]) << 16) | 0xFFFFu;
-        u32 zero = 0;
-        i64 best = 0;
+    for (int v = 0; v < V; ++v) {
+        const int i = tid + T * v;
+        if (i >= units) continue;                                    // whole quads of lanes
+        u32 at[8];                                                   // binary search over the ascending boundaries; four times the index
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const i64 f = half_to_fixed((u32)__builtin_bit_cast(uint16_t, (_Float16)cen_s[k]));
-            const i64 a = f < 0 ? -f : f;
-            if (k == 0 || a < best) { best = a; zero = k; }
-        }
+        for (int e = 0; e < 8; ++e) at[e] = 0;
 #pragma unroll
-        for (int v = 0; v < V; ++v) {
-            const int i = tid + T * v;
-            if (i >= units) continue;                                // whole quads of lanes
-            u32 packed = 0;
+        for (int step = K / 2; step > 0; step >>= 1)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                u32 a = 0;
+            for (int e = 0; e < 8; ++e) at[e] += word[v][e] > *reinterpret_cast<const u32*>(bounds + at[e] + 4 * (step - 1)) ? 4u * step : 0u;
+        u32 packed = 0;
 #pragma unroll
-                for (int k = 0; k < K - 1; ++k) a += word[v][e] > bound[k] ? 1u : 0u;
-                packed |= (word[v][e] == 0xFFFFFFFFu ? zero : a) << (BITS * e);
-            }
-            if constexpr (BITS == 2) {
-                static_cast<uint16_t*>(qidx)[(size_t)row * units + i] = (uint16_t)packed;
-            } else if constexpr (BITS == 4) {
-                static_cast<u32*>(qidx)[(size_t)row * units + i] = packed;
-            } else {
-                // four lanes hold 24 bits each: lane l of the quad writes dword l of the three
-                const u32 up = dpp_u32<0x39>(0u, packed);            // quad_perm [1,2,3,0]
-                const int l = lane & 3;
-                const u32 d = (packed >> (8 * l)) | (up << (24 - 8 * l));
-                if (l < 3) static_cast<u32*>(qidx)[((size_t)row * units + (i & ~3)) / 4 * 3 + l] = d;
-            }
+        for (int e = 0; e < 8; ++e) packed |= (word[v][e] == 0xFFFFFFFFu ? zero : at[e] >> 2) << (BITS * e);
+        if constexpr (BITS == 2) {
+            static_cast<uint16_t*>(qidx)[(size_t)row * units + i] = (uint16_t)packed;
+        } else if constexpr (BITS == 4) {
+            static_cast<u32*>(qidx)[(size_t)row * units + i] = packed;
+        } else {
+            // four lanes hold 24 bits each: lane l of the quad writes dword l of the three
+            const u32 up = dpp_u32<0x39>(0u, packed);                // quad_perm [1,2,3,0]
+            const int l = lane & 3;
+            const u32 d = (packed >> (8 * l)) | (up << (24 - 8 * l));
+            if (l < 3) static_cast<u32*>(qidx)[((size_t)row * units + (i & ~3)) / 4 * 3 + l] = d;
         }
     }
 }
@@ -658,6 +691,29 @@ hipError_t quantize_static_scratch(void** out) {
     return hipSuccess;
 }
 
+template <int BITS, class S>
+static hipError_t launch_kmeans(const QuantArgs& a, hipStream_t s) {
+    // the limit belongs to the current device's copy of the kernel; raising it is a host-side table update
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&quant_kmeans_kernel<BITS, S>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::lds(S::kMaxN));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((quant_kmeans_kernel<BITS, S>), dim3(a.M), dim3(S::T), S::lds(a.N), s, a.M, a.N, a.max_iter,
+                       static_cast<const uint16_t*>(a.w), static_cast<const uint16_t*>(a.sens), static_cast<const u32*>(a.workspace), a.rowptr, a.qidx,
+                       static_cast<uint16_t*>(a.lut), a.cols, static_cast<uint16_t*>(a.vals), a.iters);
+    return hipGetLastError();
+}
+template <class S>
+static hipError_t launch_kmeans_bits(const QuantArgs& a, hipStream_t s) {
+    return a.bits == 2 ? launch_kmeans<2, S>(a, s) : (a.bits == 3 ? launch_kmeans<3, S>(a, s) : launch_kmeans<4, S>(a, s));
+}
+// Threads per row by the row's LDS footprint: few rows fit a compute unit when they are long, so each gets more waves for the phases that
+// pass over its weights.
+static hipError_t launch_kmeans_shape(const QuantArgs& a, hipStream_t s) {
+    if (a.N <= KmeansUpTo4096::kMaxN) return launch_kmeans_bits<KmeansUpTo4096>(a, s);
+    if (a.N <= KmeansUpTo12288::kMaxN) return launch_kmeans_bits<KmeansUpTo12288>(a, s);
+    if (a.N <= KmeansUpTo16384::kMaxN) return launch_kmeans_bits<KmeansUpTo16384>(a, s);
+    return launch_kmeans_bits<KmeansBeyond>(a, s);
+}
+
 hipError_t launch_quantize(const QuantArgs& a, hipStream_t s) {
     u32* ws = static_cast<u32*>(a.workspace);
     const long long units = (long long)a.M * a.N / 8;
@@ -671,24 +727,7 @@ hipError_t launch_quantize(const QuantArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(quant_hist2_kernel, dim3(blocks), dim3(kPassThreads), 0, s, units, w4, s4, ws);
     hipLaunchKernelGGL(quant_count_kernel, dim3((a.M + kPassThreads / 64 - 1) / (kPassThreads / 64)), dim3(kPassThreads), 0, s, a.M, a.N,
                        static_cast<const uint16_t*>(a.w), static_cast<const uint16_t*>(a.sens), ws, a.rowptr);
-    // Threads per row by the row's LDS footprint (26 KB at 4096 weights, 66 KB at 11008, 159 KB at 28672, so six, two and one row per
-    // compute unit at a time): the iterations of a row are one chain of dependent steps, the other waves of the unit fill the gaps.
-    auto go = [](auto kernel, size_t lds) { return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); };
-    const int threads = a.N > 16384 ? 1024 : (a.N > 4096 ? 512 : 256);
-#define SQ_LAUNCH_KMEANS(B_, T_)                                                                                                     \
-    {                                                                                                                                \
-        const hipError_t e = go(&quant_kmeans_kernel<B_, T_>, kmeans_lds(KmeansShape<B_, T_>::kMaxN, KmeansShape<B_, T_>::NB));      \
-        if (e != hipSuccess) return e;                                                                                               \
-        hipLaunchKernelGGL((quant_kmeans_kernel<B_, T_>), dim3(a.M), dim3(T_), kmeans_lds(a.N, KmeansShape<B_, T_>::NB), s, a.M, a.N, a.max_iter, \
-                           static_cast<const uint16_t*>(a.w), static_cast<const uint16_t*>(a.sens), ws, a.rowptr, a.qidx,           \
-                           static_cast<uint16_t*>(a.lut), a.cols, static_cast<uint16_t*>(a.vals), a.iters);                         \
-    }
-#define SQ_LAUNCH_KMEANS_T(B_)                                                                                                      \
-    { if (threads == 1024) SQ_LAUNCH_KMEANS(B_, 1024) else if (threads == 512) SQ_LAUNCH_KMEANS(B_, 512) else SQ_LAUNCH_KMEANS(B_, 256) }
-    if (a.bits == 2) SQ_LAUNCH_KMEANS_T(2) else if (a.bits == 3) SQ_LAUNCH_KMEANS_T(3) else SQ_LAUNCH_KMEANS_T(4)
-#undef SQ_LAUNCH_KMEANS_T
-#undef SQ_LAUNCH_KMEANS
-    return hipGetLastError();
+    return launch_kmeans_shape(a, s);
 }
 
 }  // namespace sqllm
