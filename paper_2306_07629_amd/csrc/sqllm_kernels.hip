@@ -1403,39 +1403,77 @@ __global__ void __launch_bounds__(256) csr_rowwise_kernel(MatvecArgs g) {
     }
 }
 
-// ---------------------------------------------------------------------------------------------- parity exports
-// Same load, field extraction, table build and look-up as the matvec; one wave per (row, slice).
-// Without a table (lut == nullptr) the fp16 table is replaced by the bit patterns 0, 1, 2, ... so that the
-// look-up returns the indices themselves.
+// ---------------------------------------------------------------------------------------------- expansion to fp16 (or to one byte per index)
+// One wave expands up to kExpandUnits x 512 columns of a row: a lane handles eight neighbouring weights per unit, so that a wave reads a
+// contiguous piece of the index stream and writes 1 KB of fp16 (512 bytes of indices) with one instruction.  Same pair tables and field
+// order as the matvec; without a table the entries are the indices 0, 1, 2, ... themselves and the low bytes of the pairs are kept.
+// Every wave owns its table, so nothing waits for a barrier.  Bound by the writes: 13824x5120 at 3 bits 37.3 us (4.5 TB/s in and out; a
+// large copy reaches 5.0), against 54.4 us with 32 weights per lane and 16 dword stores at a stride of 64 bytes.
+// Eight units of requests in flight per wave; a wider row is split evenly so that no wave gets a short rest.
+constexpr int kExpandUnits = 8, kExpandWaves = 4;
+typedef u32x4 u32x4_a2 __attribute__((aligned(2)));                  // the outputs need not be aligned to more than one element
+typedef u32x2 u32x2_a1 __attribute__((aligned(1)));
+
+// the 8 BITS index bits of eight neighbouring weights (group g of the row; above them: other weights' bits)
 template <int BITS>
-__global__ void __launch_bounds__(64) decode_kernel(int M, int N, const void* qidx, const void* lut, void* idx_out, void* w_out) {
-    constexpr int K = 1 << BITS;
-    __shared__ __align__(8) u32 table[TableShape<BITS>::kTableDwords];
-    __shared__ __align__(16) uint16_t raw[K < 8 ? 8 : K];
-    const int lane = threadIdx.x;
-    const int row = blockIdx.y, slice = blockIdx.x;
-    const int j0 = slice * kSliceCols + lane * kLaneElems;
-    const bool live = j0 < N;
-    const int j0c = live ? j0 : N - kLaneElems;
-    const size_t row_dwords = (size_t)N * BITS / 32;
-    const u32* p = static_cast<const u32*>(qidx) + (size_t)row * row_dwords + (size_t)(j0c / 32) * BITS;
-    const LaneChunk<BITS> c = load_chunk<BITS>(p);
-    if (lane < K) raw[lane] = lut ? static_cast<const uint16_t*>(lut)[(size_t)row * K + lane] : (uint16_t)lane;
-    __syncthreads();
-    build_tables<BITS, 1>(table, raw, lane);
-    __syncthreads();
-    u32 w[16];
-    lookup_chunk<BITS>(c, table, w);
-    if (!live) return;
-    if (idx_out) {
-        uint8_t* o = static_cast<uint8_t*>(idx_out) + (size_t)row * N + j0;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) { o[2 * k] = (uint8_t)(w[k] & 0xFF); o[2 * k + 1] = (uint8_t)(w[k] >> 16); }
+__device__ __forceinline__ u32 load_group(const char* __restrict__ qrow, int g, int groups, int lane) {
+    if constexpr (BITS == 3) {
+        // four lanes share three dwords: lane l of the quad fetches dword l (lane 3 dword 2 again) and takes bits [24 l, 24 l + 24)
+        const int l = lane & 3, chunk = min(g >> 2, (groups >> 2) - 1);
+        const u32 d = __builtin_nontemporal_load(reinterpret_cast<const u32*>(qrow) + 3 * chunk + min(l, 2));
+        const u32 lo = (u32)__builtin_amdgcn_mov_dpp((int)d, 0x90, 0xF, 0xF, true);   // quad_perm [0,0,1,2]
+        const u32 hi = (u32)__builtin_amdgcn_mov_dpp((int)d, 0xA4, 0xF, 0xF, true);   // quad_perm [0,1,2,2]
+        return funnel_shr(hi, lo, (24u * (u32)l) & 31u);
+    } else if constexpr (BITS == 4) {
+        return __builtin_nontemporal_load(reinterpret_cast<const u32*>(qrow) + min(g, groups - 1));
+    } else {
+        return __builtin_nontemporal_load(reinterpret_cast<const uint16_t*>(qrow) + min(g, groups - 1));
     }
-    if (w_out) {
-        u32* o = reinterpret_cast<u32*>(static_cast<uint16_t*>(w_out) + (size_t)row * N + j0);
+}
+
+template <int BITS, bool INDICES>
+__global__ void __launch_bounds__(kExpandWaves * kWave) expand_kernel(int M, int N, int segs, const void* __restrict__ qidx, const uint16_t* __restrict__ lut, void* __restrict__ out) {
+    constexpr int K = 1 << BITS, E = TableShape<BITS>::kEntries;
+    __shared__ __align__(8) u32 tables[kExpandWaves][E];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int id = blockIdx.x * kExpandWaves + wave, row = id / segs, seg = id - row * segs;   // uniform
+    if (row >= M) return;
+    const int groups = N / 8, units = (groups + kWave - 1) / kWave, per = (units + segs - 1) / segs;   // per <= kExpandUnits
+    const int u0 = seg * per, n = min(per, units - u0);
+    const char* qrow = static_cast<const char*>(qidx) + (size_t)row * groups * BITS;
+    u32 v[kExpandUnits];
 #pragma unroll
-        for (int k = 0; k < 16; ++k) o[k] = w[k];
+    for (int k = 0; k < kExpandUnits; ++k)
+        if (k < n) v[k] = load_group<BITS>(qrow, (u0 + k) * kWave + lane, groups, lane);   // uniform branch
+    u32* table = tables[wave];
+    {
+        const uint16_t* t = INDICES ? nullptr : lut + (size_t)row * K;
+        const u32 kl = (u32)lane & (K - 1), lo = INDICES ? kl : t[kl];
+#pragma unroll
+        for (int e0 = 0; e0 < E; e0 += kWave) {
+            const u32 kh = (u32)((e0 + lane) >> BITS) & (K - 1), hi = INDICES ? kh : t[kh];
+            if (E >= kWave || lane < E) table[e0 + lane] = lo | (hi << 16);
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int k = 0; k < kExpandUnits; ++k) {
+        if (k >= n) break;                                           // uniform
+        u32 p[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) p[i] = table[(v[k] >> (2 * BITS * i)) & (E - 1)];
+        const int g = (u0 + k) * kWave + lane;
+        if (g < groups) {
+            if constexpr (INDICES) {
+                // bytes 0 and 2 of each pair
+                const u32x2 o = {__builtin_amdgcn_perm(p[1], p[0], 0x06040200u), __builtin_amdgcn_perm(p[3], p[2], 0x06040200u)};
+                *reinterpret_cast<u32x2_a1*>(static_cast<uint8_t*>(out) + (size_t)row * N + (size_t)g * 8) = o;
+            } else {
+                *reinterpret_cast<u32x4_a2*>(static_cast<uint16_t*>(out) + (size_t)row * N + (size_t)g * 8) = u32x4{p[0], p[1], p[2], p[3]};
+            }
+        }
     }
 }
 
@@ -1657,19 +1695,24 @@ hipError_t launch_csr_rowwise(const MatvecArgs& g0, hipStream_t s) {
     return hipSuccess;
 }
 
+template <int BITS>
+static void launch_expand(int M, int N, const void* qidx, const void* lut, void* idx_out, void* w_out, hipStream_t s) {
+    const int units = (N + 8 * kWave - 1) / (8 * kWave), segs = (units + kExpandUnits - 1) / kExpandUnits;
+    const dim3 grid((unsigned)((M * segs + kExpandWaves - 1) / kExpandWaves)), block(kExpandWaves * kWave);
+    if (w_out) hipLaunchKernelGGL((expand_kernel<BITS, false>), grid, block, 0, s, M, N, segs, qidx, static_cast<const uint16_t*>(lut), w_out);
+    else hipLaunchKernelGGL((expand_kernel<BITS, true>), grid, block, 0, s, M, N, segs, qidx, nullptr, idx_out);
+}
 hipError_t launch_decode(int M, int N, int bits, const void* qidx, const void* lut, void* idx_out, void* w_out, hipStream_t s) {
-    const int slices = (N + kSliceCols - 1) / kSliceCols;
-    // grid.y is limited to 65535 rows per launch
-    for (int m0 = 0; m0 < M; m0 += 65535) {
-        const int m = min(65535, M - m0);
-        const size_t qoff = (size_t)m0 * N * bits / 8;
-        const void* q = static_cast<const char*>(qidx) + qoff;
+    constexpr int kRows = 1 << 22;                                   // per launch: waves and threads of the grid stay below 2^31
+    for (int m0 = 0; m0 < M; m0 = M - m0 > kRows ? m0 + kRows : M) {
+        const int m = min(kRows, M - m0);
+        const void* q = static_cast<const char*>(qidx) + (size_t)m0 * N * bits / 8;
         const void* l = lut ? static_cast<const char*>(lut) + (size_t)m0 * (1 << bits) * 2 : nullptr;
         void* io = idx_out ? static_cast<char*>(idx_out) + (size_t)m0 * N : nullptr;
         void* wo = w_out ? static_cast<char*>(w_out) + (size_t)m0 * N * 2 : nullptr;
-        if (bits == 2) hipLaunchKernelGGL((decode_kernel<2>), dim3(slices, m), dim3(kWave), 0, s, m, N, q, l, io, wo);
-        else if (bits == 3) hipLaunchKernelGGL((decode_kernel<3>), dim3(slices, m), dim3(kWave), 0, s, m, N, q, l, io, wo);
-        else hipLaunchKernelGGL((decode_kernel<4>), dim3(slices, m), dim3(kWave), 0, s, m, N, q, l, io, wo);
+        if (bits == 2) launch_expand<2>(m, N, q, l, io, wo, s);
+        else if (bits == 3) launch_expand<3>(m, N, q, l, io, wo, s);
+        else launch_expand<4>(m, N, q, l, io, wo, s);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
