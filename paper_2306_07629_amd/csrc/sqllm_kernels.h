@@ -80,6 +80,7 @@ hipError_t quantize_static_scratch(void** device_ptr);   // the library's own wo
 hipError_t launch_quantize(const QuantArgs& a, hipStream_t s);
 
 hipError_t launch_matvec(const MatvecArgs& g, hipStream_t s);
+hipError_t launch_matvec_batch(const MatvecArgs& g, hipStream_t s);   // two to sixteen columns
 hipError_t launch_csr_rowwise(const MatvecArgs& g, hipStream_t s);
 hipError_t launch_decode(int M, int N, int bits, const void* qidx, const void* lut, void* idx_out, void* w_out, hipStream_t s);
 hipError_t launch_fp16_gemv(int M, int N, int B, const void* w, const void* x, void* y, hipStream_t s);

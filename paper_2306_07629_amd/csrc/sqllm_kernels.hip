@@ -33,34 +33,16 @@
 //   * matvec_multi_kernel / matvec_planned_multi_kernel run the workgroups of up to 16 layers in one grid: a workgroup
 //     finds its layer from the first-block table in the kernel arguments and then runs the same per-block code, so every y
 //     is bit for bit that of a launch of its own.
-// Batches: two to sixteen activation columns go to matvec_b16_kernel, which runs the dense and the sparse term on the
-// matrix cores (every lane decodes its own row, MFMAs replace the packed dot products); its header describes the
-// lane mapping.
+// Two to sixteen activation columns go to the matrix-core kernel in sqllm_batch.hip.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <string.h>
 #include <type_traits>
 
+#include "sqllm_decode.h"
 #include "sqllm_kernels.h"
 
 namespace sqllm {
-
-typedef _Float16 half_t;
-typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
-typedef uint32_t u32;
-typedef u32 u32x4 __attribute__((ext_vector_type(4)));
-typedef u32 u32x2 __attribute__((ext_vector_type(2)));
-
-constexpr int kWave = 64;
-constexpr int kLaneElems = 32;                      // indices per lane per row
-constexpr int kSliceCols = kWave * kLaneElems;      // 2048 columns per wave
-constexpr int kMaxDenseWaves = 14;                  // N <= 28672 (two more waves of the block take the sparse term)
-
-// ---------------------------------------------------------------------------------------------- helpers
-__device__ __forceinline__ u32 funnel_shr(u32 hi, u32 lo, u32 sh) { return __builtin_amdgcn_alignbit(hi, lo, sh); }
-__device__ __forceinline__ half2_t as_half2(u32 v) { return __builtin_bit_cast(half2_t, v); }
-__device__ __forceinline__ float half_bits_to_float(uint16_t h) { return (float)__builtin_bit_cast(half_t, h); }
-__device__ __forceinline__ uint16_t float_to_half_bits(float f) { return __builtin_bit_cast(uint16_t, (half_t)f); }
 
 // DPP controls (gfx9 encoding)
 constexpr int kQuadXor1 = 0xB1;        // quad_perm:[1,0,3,2]
@@ -89,21 +71,6 @@ __device__ __forceinline__ float wave_sum_to_lane63(float v) {
     v += dpp_f<kRowBcast15, 0xA>(0.f, v);           // rows 1 and 3 add the row before them
     v += dpp_f<kRowBcast31, 0xC>(0.f, v);           // rows 2 and 3 add lane 31 (= rows 0 + 1)
     return v;
-}
-
-// ---------------------------------------------------------------------------------------------- index stream
-// A lane's share of one row: BITS dwords = 32 indices.
-template <int BITS>
-struct LaneChunk {
-    u32 q[BITS];
-};
-
-template <int BITS>
-__device__ __forceinline__ LaneChunk<BITS> load_chunk(const u32* __restrict__ p) {
-    LaneChunk<BITS> c;
-#pragma unroll
-    for (int k = 0; k < BITS; ++k) c.q[k] = __builtin_nontemporal_load(p + k);
-    return c;
 }
 
 // the same from a uniform row pointer and the lane's dword offset inside the row: the address is formed by the load instruction
@@ -164,15 +131,6 @@ __device__ __forceinline__ u32 pair_offset_of(const LaneChunk<3>& c, int p) {
 }
 __device__ __forceinline__ u32 pair_offset_of(const LaneChunk<4>& c, int p) { return ((c.q[p >> 2] >> (8 * (p & 3))) & 0xFF) << 2; }
 __device__ __forceinline__ u32 pair_offset_of(const LaneChunk<2>& c, int p) { return ((c.q[p >> 3] >> (4 * (p & 7))) & 0xF) << 2; }
-
-template <int BITS>
-struct TableShape {
-    static constexpr int kEntryBits = 2 * BITS;               // a table entry holds the pair of two neighbouring indices: 4, 6 or 8 bits
-    static constexpr int kEntries = 1 << kEntryBits;          // 16, 64 or 256
-    static constexpr int kTableDwords = kEntries;             // LDS dwords of one row's table (one dword = two fp16 per entry)
-    static constexpr int kRowBytes = 2 << BITS;               // bytes of one row's fp16 table: 8, 16 or 32
-    static constexpr int kRawUnit = kRowBytes < 16 ? kRowBytes : 16;   // bytes of fp16 table one lane fetches
-};
 
 // Pair tables of R rows from their fp16 tables staged in LDS (raw[u << BITS | k]); executed by ONE wave.
 template <int BITS, int R>
@@ -925,453 +883,6 @@ __global__ void __launch_bounds__(1024) matvec_multi_kernel(MultiKernArgs<CsrLay
     matvec_block<BITS, R, D>(g, (int)blockIdx.x - m.first_block[l], NW);
 }
 
-// ---------------------------------------------------------------------------------------------- up to sixteen activation columns on the matrix cores
-// y[M][B] = (D + S) x[N][B] for 1 <= B <= 16 as a product of 16 x 16 tiles (v_mfma_f32_16x16x16_f16).  The
-// instruction multiplies A (16 rows x 16 k) by B (16 k x 16 columns): lane l supplies A[l % 16][4 (l / 16) + e]
-// and B[4 (l / 16) + e][l % 16], e = 0..3, and keeps D[4 (l / 16) + e][l % 16].
-//   * A workgroup owns R = 16 RG rows and all N columns; its NW waves deal the 128-column windows of the row out
-//     among themselves (wave w takes windows w, w + NW, ...).  In a window, lane (r, q) = (l % 16, l / 16) loads
-//     the 32 indices of row r of each row group at columns 128 t + 32 q + [0, 32), looks them up in that row's
-//     pair table -- the same decode as with one column -- and feeds weights 4 m .. 4 m + 3 to MFMA m (m = 0..7);
-//     as B operand the same lane holds the activations of batch column r at the same 32 columns, gathered from x
-//     with 16-bit loads (any row stride B <= 16, any parity) once per window and used for all RG row groups.
-//   * The sparse term runs on the matrix cores as well: 16 consecutive nonzeros are one MFMA whose A operand
-//     holds value p in the row of nonzero p (a lane compares p against the two row pointers of ITS row) and
-//     whose B operand holds the activations of column cols[p].  The steps of a row group -- aligned groups of 16
-//     nonzeros overlapping its CSR range -- are dealt out to the waves like the windows, so a heavy row is
-//     spread over all waves and no reduction other than the accumulators is needed.
-//   * Accumulators of the waves are combined through LDS in a fixed order; y is rounded to fp16 once.
-typedef _Float16 half4v_t __attribute__((ext_vector_type(4)));
-typedef float float4v_t __attribute__((ext_vector_type(4)));
-
-template <int E>
-__device__ __forceinline__ u32 quad_bcast(u32 v) {
-    return (u32)__builtin_amdgcn_mov_dpp((int)v, E * 0x55, 0xF, 0xF, true);   // quad_perm: every lane reads lane E of its quad
-}
-
-constexpr int kB16StageBytes = 16 * 400;                  // one window of x for 16 columns: 16 planes of 64 row pairs (fast path), or the window as it lies in memory plus the shifts of its quarters (4224 bytes)
-
-// Entry-major tables.  Lane l of a 16-lane group decodes its OWN matrix row, so the 32 lanes the LDS serves together
-// read 32 different (row, entry) addresses; with one table after the other every row's entries overlay the same
-// banks and the look-up takes ~7.5 cycles (hardware counters: 58 % of the LDS cycles were bank conflicts).  Here entry
-// e of the block's row rho lives at byte (e R + rho) * kEntryBytes: a row owns one bank, rows never
-// collide with each other and only the two lanes of one row can (2 passes per 32 lanes, as with one shared table).
-// LDS addresses of the 16 entries of a lane's chunk: entry index times the entry stride 1 << S, OR the
-// row's offset `base` < 1 << S (the tables start at LDS address 0: the kernel has no other static or dynamic LDS before them):
-template <int S>
-__device__ __forceinline__ void entry_offsets(const LaneChunk<3>& c, u32 base, u32 (&a)[16]) {
-#pragma unroll
-    for (int p = 0; p < 16; ++p) {
-        const int bit = 6 * p, d = bit >> 5, pos = bit & 31;
-        const u32 f = pos + 6 <= 32 ? (c.q[d] >> pos) & 63u : funnel_shr(c.q[(d + 1) % 3], c.q[d], pos) & 63u;   // a pair never starts in the last 6 bits of dword 2
-        a[p] = (f << S) | base;
-    }
-}
-template <int S>
-__device__ __forceinline__ void entry_offsets(const LaneChunk<4>& c, u32 base, u32 (&a)[16]) {
-#pragma unroll
-    for (int p = 0; p < 16; ++p) a[p] = (((c.q[p >> 2] >> (8 * (p & 3))) & 0xFFu) << S) | base;
-}
-template <int S>
-__device__ __forceinline__ void entry_offsets(const LaneChunk<2>& c, u32 base, u32 (&a)[16]) {
-#pragma unroll
-    for (int p = 0; p < 16; ++p) a[p] = (((c.q[p >> 3] >> (4 * (p & 7))) & 0xFu) << S) | base;
-}
-template <int BITS, int S>
-__device__ __forceinline__ void lookup_chunk_at(const LaneChunk<BITS>& c, u32 base, u32 (&w)[16]) {
-    u32 a[16];
-    entry_offsets<S>(c, base, a);
-#pragma unroll
-    for (int p = 0; p < 16; ++p) w[p] = *reinterpret_cast<const __attribute__((address_space(3))) u32*>(a[p]);
-}
-
-// Sparse term of the 16-column kernel.  Step j covers the nonzeros [16 j, 16 j + 16); the steps overlapping the CSR
-// range of row group rg are first[rg] .. first[rg] + count[rg] - 1, and flat step f of the block runs through the
-// row groups in order.  A wave handles NS flat steps f0, f0 + NW, ... per round: all column / value loads, then all
-// activation gathers, then the products.  Slots past the block's last step re-read step 0 and contribute nothing.
-template <int RG, int NS>
-struct B16SparseSlots {
-    int srg[NS], sj[NS];      // uniform: row group (-1: none) and step of each slot
-    u32 col[NS], val[NS];     // lane e of a quad holds nonzero 16 j + 4 q + e
-};
-
-template <int RG, int NS>
-__device__ __forceinline__ void b16_sparse_issue(const MatvecArgs& g, const int (&first)[RG], const int (&count)[RG], int total, int f0, int NW,
-                                                 int lane, B16SparseSlots<RG, NS>& S) {
-    const int last_nz = (int)g.nnz - 1;
-    const uint16_t* __restrict__ vals = static_cast<const uint16_t*>(g.vals);
-    const int e4 = 4 * (lane >> 4) + (lane & 3);
-#pragma unroll
-    for (int k = 0; k < NS; ++k) {
-        int f = f0 + k * NW;
-        S.srg[k] = -1; S.sj[k] = 0;
-        if (f < total) {
-#pragma unroll
-            for (int rg = 0; rg < RG; ++rg) {
-                if (S.srg[k] < 0) {
-                    if (f < count[rg]) { S.srg[k] = rg; S.sj[k] = first[rg] + f; }
-                    else f -= count[rg];
-                }
-            }
-        }
-        const int pl = min(16 * S.sj[k] + e4, last_nz);
-        S.col[k] = (u32)g.cols[pl];
-        S.val[k] = vals[pl];
-    }
-}
-
-// QT (B a multiple of 4): the activations of a step are gathered with ONE 8-byte load per lane -- lane e of a quad reads
-// the four columns 4 (n / 4) .. + 3 of the x row of ITS nonzero -- and a 4 x 4 transposition inside the quad (three quad
-// permutes) hands every lane its own column of all four nonzeros; otherwise four 16-bit loads per lane.
-template <int RG, int NS, bool QT>
-__device__ __forceinline__ void b16_sparse_finish(const uint16_t* __restrict__ x, int B, int nb, u32 xmask, int lane, const int (&lo)[RG], const int (&hi)[RG],
-                                                  const B16SparseSlots<RG, NS>& S, float4v_t (&acc)[RG]) {
-    const int q = lane >> 4;
-    const char* xb = reinterpret_cast<const char*>(x);
-    u32 xa[NS][2], aa[NS][2];
-    if constexpr (QT) {
-        const u32 cg = 4u * ((u32)nb >> 2);                          // first column of the lane's group of four (0 for absent columns)
-        const bool odd = (lane & 1) != 0, upper = (lane & 2) != 0;
-        const u32 sel = odd ? 0x03020706u : 0x05040100u;
-        u32x2 d[NS];
-#pragma unroll
-        for (int k = 0; k < NS; ++k) d[k] = *reinterpret_cast<const u32x2*>(xb + 2u * (S.col[k] * (u32)B + cg));   // byte offsets fit 32 bits
-#pragma unroll
-        for (int k = 0; k < NS; ++k) {
-            // rows = the quad's four nonzeros, columns = the group's four batch columns; first the 2 x 2 blocks of halves ...
-            const u32 p0 = (u32)__builtin_amdgcn_mov_dpp((int)d[k].x, 0xB1, 0xF, 0xF, true), p1 = (u32)__builtin_amdgcn_mov_dpp((int)d[k].y, 0xB1, 0xF, 0xF, true);
-            const u32 e0 = __builtin_amdgcn_perm(p0, d[k].x, sel), e1 = __builtin_amdgcn_perm(p1, d[k].y, sel);
-            // ... then the dwords between lanes 2 apart
-            const u32 send = upper ? e0 : e1;
-            const u32 recv = (u32)__builtin_amdgcn_mov_dpp((int)send, 0x4E, 0xF, 0xF, true);
-            xa[k][0] = (upper ? recv : e0) & xmask;
-            xa[k][1] = (upper ? e1 : recv) & xmask;
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < NS; ++k) {
-            // byte offsets fit 32 bits: N * B * 2 < 2^20
-            const u32 c0 = quad_bcast<0>(S.col[k]), c1 = quad_bcast<1>(S.col[k]), c2 = quad_bcast<2>(S.col[k]), c3 = quad_bcast<3>(S.col[k]);
-            const u32 x0 = *reinterpret_cast<const uint16_t*>(xb + 2u * (c0 * (u32)B + (u32)nb)), x1 = *reinterpret_cast<const uint16_t*>(xb + 2u * (c1 * (u32)B + (u32)nb));
-            const u32 x2 = *reinterpret_cast<const uint16_t*>(xb + 2u * (c2 * (u32)B + (u32)nb)), x3 = *reinterpret_cast<const uint16_t*>(xb + 2u * (c3 * (u32)B + (u32)nb));
-            xa[k][0] = (x0 | (x1 << 16)) & xmask;
-            xa[k][1] = (x2 | (x3 << 16)) & xmask;
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < NS; ++k) {
-        const int p0 = 16 * S.sj[k] + 4 * q;
-        int l = 0, h = 0;
-#pragma unroll
-        for (int rg = 0; rg < RG; ++rg) { if (S.srg[k] == rg) { l = lo[rg]; h = hi[rg]; } }
-        const u32 v0 = quad_bcast<0>(S.val[k]), v1 = quad_bcast<1>(S.val[k]), v2 = quad_bcast<2>(S.val[k]), v3 = quad_bcast<3>(S.val[k]);
-        // value p goes to the row whose CSR range holds p: 0 <= p - l < h - l as one unsigned comparison
-        const u32 span = (u32)(h - l), d0 = (u32)(p0 - l);
-        const u32 a0 = d0 < span ? v0 : 0u, a1 = d0 + 1u < span ? v1 : 0u, a2 = d0 + 2u < span ? v2 : 0u, a3 = d0 + 3u < span ? v3 : 0u;
-        aa[k][0] = a0 | (a1 << 16);
-        aa[k][1] = a2 | (a3 << 16);
-    }
-#pragma unroll
-    for (int k = 0; k < NS; ++k) {
-        const half4v_t a = __builtin_bit_cast(half4v_t, u32x2{aa[k][0], aa[k][1]});
-        const half4v_t b = __builtin_bit_cast(half4v_t, u32x2{xa[k][0], xa[k][1]});
-#pragma unroll
-        for (int rg = 0; rg < RG; ++rg)
-            if (S.srg[k] == rg) acc[rg] = __builtin_amdgcn_mfma_f32_16x16x16f16(a, b, acc[rg], 0, 0, 0);   // uniform branch
-    }
-}
-
-// B4 = 1..4: the batch is exactly 4 B4 columns (4, 8, 12 or 16); B4 = 5: exactly 2 columns -- the activations take the
-// fast paths below;  B4 == 0: any batch up to 16, activations staged as they lie in memory.
-template <int BITS, int RG, int B4>
-__global__ void __launch_bounds__(1024) matvec_b16_kernel(MatvecArgs g) {
-    constexpr int R = 16 * RG, K = 1 << BITS;
-    constexpr int TD = TableShape<BITS>::kTableDwords;
-    constexpr int kRawUnit = TableShape<BITS>::kRawUnit;
-    constexpr int kRawLanes = R * TableShape<BITS>::kRowBytes / kRawUnit;
-    constexpr int kWinCols = 128;
-    extern __shared__ __align__(2048) char smem16[];
-    u32* tables = reinterpret_cast<u32*>(smem16);                                   // R tables, each 4 TD bytes (a power of two)
-    uint16_t* raw = reinterpret_cast<uint16_t*>(smem16 + R * TD * 4);               // fp16 tables as loaded
-    char* stage0 = smem16 + R * TD * 4 + R * K * 2;                                 // per wave: staging of one x window, later its partial sums
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);     // uniform, and known to be: addresses derived from it stay in scalar registers
-    const int NW = blockDim.x >> 6;
-    const int r = lane & 15, q = lane >> 4;
-    const int r0 = blockIdx.x * R;
-    const int nrows = min(R, g.M - r0);
-    const int B = g.B;
-    const bool dense = g.qidx != nullptr, sparse = g.nnz > 0;
-    const uint16_t* __restrict__ x = static_cast<const uint16_t*>(g.x);
-    const int nwin = dense ? g.N / kWinCols : 0;
-    char* stage = stage0 + wave * kB16StageBytes;
-    const int NWD = dense ? NW : 0;                                  // every wave takes windows of the dense term (if there is one) ...
-    const bool sparse_wave = sparse;                                 // ... and afterwards a share of the sparse term
-
-    // ---- fp16 tables of the block's rows -> LDS
-    if (dense && tid < kRawLanes) {
-        const int u = tid * kRawUnit / TableShape<BITS>::kRowBytes;
-        const int row = min(r0 + u, g.M - 1);
-        const char* src = static_cast<const char*>(g.lut) + (size_t)row * TableShape<BITS>::kRowBytes + (tid * kRawUnit) % TableShape<BITS>::kRowBytes;
-        if constexpr (kRawUnit == 16) *reinterpret_cast<u32x4*>(raw + tid * 8) = *reinterpret_cast<const u32x4*>(src);
-        else *reinterpret_cast<u32x2*>(raw + tid * 4) = *reinterpret_cast<const u32x2*>(src);
-    }
-    // row pointers of the lane's own row in every row group (rows past M are empty)
-    int lo[RG], hi[RG];
-#pragma unroll
-    for (int rg = 0; rg < RG; ++rg) {
-        lo[rg] = sparse_wave ? g.rowptr[min(r0 + 16 * rg + r, g.M)] : 0;
-        hi[rg] = sparse_wave ? g.rowptr[min(r0 + 16 * rg + r + 1, g.M)] : 0;
-    }
-    const size_t row_dwords = (size_t)g.N * BITS / 32;
-    const int nb = r < B ? r : 0;                                    // lanes of absent columns read column 0 and are zeroed
-    const u32 xmask = r < B ? 0xFFFFFFFFu : 0u;
-    auto load_idx = [&](int t, LaneChunk<BITS> (&c)[RG]) {
-#pragma unroll
-        for (int rg = 0; rg < RG; ++rg) {
-            const int row = min(r0 + 16 * rg + r, g.M - 1);
-            c[rg] = load_chunk<BITS>(static_cast<const u32*>(g.qidx) + (size_t)row * row_dwords + (size_t)(4 * t + q) * BITS);
-        }
-    };
-    // Activations of a window: the 128 rows of x are 64 B contiguous dwords.  They are copied to LDS as they lie in
-    // memory (coalesced loads, 16 B dwords per quarter of the window, every quarter shifted by 32 bytes so that the four
-    // lane groups read different banks), and each lane then picks the 32 halves of ITS column with 16-bit reads.
-    // Load slot (qq, ii) covers dwords 64 ii + lane of quarter qq; slots past the quarter re-read its last dword.
-    const int qd = 16 * B;                                           // dwords of one quarter (32 rows of x)
-    u32 eoff[4];                                                     // byte offset of the lane's dword in load slot ii of a quarter
-#pragma unroll
-    for (int ii = 0; ii < 4; ++ii) eoff[ii] = 4u * (u32)min(64 * ii + lane, qd - 1);
-    const u32 stage_lds = (u32)(size_t)stage;                        // LDS byte address of the wave's staging area (uniform)
-    constexpr int kEntryBytes = 4;                                    // one pair of fp16 per entry
-    constexpr int kStrideLog2 = (RG == 2 ? 5 : 4) + 2;               // log2(R * kEntryBytes): bytes from one entry to the next
-    const u32 tab0 = (u32)r * kEntryBytes;                           // the lane's row of row group 0; the tables start at LDS address 0
-    constexpr int BT = B4 == 5 ? 2 : 4 * B4, kPitch = 256 + 16;      // fast path: columns, bytes of one column's 64 row pairs (+ bank shift)
-    constexpr u32 kPitchQ = 400;                                     // plane pitch of the 8- and 16-column paths: 64 row pairs + up to 24 dwords of rotation
-    auto load_xblock = [&](int t, u32 (&v)[16]) {
-        if constexpr (B4 == 4 || B4 == 2) {
-            // fully coalesced: load i of lane l is the 16-byte unit 64 i + l of the window (half a row of 16 columns, or
-            // a whole row of 8); the neighbouring row sits two lanes (one lane) further and is fetched with a quad permute
-            const u32x4* src = reinterpret_cast<const u32x4*>(x + (size_t)t * kWinCols * BT) + lane;
-#pragma unroll
-            for (int i = 0; i < B4; ++i) {
-                const u32x4 v4 = src[64 * i];
-                v[4 * i] = v4.x; v[4 * i + 1] = v4.y; v[4 * i + 2] = v4.z; v[4 * i + 3] = v4.w;
-            }
-        } else if constexpr (B4 > 0) {
-            // lane l fetches rows 2 l and 2 l + 1 of the window: 4 BT contiguous bytes
-            const char* src = reinterpret_cast<const char*>(x + (size_t)t * kWinCols * BT) + (u32)lane * 4u * BT;
-            if constexpr (BT == 2) {
-                const u32x2 v2 = *reinterpret_cast<const u32x2*>(src);
-                v[0] = v2.x; v[1] = v2.y;
-            } else {
-#pragma unroll
-                for (int i = 0; i < BT / 4; ++i) {
-                    const u32x4 v4 = reinterpret_cast<const u32x4*>(src)[i];
-                    v[4 * i] = v4.x; v[4 * i + 1] = v4.y; v[4 * i + 2] = v4.z; v[4 * i + 3] = v4.w;
-                }
-            }
-        } else {
-            const char* src = reinterpret_cast<const char*>(x + (size_t)t * kWinCols * B);   // uniform
-#pragma unroll
-            for (int qq = 0; qq < 4; ++qq) {
-                const char* sq = src + (size_t)(4 * qq * qd);        // uniform
-#pragma unroll
-                for (int ii = 0; ii < 4; ++ii) v[4 * qq + ii] = *reinterpret_cast<const u32*>(sq + eoff[ii]);
-            }
-        }
-    };
-    const u32 rd0 = stage_lds + 4u * q * qd + 32u * q + 2u * nb;     // slow path: row 32 q of the window, column nb
-    auto stage_x = [&](const u32 (&v)[16], u32 (&xb)[16]) {
-        if constexpr (B4 == 4 || B4 == 2) {
-            // own row k and its neighbour k ^ 1 (lane ^ 2 for 16 columns, lane ^ 1 for 8): the lane of the even row forms
-            // the pair (x[k][n], x[k + 1][n]) of the even column n of each dword, the lane of the odd row that of the odd column
-            const bool keven = B4 == 4 ? (lane & 2) == 0 : (lane & 1) == 0;
-            const u32 sel = keven ? 0x05040100u : 0x03020706u;
-            // Plane n holds the 64 row pairs of column n, rotated by rot(n) dwords (planes of kPitchQ = 100 dwords, so a
-            // rotated plane needs no wrap-around).  The rotation makes BOTH sides conflict-free: the 32 lanes the LDS
-            // serves together write 8 (16) consecutive row pairs of 4 (2) planes whose bank offsets 4 n + rot(n) are 0, 8,
-            // 16, 24 (0, 16) apart, and 8 neighbouring lanes read 16 bytes of 8 planes whose offsets are the 8 multiples
-            // of 4.  Without it every write was a 4-way conflict (counters: 61 % of the LDS cycles).
-            //   16 columns: rot(n) = 4 + 4 [n%4 == 1] - 4 [n%4 == 2] + 16 [n >= 8];   8 columns: rot(n) = 12 - 4 (n / 2) + 12 (n % 2)
-            const u32 odd = keven ? 0u : 1u, h = (u32)lane & 1u;
-            const u32 wr = B4 == 4 ? stage_lds + (8u * h + odd) * kPitchQ + ((u32)(lane >> 2) + 4u * odd + 16u * h) * 4u
-                                   : stage_lds + odd * kPitchQ + ((u32)(lane >> 1) + 12u * odd) * 4u;
-#pragma unroll
-            for (int i = 0; i < B4; ++i)
-#pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    const u32 own = v[4 * i + d];
-                    const u32 other = (u32)__builtin_amdgcn_mov_dpp((int)own, B4 == 4 ? 0x4E : 0xB1, 0xF, 0xF, true);   // quad_perm [2,3,0,1] / [1,0,3,2]
-                    const u32 pair = __builtin_amdgcn_perm(other, own, sel);
-                    const u32 off = B4 == 4 ? (u32)(2 * d) * kPitchQ + 64u * i + 16u * (1 - (d & 1))
-                                            : (u32)(2 * d) * kPitchQ + 128u * i + 4u * (12 - 4 * d);
-                    *reinterpret_cast<__attribute__((address_space(3))) u32*>(wr + off) = pair;
-                }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            const u32 n3 = (u32)nb & 3u;
-            const u32 rot = B4 == 4 ? 4u + (n3 == 1u ? 4u : 0u) - (n3 == 2u ? 4u : 0u) + 16u * ((u32)nb >> 3)
-                                    : 12u - 4u * (((u32)nb & 7u) >> 1) + 12u * ((u32)nb & 1u);
-            const u32 rd = stage_lds + (u32)nb * kPitchQ + ((u32)q * 16u + rot) * 4u;
-            const u32 xm = B4 == 4 ? 0xFFFFFFFFu : xmask;            // with 16 columns every lane's column exists
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const u32x4 v4 = *reinterpret_cast<const __attribute__((address_space(3))) u32x4*>(rd + 16u * i);
-                xb[4 * i] = v4.x & xm; xb[4 * i + 1] = v4.y & xm; xb[4 * i + 2] = v4.z & xm; xb[4 * i + 3] = v4.w & xm;
-            }
-        } else if constexpr (B4 > 0) {
-            // v[d], d < BT / 2: columns 2 d, 2 d + 1 of row 2 l; v[BT / 2 + d]: the same of row 2 l + 1.  The pair
-            // (x[2 l][n], x[2 l + 1][n]) goes to dword l of column n's plane; lane (n, q) then reads 64 bytes of plane n.
-#pragma unroll
-            for (int n = 0; n < BT; ++n) {
-                const u32 pair = __builtin_amdgcn_perm(v[BT / 2 + n / 2], v[n / 2], (n & 1) ? 0x07060302u : 0x05040100u);
-                *reinterpret_cast<__attribute__((address_space(3))) u32*>(stage_lds + (u32)n * kPitch + (u32)lane * 4u) = pair;
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            const u32 rd = stage_lds + (u32)nb * kPitch + (u32)q * 64u;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const u32x4 v4 = *reinterpret_cast<const __attribute__((address_space(3))) u32x4*>(rd + 16u * i);
-                xb[4 * i] = v4.x & xmask; xb[4 * i + 1] = v4.y & xmask; xb[4 * i + 2] = v4.z & xmask; xb[4 * i + 3] = v4.w & xmask;
-            }
-        } else {
-            // the strides are recomputed from a copy of B the compiler cannot see through: hoisted out of the window
-            // loop the 48 addresses would occupy 48 registers for the whole kernel
-            u32 Bl = (u32)B;
-            asm volatile("" : "+s"(Bl));
-#pragma unroll
-            for (int qq = 0; qq < 4; ++qq) {
-                const u32 base = stage_lds + 64u * qq * Bl + 32u * qq;   // uniform
-#pragma unroll
-                for (int ii = 0; ii < 4; ++ii)
-                    *reinterpret_cast<__attribute__((address_space(3))) u32*>(base + eoff[ii]) = v[4 * qq + ii];
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-            for (int p = 0; p < 16; ++p) {
-                const u32 a = *reinterpret_cast<const __attribute__((address_space(3))) uint16_t*>(rd0 + (u32)(2 * p) * 2u * Bl);
-                const u32 b = *reinterpret_cast<const __attribute__((address_space(3))) uint16_t*>(rd0 + (u32)(2 * p + 1) * 2u * Bl);
-                xb[p] = (a | (b << 16)) & xmask;
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    };
-    // ---- the first two windows of this wave are requested before the tables are built
-    LaneChunk<BITS> c0[RG], c1[RG], c2[RG];
-    u32 xb[16], xv[16];
-    int t = dense ? wave : 0;                                        // wave w takes windows w, w + NWD, ... (NWD <= nwin)
-    const int last_t = t < nwin ? wave + ((nwin - 1 - wave) / NWD) * NWD : 0;   // this wave's last window
-    if (t < nwin) {
-        load_xblock(t, xv);
-        load_idx(t, c0);
-        load_idx(min(t + NWD, last_t), c1);
-    }
-    __syncthreads();
-    if (dense)
-        for (int o = tid; o < R * TableShape<BITS>::kEntries; o += blockDim.x) {
-            // consecutive threads write consecutive rows of one entry (conflict-free); see entry_offsets for the layout
-            const int rho = o % R, e = o / R;
-            const uint16_t* rr = raw + rho * K;
-            const u32 lo16 = rr[e & (K - 1)], hi16 = rr[e >> BITS];
-            tables[o] = lo16 | (hi16 << 16);
-        }
-    __syncthreads();
-
-    float4v_t acc[RG];
-#pragma unroll
-    for (int rg = 0; rg < RG; ++rg) acc[rg] = float4v_t{0.f, 0.f, 0.f, 0.f};
-
-    // ---- dense term: windows t, t + NW, ...  Indices are requested two windows ahead, activations one window ahead
-    //      (from L2) and staged while the matrix cores work on the current window.  Past the wave's last window the
-    //      requests repeat that window (valid addresses, results unused) instead of branching around loads.
-    if (t < nwin) {
-        stage_x(xv, xb);
-        load_xblock(min(t + NWD, last_t), xv);
-    }
-    for (; t < nwin; t += NWD) {
-        load_idx(min(t + 2 * NWD, last_t), c2);
-        u32 w[2][16];
-        lookup_chunk_at<BITS, kStrideLog2>(c0[0], tab0, w[0]);
-#pragma unroll
-        for (int rg = 0; rg < RG; ++rg) {
-            if (rg + 1 < RG) lookup_chunk_at<BITS, kStrideLog2>(c0[rg + 1], tab0 + 16u * (rg + 1) * kEntryBytes, w[(rg + 1) & 1]);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int m = 0; m < 8; ++m) {
-                const half4v_t a = __builtin_bit_cast(half4v_t, u32x2{w[rg & 1][2 * m], w[rg & 1][2 * m + 1]});
-                const half4v_t b = __builtin_bit_cast(half4v_t, u32x2{xb[2 * m], xb[2 * m + 1]});
-                acc[rg] = __builtin_amdgcn_mfma_f32_16x16x16f16(a, b, acc[rg], 0, 0, 0);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        stage_x(xv, xb);                                             // window t + NWD
-        load_xblock(min(t + 2 * NWD, last_t), xv);
-#pragma unroll
-        for (int rg = 0; rg < RG; ++rg) { c0[rg] = c1[rg]; c1[rg] = c2[rg]; }
-    }
-
-    // ---- sparse term, after the dense windows: every wave takes steps wave, wave + NW, ... of the block (a heavy row
-    //      is spread over all waves); rounds of 4 steps per wave, of 8 while more than 4 NW steps are left, of 12 beyond
-    //      8 NW (16 would spill; 8192x8192 at 16 columns: 23.1 -> 22.2 us with the rounds of 12)
-    if (sparse_wave) {
-        int first[RG], count[RG], total = 0;                         // uniform
-#pragma unroll
-        for (int rg = 0; rg < RG; ++rg) {
-            const int P0 = __builtin_amdgcn_readlane(lo[rg], 0), P1 = __builtin_amdgcn_readlane(hi[rg], 15);
-            first[rg] = P0 >> 4;
-            count[rg] = P1 > P0 ? ((P1 - 1) >> 4) - (P0 >> 4) + 1 : 0;
-            total += count[rg];
-        }
-        int f0 = wave;
-        while (f0 < total) {
-            if (total - f0 > 8 * NW) {
-                B16SparseSlots<RG, 12> S;
-                b16_sparse_issue<RG, 12>(g, first, count, total, f0, NW, lane, S);
-                b16_sparse_finish<RG, 12, (B4 >= 1 && B4 <= 4)>(x, B, nb, xmask, lane, lo, hi, S, acc);
-                f0 += 12 * NW;
-            } else if (total - f0 > 4 * NW) {
-                B16SparseSlots<RG, 8> S;
-                b16_sparse_issue<RG, 8>(g, first, count, total, f0, NW, lane, S);
-                b16_sparse_finish<RG, 8, (B4 >= 1 && B4 <= 4)>(x, B, nb, xmask, lane, lo, hi, S, acc);
-                f0 += 8 * NW;
-            } else {
-                B16SparseSlots<RG, 4> S;
-                b16_sparse_issue<RG, 4>(g, first, count, total, f0, NW, lane, S);
-                b16_sparse_finish<RG, 4, (B4 >= 1 && B4 <= 4)>(x, B, nb, xmask, lane, lo, hi, S, acc);
-                f0 += 4 * NW;
-            }
-        }
-    }
-
-    // ---- combine the waves' accumulators in a fixed order: lane (r, q) holds rows 4 q + e of column r
-#pragma unroll
-    for (int rg = 0; rg < RG; ++rg) {
-        const float v[4] = {acc[rg].x, acc[rg].y, acc[rg].z, acc[rg].w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) reinterpret_cast<float*>(stage)[(16 * rg + 4 * q + e) * 16 + r] = v[e];
-    }
-    __syncthreads();
-    uint16_t* __restrict__ y = static_cast<uint16_t*>(g.y);
-    for (int o = tid; o < R * 16; o += blockDim.x) {
-        const int row = o >> 4, n = o & 15;
-        if (row < nrows && n < B) {
-            float sum = 0.f;
-            for (int wv = 0; wv < NW; ++wv) sum += reinterpret_cast<const float*>(stage0 + wv * kB16StageBytes)[row * 16 + n];
-            const size_t yo = (size_t)(r0 + row) * B + n;
-            if (g.accumulate) sum += half_bits_to_float(y[yo]);
-            y[yo] = float_to_half_bits(sum);
-        }
-    }
-}
-
 // ---------------------------------------------------------------------------------------------- standard CSR kernel
 // one thread per row (the kernel the paper's App. C calls "standard")
 template <int NB>
@@ -1635,49 +1146,13 @@ hipError_t launch_matvec_multi(const MultiArgs& m, int bits, int R, hipStream_t 
     return bits == 2 ? launch_multi_r<2, 4>(m, s) : (bits == 3 ? launch_multi_r<3, 4>(m, s) : launch_multi_r<4, 4>(m, s));
 }
 
-// up to 16 columns in one launch: 32 rows per workgroup when that still gives every compute unit a workgroup
-// Measured (8192x8192, 11008x4096, 4096x4096, 22016x8192 at 16 columns): 8 waves per workgroup beat 16 (fused 23.4 / 22.2 /
-// 9.8 us against 24.3 / 27.6 / 11.0) and 4 (the sparse term then has too few waves); 32 rows per workgroup beat 16 from
-// M = 8192 on (dense 15.1 against 19.6 us: the activations a workgroup stages serve twice the rows).
-constexpr int kB16Waves = 8;
-constexpr int kB16TwoGroupsMinM = 8192;
-template <int BITS, int RG, int B4>
-static hipError_t launch_matvec_b16_r(const MatvecArgs& g, hipStream_t s) {
-    constexpr int R = 16 * RG;
-    const int nwin = g.qidx ? g.N / 128 : 0;
-    const int NW = nwin ? (nwin < kB16Waves ? nwin : kB16Waves) : kB16Waves;   // without a dense term all waves share the sparse steps
-    const size_t lds = (size_t)R * TableShape<BITS>::kTableDwords * 4 + (size_t)R * (2 << BITS) + (size_t)NW * kB16StageBytes;
-    // raised on every launch: the attribute belongs to the current device's copy of the kernel, and the call is a host-side table update
-    const hipError_t ea = hipFuncSetAttribute(reinterpret_cast<const void*>(&matvec_b16_kernel<BITS, RG, B4>), hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024);
-    if (ea != hipSuccess) return ea;
-    hipLaunchKernelGGL((matvec_b16_kernel<BITS, RG, B4>), dim3((g.M + R - 1) / R), dim3(NW * kWave), lds, s, g);
-    return hipGetLastError();
-}
-template <int BITS, int RG>
-static hipError_t launch_matvec_b16_b(const MatvecArgs& g, hipStream_t s) {
-    // batches of exactly 2, 4, 8, 12 or 16 columns: pairs of rows of x are whole 8- or 16-byte units and take the fast
-    // activation paths
-    switch (g.B) {
-        case 2: return launch_matvec_b16_r<BITS, RG, 5>(g, s);
-        case 4: return launch_matvec_b16_r<BITS, RG, 1>(g, s);
-        case 8: return launch_matvec_b16_r<BITS, RG, 2>(g, s);
-        case 12: return launch_matvec_b16_r<BITS, RG, 3>(g, s);
-        case 16: return launch_matvec_b16_r<BITS, RG, 4>(g, s);
-        default: return launch_matvec_b16_r<BITS, RG, 0>(g, s);
-    }
-}
-template <int BITS>
-static hipError_t launch_matvec_b16(const MatvecArgs& g, hipStream_t s) {
-    return g.M >= kB16TwoGroupsMinM ? launch_matvec_b16_b<BITS, 2>(g, s) : launch_matvec_b16_b<BITS, 1>(g, s);
-}
-
 hipError_t launch_matvec(const MatvecArgs& g, hipStream_t s) {
     // one column: the vector-ALU kernel; two or more: one launch of the 16-column kernel (every weight is decoded once for all
     // columns), also without a dense term
     if (g.B == 1 && g.plan && g.qidx && g.nnz > 0 && !g.accumulate)
         return g.bits == 2 ? launch_matvec_planned<2>(g, s) : (g.bits == 3 ? launch_matvec_planned<3>(g, s) : launch_matvec_planned<4>(g, s));
     if (g.B == 1) return g.bits == 2 ? launch_matvec_one<2>(g, s) : (g.bits == 3 ? launch_matvec_one<3>(g, s) : launch_matvec_one<4>(g, s));
-    return g.bits == 2 ? launch_matvec_b16<2>(g, s) : (g.bits == 3 ? launch_matvec_b16<3>(g, s) : launch_matvec_b16<4>(g, s));
+    return launch_matvec_batch(g, s);
 }
 
 hipError_t launch_csr_rowwise(const MatvecArgs& g0, hipStream_t s) {

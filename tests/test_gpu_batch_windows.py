@@ -1,0 +1,77 @@
+"""The batch kernel where its split can go wrong: the row counts at which the rows and waves per workgroup change, a last row group of one
+row, fewer windows than dense waves, rows whose nonzeros fill many windows (what the sparse waves leave over is shared by all waves), every
+batch size with and without a dense term, and an infinite activation, which must stay with the rows that share a 16-row tile with its
+nonzero.  Bounds: 2e-3 sum |W||x| against the fp64 oracle, plus half the spacing of subnormal results."""
+import numpy as np
+import pytest
+
+import gen
+import oracle
+
+pytestmark = pytest.mark.gpu
+TOL = 2e-3
+
+
+def check(y, ref, absdot, what):
+    err = np.abs(y.cpu().numpy().view(np.float16).astype(np.float64) - ref)
+    assert (err <= TOL * absdot + 2.0 ** -25).all(), (what, float(np.max(err / (TOL * absdot + 2.0 ** -25))))
+
+
+@pytest.mark.parametrize("M,N,bits,B", [(4096, 128, 3, 16), (4097, 256, 4, 5), (8192, 384, 2, 7), (8193, 1024, 3, 13), (17, 5120, 4, 8),
+                                        (33, 640, 2, 3), (1, 28672, 3, 16)])
+def test_row_counts_where_the_split_changes(M, N, bits, B):
+    import paper_2306_07629_amd as sq
+    print(f"batch M={M} N={N} bits={bits} B={B}", flush=True)
+    for frac, skew in ((0.0, None), (0.01, (0.1, 0.5))):
+        L = gen.make_layer(M, N, bits, frac=frac, skew=skew, B=B, seed=M + N + B)
+        D = sq.DeviceLayer(L)
+        ref, absdot = oracle.layer_matvec(L)
+        check(D.matvec(), ref, absdot, ("fused", frac))
+
+
+@pytest.mark.parametrize("B", list(range(2, 17)))
+def test_heavy_rows_fill_many_windows(B):
+    """two full rows of 6144 columns (48 windows each) in one workgroup, neighbours empty or with a few nonzeros"""
+    import torch
+    import paper_2306_07629_amd as sq
+    M, N, bits = 50, 6144, 3
+    print(f"heavy B={B}", flush=True)
+    L = gen.make_layer(M, N, bits, frac=0.0, skew=None, B=B, seed=B)
+    rng = np.random.default_rng(B)
+    counts = rng.integers(0, 40, M)
+    counts[[3, 20]] = N
+    counts[[4, 15, 16, 49]] = 0
+    rowptr = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    cols = np.concatenate([np.sort(rng.choice(N, c, replace=False)) for c in counts]).astype(np.int32)
+    vals = (rng.standard_normal(cols.size) * 0.1).astype(np.float16).view(np.uint16)
+    L.rowptr, L.cols, L.vals, L.nnz = rowptr, cols, vals, int(cols.size)
+    D = sq.DeviceLayer(L)
+    ref, absdot = oracle.matvec(M, N, bits, B, L.qidx, L.lut, rowptr, cols, vals, L.x)
+    y = D.matvec().clone()
+    check(y, ref, absdot, "fused")
+    assert torch.equal(D.matvec(), y)                                # a fixed order of additions
+    zero = np.zeros_like(L.lut)
+    ref, absdot = oracle.matvec(M, N, bits, B, L.qidx, zero, rowptr, cols, vals, L.x)
+    check(D.csr_spmv(), ref, absdot, "sparse alone")
+
+
+@pytest.mark.parametrize("B", [2, 5, 8, 16])
+@pytest.mark.parametrize("M", [64, 5000])                            # 16 and 32 rows per workgroup
+def test_infinite_activation_stays_in_its_tile(M, B):
+    import torch
+    import paper_2306_07629_amd as sq
+    N = 256
+    print(f"inf M={M} B={B}", flush=True)
+    rowptr = np.arange(M + 1, dtype=np.int32)
+    cols = np.full(M, 7, dtype=np.int32)
+    cols[20] = 9                                                     # the only nonzero of the column whose activations are infinite
+    x = np.ones((N, B), dtype=np.float16)
+    x[9] = np.inf
+    x[11] = np.nan                                                   # no nonzero reads it
+    y = torch.zeros((M, B), dtype=torch.int16, device="cuda")
+    dev = lambda a: torch.from_numpy(a).cuda()
+    sq.sqllm_csr_spmv(M, N, M, B, dev(rowptr), dev(cols), dev(np.full(M, 0x3C00, np.int16)), dev(x.view(np.int16)), y)
+    got = y.cpu().numpy().view(np.float16)
+    other = np.r_[0:16, 32:M]
+    assert np.array_equal(got[other], np.ones((M - 16, B), np.float16))
+    assert np.isinf(got[20]).all()

@@ -1,0 +1,86 @@
+"""Host-side check that the batch kernel never reads past the end of an input array: every address range it touches, re-computed from the
+clamping formulas it uses (rows past M, windows past a wave's last one, surplus lanes of an index load, nonzeros past a row group, the
+pieces in which a gathered row of x is read), lies inside the array."""
+import numpy as np
+import pytest
+
+from test_read_bounds import SHAPES, rowptr_for
+
+LANES = np.arange(64)
+
+
+def row_pieces(B):
+    """(offset, bytes) of the loads that fetch one row of B halves at any 2-byte alignment"""
+    out, n4 = [], B // 8 * 4
+    n2 = n4 + (2 if B % 8 >= 4 else 0)
+    out += [(4 * i, 16) for i in range(0, n4, 4)]
+    if n2 > n4:
+        out.append((4 * n4, 8))
+    if B % 4 >= 2:
+        out.append((4 * n2, 4))
+    if B % 2:
+        out.append((2 * (B - 1), 2))
+    return out
+
+
+def batch_kernel_reads(M, N, bits, B, rowptr, cols):
+    two = (M + 15) // 16 > 256
+    RG = 2 if two else 1
+    R, K = 16 * RG, 1 << bits
+    groups = (M + R - 1) // R
+    nwin, nnz, one = N // 128, int(rowptr[-1]), groups <= 256
+    ND = min(nwin, (6 if nnz else 8) if one else 4)
+    NS = (2 if one else 4) if nnz else 0
+    heavy = int(np.argmax(np.diff(rowptr))) // R
+    for block in sorted({0, groups - 1, groups // 2, heavy}):
+        r0 = block * R
+        rows = np.minimum(r0 + np.arange(R), M - 1)
+        yield "lut", int(rows.min()) * 2 * K, (int(rows.max()) + 1) * 2 * K
+        gp, ge = [], []
+        for rg in range(RG):
+            lo = np.minimum(r0 + 16 * rg + np.arange(16), M)
+            hi = np.minimum(r0 + 16 * rg + np.arange(16) + 1, M)
+            if nnz:
+                yield "rowptr", 4 * int(lo.min()), 4 * int(hi.max()) + 4
+            gp.append(int(rowptr[lo[0]]))
+            ge.append(int(rowptr[hi[15]]))
+        p = np.minimum(LANES, 16 * bits - 1)
+        for wave in range(ND):
+            last_t = wave + (nwin - 1 - wave) // ND * ND
+            t = wave
+            while t < nwin + 3 * ND:
+                tt = min(t, last_t)
+                for rg in range(RG):
+                    row = np.minimum(r0 + 16 * rg + p // bits, M - 1).astype(np.int64)
+                    off = row * (N * bits // 8) + (p % bits) * 16 + tt * bits * 16
+                    yield "qidx", int(off.min()), int(off.max()) + 16
+                yield "x", tt * 256 * B, (tt + 1) * 256 * B          # 64 lanes times 4 B bytes
+                t += ND
+        for rg in range(RG):
+            for f in range((ge[rg] - gp[rg] + 127) // 128):
+                q = np.minimum(gp[rg] + 128 * f + np.arange(128), ge[rg] - 1)
+                yield "cols", 4 * int(q.min()), 4 * int(q.max()) + 4
+                yield "vals", 2 * int(q.min()), 2 * int(q.max()) + 2
+                c = cols[q].astype(np.int64)
+                for off, n in ([(0, 2 * B)] if B in (8, 16) else row_pieces(B)):
+                    yield "x", int(c.min()) * 2 * B + off, int(c.max()) * 2 * B + off + n
+
+
+@pytest.mark.parametrize("B", range(2, 17))
+def test_a_gathered_row_is_read_once_and_no_further(B):
+    seen = np.zeros(2 * B, dtype=int)
+    for off, n in row_pieces(B):
+        assert off + n <= 2 * B
+        seen[off:off + n] += 1
+    assert (seen == 1).all()
+
+
+@pytest.mark.parametrize("M,N,bits,B", [s for s in SHAPES if s[3] > 1] + [(4096, 128, 3, 16), (4097, 256, 4, 5), (8193, 384, 3, 13)])
+def test_every_load_of_the_batch_kernel_stays_inside_its_array(M, N, bits, B):
+    rowptr = rowptr_for(M, N, M + N + bits)
+    nnz = int(rowptr[-1])
+    cols = np.random.default_rng(M).integers(0, N, nnz)
+    cols[:2] = (0, N - 1)
+    for name, lo, hi in batch_kernel_reads(M, N, bits, B, rowptr, cols):
+        size = {"x": 2 * N * B, "qidx": M * N * bits // 8, "lut": M * 2 * (1 << bits), "rowptr": 4 * (M + 1), "cols": 4 * nnz, "vals": 2 * nnz}[name]
+        assert 0 <= lo and hi <= size, (name, lo, hi, size)
