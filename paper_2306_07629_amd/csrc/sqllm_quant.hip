@@ -43,13 +43,19 @@ __device__ __forceinline__ u32 umin(u32 a, u32 b) { return a < b ? a : b; }
 __device__ __forceinline__ u32 umax(u32 a, u32 b) { return a < b ? b : a; }
 template <int CTRL, int ROW_MASK = 0xF>
 __device__ __forceinline__ u32 dpp_u32(u32 old, u32 v) { return (u32)__builtin_amdgcn_update_dpp((int)old, (int)v, CTRL, ROW_MASK, 0xF, false); }
-constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kRowHalfMirror = 0x141, kRowMirror = 0x140;
+constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kRowHalfMirror = 0x141, kRowMirror = 0x140, kRowShl1 = 0x101, kRowRor8 = 0x128;
 constexpr int kRowShr1 = 0x111, kRowShr2 = 0x112, kRowShr4 = 0x114, kRowShr8 = 0x118, kRowBcast15 = 0x142, kRowBcast31 = 0x143;
+// the value of the lane and of the lane in the neighbouring row of 16 (row ^ 1), or in the other half of the wave
+struct Two { u32 a, b; };
+__device__ __forceinline__ Two row_pair(u32 v) { const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false); return {r[0], r[1]}; }
+__device__ __forceinline__ Two half_pair(u32 v) { const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false); return {r[0], r[1]}; }
 struct Plain {                                                       // a 32-bit count or sum
     u32 v;
     __device__ __forceinline__ Plain operator+(const Plain& o) const { return {v + o.v}; }
     template <int CTRL, int ROW_MASK = 0xF>
     __device__ __forceinline__ Plain moved() const { return {dpp_u32<CTRL, ROW_MASK>(0, v)}; }
+    __device__ __forceinline__ Plain rows_added() const { const Two t = row_pair(v); return {t.a + t.b}; }
+    __device__ __forceinline__ Plain halves_added() const { const Two t = half_pair(v); return {t.a + t.b}; }
 };
 // sum over each group of eight lanes, in all its lanes
 template <class T>
@@ -58,6 +64,13 @@ __device__ __forceinline__ T group_sum(T v) {
     v = v + v.template moved<kQuadXor2>();
     v = v + v.template moved<kRowHalfMirror>();
     return v;
+}
+// sum over the lanes l, l ^ STEP, l ^ 2 STEP, ... (STEP = 8 or 16) of the wave, in all of them
+template <int STEP, class T>
+__device__ __forceinline__ T strided_sum(T v) {
+    if constexpr (STEP == 8) v = v + v.template moved<kRowRor8>();
+    v = v.rows_added();
+    return v.halves_added();
 }
 // inclusive prefix sum over the 64 lanes
 template <class T>
@@ -267,6 +280,11 @@ struct Moment {
         const u32 lo = dpp_u32<CTRL, ROW_MASK>(0, (u32)(u64)v), hi = dpp_u32<CTRL, ROW_MASK>(0, (u32)((u64)v >> 32));
         return {(i64)((u64)lo | ((u64)hi << 32))};
     }
+    __device__ __forceinline__ static Moment joined(const Two& lo, const Two& hi) {
+        return {(i64)(((u64)lo.a | ((u64)hi.a << 32)) + ((u64)lo.b | ((u64)hi.b << 32)))};
+    }
+    __device__ __forceinline__ Moment rows_added() const { return joined(row_pair((u32)(u64)v), row_pair((u32)((u64)v >> 32))); }
+    __device__ __forceinline__ Moment halves_added() const { return joined(half_pair((u32)(u64)v), half_pair((u32)((u64)v >> 32))); }
 };
 template <>
 struct Moment<true> {
@@ -284,14 +302,11 @@ struct Moment<true> {
         const Moment<false> a = Moment<false>{lo}.template moved<CTRL, ROW_MASK>(), b = Moment<false>{hi}.template moved<CTRL, ROW_MASK>();
         return {a.v, b.v};
     }
+    __device__ __forceinline__ Moment rows_added() const { return {Moment<false>{lo}.rows_added().v, Moment<false>{hi}.rows_added().v}; }
+    __device__ __forceinline__ Moment halves_added() const { return {Moment<false>{lo}.halves_added().v, Moment<false>{hi}.halves_added().v}; }
 };
-// Orders the LDS accesses of one wave (they execute in order; this keeps the compiler from reordering them).
-__device__ __forceinline__ void wave_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
+template <int W> struct U32Vec { typedef u32 type __attribute__((ext_vector_type(W))); };
+template <int W> using u32vec = typename U32Vec<W>::type;
 // Largest key k with 2 w(k) <= t, t between the smallest and the largest fp16 value doubled (the correction steps make it exact whatever
 // the conversion rounds to).
 __device__ __forceinline__ u32 key_below(float t) {
@@ -350,9 +365,6 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
     __shared__ u32 wsum[NWAVES];
     __shared__ i64 wmom[2 * NWAVES];
     __shared__ u32 kmm[2];
-    __shared__ u32 Fs0[2][K + 1];
-    __shared__ i64 Fs1[4 * (K + 1)];
-    __shared__ int moved[2][SETS];
     __shared__ float cen_s[K];
     __shared__ u32 bound[K], rank_bucket[K], nearest;
 
@@ -488,7 +500,6 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
         const int NC = N / CW;                                       // whole chunks: N is a multiple of 128
         Mom* C1 = reinterpret_cast<Mom*>(sums);                      // [NC + 1] sum of s w 2^24 in front of chunk c
         u32* C0 = reinterpret_cast<u32*>(C1 + NC + 1);               // [NC + 1] sum of s
-        Mom* F1 = reinterpret_cast<Mom*>(Fs1);
         Mom* wm = reinterpret_cast<Mom*>(wmom);
         // ---- 5. sums in front of every chunk; thread t owns the chunks CT t ..
         const int nchunks = (n_dense + CW - 1) / CW;
@@ -533,8 +544,8 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
         __syncthreads();
         // ---- 6. equal-count start: the key of the weight of rank r, found bit by bit inside its bucket, by the eight lanes that will work on
         //         the boundary above that centroid
-        const int k0 = 8 * wave + q;
         if (wave < SETS) {
+            const int k0 = 8 * wave + q;
             const int kr = min(k0, K - 1);
             const int r = (int)(((u64)(2 * kr + 1) * (u64)n_dense) / (u64)(2 * K));
             const int b0 = (int)rank_bucket[kr], p0 = (int)start[b0], p1 = (int)start[b0 + 1];
@@ -552,63 +563,55 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
             }
             if (n == 0 && k0 < K) cen_s[k0] = half_bits_to_f32(key_half(key));
         }
-        if (tid < 2) {
-            Fs0[tid][0] = 0; F1[tid * (K + 1)] = Mom::zero();
-            Fs0[tid][K] = C0[nchunks]; F1[tid * (K + 1) + K] = C1[nchunks];
-        }
         __syncthreads();
-        if (SETS == 1 && wave != 0) return;                          // uniform
-        // ---- 7. Lloyd iterations: group q of wave s < SETS evaluates boundary k0 = 8 s + q; its even lanes hold centroid k0, its odd ones
-        //         k0 + 1.  The sums of two successive iterations use different arrays, so one barrier per iteration is enough.
-        const int kc = min(k0 + (n & 1), K - 1);
-        float cen = wave < SETS ? cen_s[kc] : 0.f;
+        if (wave != 0) return;                                       // uniform
+        // ---- 7. Lloyd iterations, by one wave: lane l belongs to boundary k = l % COLS (between the centroids k and k + 1) and holds
+        //         centroid k.  Neighbouring boundaries are neighbouring lanes, so centroids and sums change hands without LDS.
+        constexpr int COLS = K > 8 ? 16 : 8, SUBS = 64 / COLS, WPL = 16 / SUBS;   // words per lane and round
+        const int k = lane & (COLS - 1), sub = lane / COLS;
+        const bool boundary = k < K - 1;
+        const u32 all0 = C0[nchunks];
+        const Mom all1 = C1[nchunks];
+        float cen = cen_s[min(k, K - 1)];
         u32 prev = 0xFFFFFFFFu;
-        for (int par = 0;; par ^= 1) {
-            bool any = false;
-            if (wave < SETS) {                                       // uniform
-                const u32 kk = key_below(__fadd_rn(cen, __builtin_bit_cast(float, dpp_u32<kQuadXor1>(0u, __builtin_bit_cast(u32, cen)))));
-                const u32 b = (umin(umax(kk, kmin), kmax) - kmin) >> shift;
-                u32 p0 = start[b], p1 = start[b + 1];
-                if (kk < kmin) { p0 = 0; p1 = 0; }
-                const u32 kkw = (kk << 16) | 0xFFFFu;
-                const u32 j0 = p0 & ~(u32)(CW - 1);
-                const u32 c0 = C0[j0 / CW];
-                const Mom c1 = C1[j0 / CW];
-                u32 pos = 0, s0 = 0;
-                Mom s1 = Mom::zero();
-                for (u32 j1 = j0; __any(j1 < p1); j1 += 16) {
-                    const u32 ja = j1 + n, jb = ja + 8;
-                    const u32 va = A[umin(ja, N - 1)], vb = A[umin(jb, N - 1)];
-                    const bool ina = ja < p1 && (ja < p0 || va <= kkw), inb = jb < p1 && (jb < p0 || vb <= kkw);
-                    pos += (ina ? 1u : 0u) + (inb ? 1u : 0u);
-                    const u32 za = ina ? va : 0x80000000u, zb = inb ? vb : 0x80000000u;
-                    s0 += (za & 0xFFFFu) + (zb & 0xFFFFu);
-                    s1 = s1 + Mom::product(za) + Mom::product(zb);
-                }
-                pos = group_sum(Plain{pos}).v + j0;
-                s0 = group_sum(Plain{s0}).v + c0;
-                s1 = group_sum(s1) + c1;
-                if (n == 0 && k0 < K - 1) { Fs0[par][k0 + 1] = s0; F1[par * (K + 1) + k0 + 1] = s1; }
-                any = __any(k0 < K - 1 && pos != prev);
-                if (SETS > 1 && lane == 0) moved[par][wave] = any ? 1 : 0;
-                prev = pos;
-            }
-            if constexpr (SETS > 1) {
-                __syncthreads();
+        for (;;) {
+            const u32 kk = key_below(__fadd_rn(cen, __builtin_bit_cast(float, dpp_u32<kRowShl1>(__builtin_bit_cast(u32, cen), __builtin_bit_cast(u32, cen)))));
+            const u32 b = (umin(umax(kk, kmin), kmax) - kmin) >> shift;
+            u32 p0 = start[b], p1 = start[b + 1];
+            if (kk < kmin) { p0 = 0; p1 = 0; }
+            const u32 kkw = (kk << 16) | 0xFFFFu;
+            const u32 j0 = p0 & ~(u32)(CW - 1);
+            const u32 c0 = C0[j0 / CW];
+            const Mom c1 = C1[j0 / CW];
+            u32 pos = 0, s0 = 0;
+            Mom s1 = Mom::zero();
+            for (u32 j1 = j0; __any(j1 < p1); j1 += 16) {            // what a lane reads past A is not used
+                const u32 j = j1 + WPL * sub;
+                u32 v[WPL];
+                *reinterpret_cast<u32vec<WPL>*>(v) = *reinterpret_cast<const u32vec<WPL>*>(A + umin(j, N - WPL));
 #pragma unroll
-                for (int k = 0; k < SETS; ++k) any = any || moved[par][k] != 0;
-            } else {
-                wave_fence();
+                for (int i = 0; i < WPL; ++i) {
+                    const bool in = j + i < p1 && (j + i < p0 || v[i] <= kkw);
+                    pos += in ? 1u : 0u;
+                    const u32 z = in ? v[i] : 0x80000000u;
+                    s0 += z & 0xFFFFu;
+                    s1 = s1 + Mom::product(z);
+                }
             }
-            if (!any || it == max_iter) break;                       // uniform
-            if (wave < SETS) {
-                const u32 m0 = Fs0[par][kc + 1] - Fs0[par][kc];
-                const Mom m1 = F1[par * (K + 1) + kc + 1] - F1[par * (K + 1) + kc];
-                if (m0 > 0) cen = (float)(m1.value() * 5.9604644775390625e-08 / (double)m0);
-            }
+            pos = strided_sum<COLS>(Plain{pos}).v + j0;
+            s0 = strided_sum<COLS>(Plain{s0}).v + c0;
+            s1 = strided_sum<COLS>(s1) + c1;
+            if (!__any(boundary && pos != prev) || it == max_iter) break;   // uniform
+            prev = pos;
+            if (!boundary) { s0 = all0; s1 = all1; }
+            const Plain below0 = Plain{s0}.template moved<kRowShr1>();
+            const Mom below1 = s1.template moved<kRowShr1>();
+            const u32 m0 = s0 - (k == 0 ? 0u : below0.v);
+            const Mom m1 = k == 0 ? s1 : s1 - below1;
+            if (m0 > 0) cen = (float)(m1.value() * 5.9604644775390625e-08 / (double)m0);
             ++it;
         }
-        if (wave < SETS && n == 0 && k0 < K) cen_s[k0] = cen;
+        if (lane < K) cen_s[lane] = cen;
     };
     if (n_dense > 0) {
         if (kmax >= 0xD800u || kmin <= 0x27FFu) solve(std::integral_constant<bool, true>{});    // |w| >= 128 somewhere
