@@ -268,10 +268,8 @@ template <bool WIDE>
 struct Moment {
     i64 v;
     __device__ __forceinline__ static Moment zero() { return {0}; }
-    __device__ __forceinline__ static Moment product(u32 word) {     // word: key << 16 | sensitivity
-        const int fixed = (int)(half_bits_to_f32(key_half(word >> 16)) * 16777216.0f);   // exact
-        return {(i64)fixed * (i64)(int)(word & 0xFFFFu)};
-    }
+    // w24: a weight times 2^24 (exact in fp32), s: its sensitivity
+    __device__ __forceinline__ static Moment product(float w24, u32 /*half*/, u32 s) { return {(i64)(int)w24 * (i64)(int)s}; }
     __device__ __forceinline__ Moment operator+(const Moment& o) const { return {v + o.v}; }
     __device__ __forceinline__ Moment operator-(const Moment& o) const { return {v - o.v}; }
     __device__ __forceinline__ double value() const { return (double)v; }
@@ -290,8 +288,8 @@ template <>
 struct Moment<true> {
     i64 lo, hi;
     __device__ __forceinline__ static Moment zero() { return {0, 0}; }
-    __device__ __forceinline__ static Moment product(u32 word) {
-        const i64 p = half_to_fixed(key_half(word >> 16)) * (i64)(word & 0xFFFFu);
+    __device__ __forceinline__ static Moment product(float /*w24*/, u32 half, u32 s) {
+        const i64 p = half_to_fixed(half) * (i64)s;
         return {(i64)((u64)p & 0xFFFFFFFFull), p >> 32};
     }
     __device__ __forceinline__ Moment operator+(const Moment& o) const { return {lo + o.lo, hi + o.hi}; }
@@ -318,10 +316,15 @@ __device__ __forceinline__ u32 key_below(float t) {
     return k;
 }
 
+// A word of the row in LDS: fp16 bits << 16 | sensitivity
+__device__ __forceinline__ float weight24(u32 word) { return half_bits_to_f32(word >> 16) * 16777216.0f; }
+constexpr u32 kBeyond = 0x7C000000u;                                 // +infinity with sensitivity 0: above every boundary, adds nothing
+constexpr int kPad = 16;                                             // words of it behind the row: a round of the iterations ends there at the latest
+
 // One block of T threads per row.  In one dimension the clusters of Lloyd's method are intervals of the sorted weights, so an update
 // only needs, for each of the K - 1 boundaries, how many weights lie below it and their exact sums.  The row is not sorted for that:
 //   * it is read once; every thread keeps its weights as words (key << 16 | sensitivity) in registers until the indices are written;
-//   * a counting sort puts the words into NB buckets of 2^shift consecutive keys (shift from the row's smallest and largest key); the
+//   * a counting sort puts the words, with the fp16 bits in place of the key, into NB buckets of 2^shift consecutive keys (shift from the row's smallest and largest key); the
 //     atomic that counts a word also gives its place in the bucket; the order inside a bucket does not matter, all sums are integers;
 //   * C0 / C1 hold the sums in front of every chunk of eight words;
 //   * eight lanes evaluate a boundary: the key below it names the bucket, and the sums are those in front of the chunk in which the
@@ -342,8 +345,8 @@ struct KmeansShape {
     static constexpr int kMaxN = 8 * T_ * V_ < 28672 ? 8 * T_ * V_ : 28672;
     static constexpr int kLogNB = LOG_NB, NB = 1 << LOG_NB;
     static constexpr int kChunksPerThread = (kMaxN / CHUNK + T_ - 1) / T_;
-    static constexpr size_t sum_bytes(int N) { return (size_t)(N / CHUNK + 1) * 12 + 32; }           // also holds (N / (2 CHUNK) + 1) * 20
-    static constexpr size_t lds(int N) { return (size_t)N * 4 + sum_bytes(N) + (size_t)(NB + 2) * 2; }
+    static constexpr size_t sum_bytes(int N) { return (size_t)(N / CHUNK + 1) * 12; }                // also holds (N / (2 CHUNK) + 1) * 20
+    static constexpr size_t lds(int N) { return (size_t)(N + kPad) * 4 + sum_bytes(N) + (size_t)(NB + 2) * 2; }
 };
 typedef KmeansShape<256, 2, 11, 8, 6> KmeansUpTo4096;                // 26 KB of LDS at 4096 weights: six rows per compute unit
 typedef KmeansShape<512, 3, 12, 8, 4> KmeansUpTo12288;               // 69 KB at 11008: two
@@ -358,7 +361,7 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
     constexpr int T = S::T, V = S::V, NB = S::NB, NBT = NB / T, NWAVES = T / 64;
     extern __shared__ __align__(16) char smem[];
     u32* A = reinterpret_cast<u32*>(smem);                           // words by bucket
-    char* sums = smem + (size_t)N * 4;                               // sums in front of every chunk: moments, then sensitivities
+    char* sums = smem + (size_t)(N + kPad) * 4;                               // sums in front of every chunk: moments, then sensitivities
     u32* start32 = reinterpret_cast<u32*>(sums + S::sum_bytes(N));   // first place of every bucket, two to a word; counts before the scan
     const uint16_t* start = reinterpret_cast<const uint16_t*>(start32);
     u32* emask = A;                                                  // bit j: weight j is extracted (A is filled after its last use)
@@ -366,8 +369,9 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
     __shared__ i64 wmom[2 * NWAVES];
     __shared__ u32 kmm[2];
     __shared__ float cen_s[K];
-    __shared__ u32 bound[K], rank_bucket[K], nearest;
+    __shared__ u32 bound[K], nearest;
 
+    u32* rank_bucket = bound;                                        // buckets of the start ranks, until the boundaries of the table take their place
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), row = blockIdx.x;
     const int n = lane & 7, q = lane >> 3;                           // eight lanes per boundary
     const u32 key_min = ws[kWsThr], key_max = ws[kWsThr + 1], s_thr = ws[kWsThr + 2];
@@ -489,7 +493,9 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
     for (int v = 0; v < V; ++v)
 #pragma unroll
         for (int e = 0; e < 8; ++e)
-            if (word[v][e] != 0xFFFFFFFFu) A[start[bucket_of(word[v][e])] + ((e & 1) ? rank[v][e >> 1] >> 16 : rank[v][e >> 1] & 0xFFFFu)] = word[v][e];
+            if (word[v][e] != 0xFFFFFFFFu)
+                A[start[bucket_of(word[v][e])] + ((e & 1) ? rank[v][e >> 1] >> 16 : rank[v][e >> 1] & 0xFFFFu)] = (key_half(word[v][e] >> 16) << 16) | (word[v][e] & 0xFFFFu);
+    for (int j = n_dense + tid; j < N + kPad; j += T) A[j] = kBeyond;
     __syncthreads();
 
     int it = 0;
@@ -518,9 +524,8 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
                         const u32 vv[4] = {v4.x, v4.y, v4.z, v4.w};
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
-                            const u32 z = j + e < n_dense ? vv[e] : 0x80000000u;   // +0 with sensitivity 0
-                            s0[k] += z & 0xFFFFu;
-                            s1[k] = s1[k] + Mom::product(z);
+                            s0[k] += vv[e] & 0xFFFFu;                // 0 past the last word
+                            s1[k] = s1[k] + Mom::product(weight24(vv[e]), vv[e] >> 16, vv[e] & 0xFFFFu);
                         }
                     }
                 }
@@ -549,14 +554,14 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
             const int kr = min(k0, K - 1);
             const int r = (int)(((u64)(2 * kr + 1) * (u64)n_dense) / (u64)(2 * K));
             const int b0 = (int)rank_bucket[kr], p0 = (int)start[b0], p1 = (int)start[b0 + 1];
-            const u32 first = A[min(p0 + n, N - 1)] >> 16;
+            const u32 first = half_key(A[min(p0 + n, N - 1)] >> 16);
             u32 key = kmin + ((u32)b0 << shift);
             for (int b = shift - 1; b >= 0; --b) {
                 const u32 cand = key + (1u << b);                    // no more than r - p0 words below cand: the key is cand or above
                 u32 below = 0, v = first;
                 for (int j0 = p0; __any(j0 < p1); j0 += 8) {
                     const int j = j0 + n;
-                    if (j0 != p0) v = A[min(j, N - 1)] >> 16;
+                    if (j0 != p0) v = half_key(A[min(j, N - 1)] >> 16);
                     below += j < p1 && v < cand ? 1u : 0u;
                 }
                 if ((int)group_sum(Plain{below}).v <= r - p0) key = cand;
@@ -575,27 +580,29 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
         float cen = cen_s[min(k, K - 1)];
         u32 prev = 0xFFFFFFFFu;
         for (;;) {
-            const u32 kk = key_below(__fadd_rn(cen, __builtin_bit_cast(float, dpp_u32<kRowShl1>(__builtin_bit_cast(u32, cen), __builtin_bit_cast(u32, cen)))));
+            const float t = __fadd_rn(cen, __builtin_bit_cast(float, dpp_u32<kRowShl1>(__builtin_bit_cast(u32, cen), __builtin_bit_cast(u32, cen))));
+            const u32 kk = key_below(t);
             const u32 b = (umin(umax(kk, kmin), kmax) - kmin) >> shift;
-            u32 p0 = start[b], p1 = start[b + 1];
-            if (kk < kmin) { p0 = 0; p1 = 0; }
-            const u32 kkw = (kk << 16) | 0xFFFFu;
+            const u32 p0 = kk < kmin ? 0u : start[b], p1 = kk < kmin ? 0u : start[b + 1];
+            // 2 w <= t, with both sides scaled exactly.  It holds for all words in front of the bucket and for none behind it, which a lane
+            // may read as well; behind the last word lie kPad that are above every t.
+            const float t24 = t * 8388608.0f;
             const u32 j0 = p0 & ~(u32)(CW - 1);
             const u32 c0 = C0[j0 / CW];
             const Mom c1 = C1[j0 / CW];
             u32 pos = 0, s0 = 0;
             Mom s1 = Mom::zero();
-            for (u32 j1 = j0; __any(j1 < p1); j1 += 16) {            // what a lane reads past A is not used
-                const u32 j = j1 + WPL * sub;
+            for (u32 j = j0 + WPL * sub; __any(j - WPL * sub < p1); j += 16) {
                 u32 v[WPL];
-                *reinterpret_cast<u32vec<WPL>*>(v) = *reinterpret_cast<const u32vec<WPL>*>(A + umin(j, N - WPL));
+                *reinterpret_cast<u32vec<WPL>*>(v) = *reinterpret_cast<const u32vec<WPL>*>(A + umin(j, N + kPad - WPL));
 #pragma unroll
                 for (int i = 0; i < WPL; ++i) {
-                    const bool in = j + i < p1 && (j + i < p0 || v[i] <= kkw);
+                    const float w24 = weight24(v[i]);
+                    const bool in = j < (u32)(N + kPad) && w24 <= t24;
+                    const u32 s = in ? v[i] & 0xFFFFu : 0u;
                     pos += in ? 1u : 0u;
-                    const u32 z = in ? v[i] : 0x80000000u;
-                    s0 += z & 0xFFFFu;
-                    s1 = s1 + Mom::product(z);
+                    s0 += s;
+                    s1 = s1 + Mom::product(w24, v[i] >> 16, s);
                 }
             }
             pos = strided_sum<COLS>(Plain{pos}).v + j0;
