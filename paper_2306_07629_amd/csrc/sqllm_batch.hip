@@ -15,8 +15,8 @@
 //   * Accumulators of the waves are combined through LDS in a fixed order; y is rounded to fp16 once.
 // Bound by what the compute units fetch: every workgroup reads all of x (67 MB through the L2s at 8192x8192 and 16 columns) beside its
 // indices and the gathered rows; LDS and vector ALU are busy for about a third of the launch each.  8192x8192, 3 bits, 16 columns, 0.45 %
-// nonzeros: 18.6 us (21.3 when the sparse term followed the dense one on the same waves and a nonzero's activations were gathered in 8-byte
-// pieces); 13824x5120, 4 bits, 5 columns: 17.1 us (28.7 when batches other than 2, 4, 8, 12 and 16 picked their columns out of LDS with
+// nonzeros: 15.4 us (21.2 when the sparse term followed the dense one on the same waves and a nonzero's activations were gathered in 8-byte
+// pieces); 13824x5120, 4 bits, 5 columns: 12.4 us (28.7 when batches other than 2, 4, 8, 12 and 16 picked their columns out of LDS with
 // 16-bit reads, and each of 864 workgroups built its tables through LDS).
 // Lanes of absent columns (r >= B) carry some other column's activations: their products only reach columns that are not stored.
 #include <hip/hip_runtime.h>
@@ -138,9 +138,11 @@ __global__ void __launch_bounds__(kMaxBatchWaves * kWave) matvec_batch_kernel(Ma
             piece[rg] = reinterpret_cast<const u32x4*>(static_cast<const u32*>(g.qidx) + (size_t)min(r0 + 16 * rg + row, g.M - 1) * row_dwords) + part;
         idx_wr = wave_lds + Stage::template index_piece<BITS>(row, part);
     }
+    // Plain loads: a line of 128 bytes holds the windows of two or three waves, and non-temporal ones fetch it for each (8192x8192 at 16
+    // columns 15.4 against 18.6 us a call, 19.2 against 20.9 with the weights coming from HBM).
     auto load_idx = [&](int t, u32x4 (&c)[NP]) {
 #pragma unroll
-        for (int j = 0; j < NP; ++j) c[j] = __builtin_nontemporal_load(piece[j] + t * BITS);
+        for (int j = 0; j < NP; ++j) c[j] = piece[j][t * BITS];
     };
     const u32 idx_rd = wave_lds + Stage::template index_chunk<BITS>(r, q);
     const u32 stage_lds = wave_lds + (dense_wave ? (u32)Stage::index_bytes(BITS) : 256u);
