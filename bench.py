@@ -647,7 +647,7 @@ def main():
         "device": device_info(torch), "context_device_copy_1gib_gbs_read_plus_write": copy_gbs,
         "roofline": {"bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS,
                      "traffic": traffic,
-                     "kernel": (f"sqllm::matvec_kernel<{bits},*>" if args.no_plan else f"sqllm::matvec_planned_kernel<{bits},*>") if B == 1 else f"sqllm::matvec_b16_kernel<{bits},*>",
+                     "kernel": (f"sqllm::matvec_kernel<{bits},*>" if args.no_plan else f"sqllm::matvec_planned_kernel<{bits},*>") if B == 1 else f"sqllm::matvec_batch_kernel<{bits},*>",
                      "algorithmic_bytes_per_launch": step_bytes / len(shapes)},
         "cpu_baseline": cpu,
     }

@@ -23,7 +23,7 @@ def is_stale() -> bool:
     if not os.path.exists(LIB):
         return True
     t = os.path.getmtime(LIB)
-    deps = sources() + [os.path.join(CSRC, "sqllm_kernels.h"), os.path.join(ROOT, "include", "sqllm.h")]
+    deps = sources() + [os.path.join(CSRC, "sqllm_kernels.h"), os.path.join(CSRC, "sqllm_decode.h"), os.path.join(ROOT, "include", "sqllm.h")]
     return any(os.path.getmtime(d) > t for d in deps)
 
 

@@ -440,11 +440,13 @@ __global__ void __launch_bounds__(kMaxBatchWaves * kWave) matvec_batch_kernel(Ma
 
 // ---------------------------------------------------------------------------------------------- launcher
 // Rows and waves per workgroup.  16 rows while that gives every compute unit at most one workgroup, else 32: the activations that a
-// workgroup reads and transposes serve twice the rows (5120x5120 at 16 columns 9.3 against 11.2 us, 4608x16384 29.0 against 34.9; with
-// fewer rows half the units would idle: 1024x8192 14.3 against 10.4).
-// Six dense and two sparse waves while there is one workgroup per unit (4096x11008 at 16 columns 14.9 us; four and four 16.8, eight and
-// four 15.3); beyond that four and four, so that two workgroups fit a unit (13824x5120 at 5 columns 17.5 us; six and two 19.2, eight and
-// four 21.7).  Without a sparse term eight and four dense waves (8192x8192 14.6 against 15.5 us, 13824x5120 16.8 against 14.8).
+// workgroup reads and transposes serve twice the rows (weights from HBM, 0.45 % nonzeros, six and two waves: 5120x5120 at 16 columns 9.3
+// against 10.9 us, 8192x8192 19.1 against 22.2; with fewer rows half the units would idle: 1024x8192 12.2 against 9.5, 4096x11008 20.5
+// against 15.8).
+// Six dense and two sparse waves while there is one workgroup per unit (4096x11008 at 16 columns 15.8 us; four and four 17.7, eight and
+// two 15.6, eight and four 15.9; 8192x8192 19.1 / 19.0 / 20.1 / 19.2); beyond that four and four, so that two workgroups fit a unit
+// (13824x5120 at 5 columns 17.3 us; six and two 18.2, eight and four 19.3; 22016x2048 at 16 columns 17.6 / 18.6 / 19.5).  Without a sparse
+// term eight and four dense waves (8192x8192 14.3 against 15.8 us, 13824x5120 15.5 against 14.2).
 constexpr int kUnits = 256;
 template <int BITS, int RG, int BT>
 static hipError_t launch_batch_r(const MatvecArgs& g, hipStream_t s) {
