@@ -324,19 +324,20 @@ constexpr int kPad = 16;                                             // words of
 // One block of T threads per row.  In one dimension the clusters of Lloyd's method are intervals of the sorted weights, so an update
 // only needs, for each of the K - 1 boundaries, how many weights lie below it and their exact sums.  The row is not sorted for that:
 //   * it is read once; every thread keeps its weights as words (key << 16 | sensitivity) in registers until the indices are written;
-//   * a counting sort puts the words, with the fp16 bits in place of the key, into NB buckets of 2^shift consecutive keys (shift from the row's smallest and largest key); the
+//   * a counting sort puts the words, with the fp16 bits in place of the key, into NB buckets of 2^shift consecutive keys (shift from the
+//     row's smallest and largest key); the
 //     atomic that counts a word also gives its place in the bucket; the order inside a bucket does not matter, all sums are integers;
 //   * C0 / C1 hold the sums in front of every chunk of eight words;
-//   * eight lanes evaluate a boundary: the key below it names the bucket, and the sums are those in front of the chunk in which the
-//     bucket starts plus the words up to the end of the bucket that precede the bucket or have a key within the boundary.  A bucket
-//     holds a handful of words, so that is one round of two words per lane.  A wave takes eight boundaries: tables of up to eight
-//     entries iterate inside one wave without a barrier, larger ones in two waves with one barrier.
+//   * eight lanes (four with 16 entries) evaluate a boundary: the key below it names the bucket, and the sums are those in front of the chunk
+//     in which the bucket starts plus the words from there on that lie below the boundary.  A bucket holds a handful of words, so that is
+//     one or two rounds of 16 words.  One wave iterates: neighbouring boundaries are neighbouring lanes, so no barrier and no LDS stand
+//     between two updates.
 // The decisions and integers are those of a pass over all weights per update, hence the same result.
-// Bound by the vector ALU (62 % busy at 4096x4096, 51 % at 4096x11008) and by the latency of the chain boundary -> bucket -> words ->
-// reduction -> division, which the other rows on the unit cover only in part (six at 4096 weights, two at 11008).  Against a bitonic sort of the
-// row in LDS and a 64-way search per boundary with reductions over 64 lanes: 4096x4096 at 3 bits 409 -> 112 us (22 updates per row, 2.6 us
-// each over the matrix), 4096x11008 at 4 bits 1164 -> 377 us (32 updates, 7.5 us each).  16 lanes per boundary and chunks of 16 words:
-// 134 and 447 us (vector ALU 84 % busy).
+// Bound by the latency of the chain boundary -> bucket -> words -> reduction -> division (about 1600 cycles), which the other rows on the
+// unit cover only in part (six at 4096 weights, two at 11008: what their LDS allows).  Against a bitonic sort of the row in LDS and a 64-way
+// search per boundary with reductions over 64 lanes: 4096x4096 at 3 bits 409 -> 101 us (22 updates per row, 1.9 us each over the
+// matrix), 4096x11008 at 4 bits 1164 -> 329 us (32 updates, 5.9 us each).  With a wave per eight boundaries, keys in the words and sums
+// exchanged through LDS: 112 and 377 us.
 // Threads T, units of eight weights per thread V, buckets, words per chunk of running sums (twice as many in wide rows), and the waves per
 // SIMD the registers are held down for.
 template <int T_, int V_, int LOG_NB, int CHUNK, int WAVES>
