@@ -23,7 +23,8 @@ def is_stale() -> bool:
     if not os.path.exists(LIB):
         return True
     t = os.path.getmtime(LIB)
-    deps = sources() + [os.path.join(CSRC, "sqllm_kernels.h"), os.path.join(CSRC, "sqllm_decode.h"), os.path.join(ROOT, "include", "sqllm.h")]
+    headers = [os.path.join(CSRC, h) for h in ("sqllm_kernels.h", "sqllm_decode.h", "sqllm_batch_split.h")]
+    deps = sources() + headers + [os.path.join(ROOT, "include", "sqllm.h")]
     return any(os.path.getmtime(d) > t for d in deps)
 
 

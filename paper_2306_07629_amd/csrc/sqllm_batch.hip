@@ -23,6 +23,7 @@
 #include <stdint.h>
 #include <type_traits>
 
+#include "sqllm_batch_split.h"
 #include "sqllm_decode.h"
 #include "sqllm_kernels.h"
 
@@ -296,26 +297,28 @@ __global__ void __launch_bounds__(kMaxBatchWaves * kWave) matvec_batch_kernel(Ma
 #pragma unroll
     for (int rg = 0; rg < RG; ++rg) {
         gp[rg] = __builtin_amdgcn_readlane(lo[rg], 0);
-        wins[rg] = (__builtin_amdgcn_readlane(hi[rg], 15) - gp[rg] + 127) >> 7;
+        wins[rg] = window_count(gp[rg], __builtin_amdgcn_readlane(hi[rg], 15));
         total += wins[rg];
     }
     struct Entries { u32 col[4], val[2]; };
     auto find_window = [&](int f, int& rg, int& p0) {                // f < total
-        rg = 0; p0 = gp[0] + 128 * f;
-        if constexpr (RG == 2) { if (f >= wins[0]) { rg = 1; p0 = gp[1] + 128 * (f - wins[0]); } }
+        rg = RG == 2 && f >= wins[0] ? 1 : 0;
+        p0 = (rg == 0 ? gp[0] : gp[RG - 1]) + kWindowNonzeros * (rg == 0 ? f : f - wins[0]);
     };
     auto load_entries = [&](int f, Entries& e) {                     // positions past the row group repeat its last nonzero
         int rg, p0;
         find_window(f, rg, p0);
-        const int last = __builtin_amdgcn_readlane(rg == 0 ? hi[0] : hi[RG - 1], 15) - 1;
+        const int rest = window_rest(p0, __builtin_amdgcn_readlane(rg == 0 ? hi[0] : hi[RG - 1], 15));
+        const int* __restrict__ cols = g.cols + p0;                  // uniform
+        const uint16_t* __restrict__ vals = static_cast<const uint16_t*>(g.vals) + p0;
         constexpr int n = BT == 16 ? 4 : 2;
 #pragma unroll
         for (int i = 0; i < n; ++i) {
             const int k = BT == 16 ? (lane >> 1) + 32 * i : (BT == 8 ? lane + 64 * i : 2 * lane + i);
-            e.col[i] = (u32)g.cols[min(p0 + k, last)];
+            e.col[i] = (u32)cols[min(k, rest)];
         }
 #pragma unroll
-        for (int i = 0; i < 2; ++i) e.val[i] = static_cast<const uint16_t*>(g.vals)[min(p0 + 2 * lane + i, last)];
+        for (int i = 0; i < 2; ++i) e.val[i] = vals[min(2 * lane + i, rest)];
     };
     auto gather = [&](const Entries& e, u32 (&v)[16]) {              // byte offsets fit 32 bits: N * B * 2 < 2^20
         const char* xc = reinterpret_cast<const char*>(x);
@@ -365,10 +368,7 @@ __global__ void __launch_bounds__(kMaxBatchWaves * kWave) matvec_batch_kernel(Ma
             u32 vw[16];
             get_x(wave_lds + 64u * (u32)q, vw);                      // the 32 values of the lane's nonzeros
             wave_fence();
-            // bit k: nonzero p0 + 32 q + k belongs to the lane's row; the positions past the row group belong to no row
-            const int pk = p0 + 32 * q, l = wg == 0 ? lo[0] : lo[RG - 1], h = wg == 0 ? hi[0] : hi[RG - 1];
-            const u32 b0 = (u32)min(max(l - pk, 0), 32), b1 = (u32)min(max(h - pk, 0), 32);
-            const u32 bits = (u32)((1ull << b1) - (1ull << b0));
+            const u32 bits = window_row_bits(wg == 0 ? lo[0] : lo[RG - 1], wg == 0 ? hi[0] : hi[RG - 1], p0, q);
             u32 w[16];
 #pragma unroll
             for (int i = 0; i < 16; ++i) {

@@ -75,3 +75,30 @@ def test_infinite_activation_stays_in_its_tile(M, B):
     other = np.r_[0:16, 32:M]
     assert np.array_equal(got[other], np.ones((M - 16, B), np.float16))
     assert np.isinf(got[20]).all()
+
+
+@pytest.mark.parametrize("M,B", [(4096, 16), (65536, 5)])            # 16 and 32 rows per workgroup
+def test_nonzeros_up_to_the_largest_position(M, B):
+    """2^31 - 1 nonzeros (13 GB; entries of one row and column add up): the last windows begin less than 128 positions before the end of
+    the 32-bit range.  Small integers, so every sum is exact."""
+    import torch
+    import paper_2306_07629_amd as sq
+    N, nnz = 128, 2 ** 31 - 1
+    print(f"largest nnz M={M} B={B}", flush=True)
+    rowptr = torch.minimum(torch.arange(M + 1, dtype=torch.int64) * (2 ** 31 // M), torch.tensor(nnz)).to(torch.int32)
+    cols = torch.full((nnz,), 3, dtype=torch.int32, device="cuda")
+    vals = torch.zeros(nnz, dtype=torch.int16, device="cuda")
+    first = int(rowptr[M - 1])
+    for lo, hi in ((0, 2), (first - 3, first + 5), (nnz - 130, nnz)):
+        vals[lo:hi] = 0x3C00
+    x = torch.zeros((N, B), dtype=torch.float16, device="cuda")
+    x[3] = torch.arange(1, B + 1, dtype=torch.float16)
+    x[0] = x[127] = float("inf")                                     # columns that no nonzero names
+    y = torch.zeros((M, B), dtype=torch.float16, device="cuda")
+    sq.sqllm_csr_spmv(M, N, nnz, B, rowptr.cuda(), cols, vals, x, y)
+    want = torch.zeros((M, B), dtype=torch.float16)
+    want[0], want[M - 2], want[M - 1] = 2 * x[3].cpu(), 3 * x[3].cpu(), 135 * x[3].cpu().float()
+    got = y.cpu()
+    del cols, vals
+    torch.cuda.empty_cache()
+    assert torch.equal(got, want)
