@@ -320,6 +320,10 @@ __device__ __forceinline__ u32 key_below(float t) {
 __device__ __forceinline__ float weight24(u32 word) { return half_bits_to_f32(word >> 16) * 16777216.0f; }
 constexpr u32 kBeyond = 0x7C000000u;                                 // +infinity with sensitivity 0: above every boundary, adds nothing
 constexpr int kPad = 16;                                             // words of it behind the row: a round of the iterations ends there at the latest
+// Words from which a bucket is sorted and searched instead of read through.  A round reads 16 words and a bisection step one, in about the
+// same time: at 128 words rows of 8-bit levels, whose fullest buckets hold 137, lost (4096x11008 at 4 bits 751 us, 639 at 256 words, 633
+// without); at 512 rows with buckets in between lost (8192x1024 at 2 bits, two values: 362 us, 165 at 256 words).
+constexpr int kHeavy = 256;
 
 // One block of T threads per row.  In one dimension the clusters of Lloyd's method are intervals of the sorted weights, so an update
 // only needs, for each of the K - 1 boundaries, how many weights lie below it and their exact sums.  The row is not sorted for that:
@@ -331,7 +335,10 @@ constexpr int kPad = 16;                                             // words of
 //   * eight lanes (four with 16 entries) evaluate a boundary: the key below it names the bucket, and the sums are those in front of the chunk
 //     in which the bucket starts plus the words from there on that lie below the boundary.  A bucket holds a handful of words, so that is
 //     one or two rounds of 16 words.  One wave iterates: neighbouring boundaries are neighbouring lanes, so no barrier and no LDS stand
-//     between two updates.
+//     between two updates;
+//   * pruned, constant or already quantised rows have few keys and many words of each.  Buckets of kHeavy words or more are therefore put in
+//     the order of their keys, and an update bisects them instead of reading them through (nine tenths zeros, 32 updates: 4096x11008 at 4
+//     bits 0.84 ms, read through 16.3; 1024x28672 0.52 ms, read through 18.7).
 // The decisions and integers are those of a pass over all weights per update, hence the same result.
 // Bound by the latency of the chain boundary -> bucket -> words -> reduction -> division (about 1600 cycles), which the other rows on the
 // unit cover only in part (six at 4096 weights, two at 11008: what their LDS allows).  Against a bitonic sort of the row in LDS and a 64-way
@@ -368,7 +375,7 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
     u32* emask = A;                                                  // bit j: weight j is extracted (A is filled after its last use)
     __shared__ u32 wsum[NWAVES];
     __shared__ i64 wmom[2 * NWAVES];
-    __shared__ u32 kmm[2];
+    __shared__ u32 kmm[2], crowded;                                  // smallest and largest key; is there a heavy bucket?
     __shared__ float cen_s[K];
     __shared__ u32 bound[K], nearest;
 
@@ -391,7 +398,7 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
             wv[v] = wr[i]; sv[v] = sr[i];
         }
         for (int b = tid; b < NB / 2 + 1; b += T) start32[b] = 0;
-        if (tid == 0) { kmm[0] = 0xFFFFu; kmm[1] = 0; nearest = 0xFFFFFFFFu; }
+        if (tid == 0) { kmm[0] = 0xFFFFu; kmm[1] = 0; crowded = 0; nearest = 0xFFFFFFFFu; }
         u32 kmin = 0xFFFFu, kmax = 0;
 #pragma unroll
         for (int v = 0; v < V; ++v) {
@@ -424,7 +431,7 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
     auto bucket_of = [&](u32 wd) { return ((wd >> 16) - kmin) >> shift; };
 
     // ---- 2. count the buckets; the count before gives a word its place
-    u32 rank[V][4];                                                  // two to a word
+    u32 rank[V][4], most = 0;                                        // two to a word
 #pragma unroll
     for (int v = 0; v < V; ++v)
 #pragma unroll
@@ -435,7 +442,9 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
                 r = (atomicAdd(&start32[b >> 1], 1u << sh) >> sh) & 0xFFFFu;   // a bucket holds fewer than 2^15 words
             }
             rank[v][e >> 1] = (e & 1) ? rank[v][e >> 1] | (r << 16) : r;
+            most = umax(most, r);
         }
+    if (most >= kHeavy - 1) crowded = 1;
     const u32 ext = tid < N / 32 ? emask[tid] : 0u;
     __syncthreads();
     // ---- 3. one scan over the threads for the places of the buckets (low half) and of the CSR entries (high half); both are below 2^15
@@ -489,7 +498,52 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
         }
     }
     __syncthreads();
-    // ---- 4. the words by bucket
+    const bool heavy = __builtin_amdgcn_readfirstlane((int)crowded) != 0;   // uniform in the block
+    // ---- 4. the words by bucket; those of a heavy bucket by key: a second count, over the 2^shift keys of the bucket, gives their places.
+    //         A heavy bucket holds a multiple of kHeavy among its first kHeavy places, which names its counters.
+    if (heavy && shift > 0) {
+        u32* sub32 = reinterpret_cast<u32*>(sums);                   // [slots][2^shift] 16-bit counters, then first places
+        const uint16_t* sub = reinterpret_cast<const uint16_t*>(sums);
+        u32 least = kmin;                                            // a copy the compiler cannot see through: the words' bucket numbers are not
+        asm volatile("" : "+s"(least));                              // kept in registers from one pass over them to the next
+        auto counter_of = [&](u32 wd, int& i) {                      // false: not in a heavy bucket
+            const u32 key = (wd >> 16) - least, b = key >> shift, p = start[b];
+            i = (int)(((p + kHeavy - 1) / kHeavy << shift) | (key & ((1u << shift) - 1u)));
+            return (u32)start[b + 1] - p >= (u32)kHeavy;
+        };
+        const int half = 1 << (shift - 1), slots = (N + kHeavy - 1) / kHeavy;   // words per bucket, buckets with counters
+        for (int i = tid; i < slots * half; i += T) sub32[i] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                int i;
+                if (word[v][e] != 0xFFFFFFFFu && counter_of(word[v][e], i)) {
+                    const u32 sh = 16 * (i & 1), r = (atomicAdd(&sub32[i >> 1], 1u << sh) >> sh) & 0xFFFFu;
+                    rank[v][e >> 1] = (e & 1) ? (rank[v][e >> 1] & 0xFFFFu) | (r << 16) : (rank[v][e >> 1] & 0xFFFF0000u) | r;
+                }
+                __builtin_amdgcn_sched_barrier(0);                   // one word after the other: no registers for several
+            }
+        __syncthreads();
+        for (int s = tid; s < slots; s += T) {
+            u32 run = 0;
+            for (int i = s * half; i < (s + 1) * half; ++i) {
+                const u32 c = sub32[i], second = run + (c & 0xFFFFu);
+                sub32[i] = run | (second << 16);
+                run = second + (c >> 16);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                int i;
+                if (word[v][e] != 0xFFFFFFFFu && counter_of(word[v][e], i)) rank[v][e >> 1] += (u32)sub[i] << (16 * (e & 1));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+    }
 #pragma unroll
     for (int v = 0; v < V; ++v)
 #pragma unroll
@@ -500,8 +554,8 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
     __syncthreads();
 
     int it = 0;
-    auto solve = [&](auto wide) {
-        constexpr bool WIDE = decltype(wide)::value;
+    auto solve = [&](auto wide, auto crowded_row) {
+        constexpr bool WIDE = decltype(wide)::value, CROWDED = decltype(crowded_row)::value;   // may there be heavy buckets?
         constexpr int CW = WIDE ? 2 * S::kChunk : S::kChunk, CT = S::kChunksPerThread;
         typedef Moment<WIDE> Mom;
         const int NC = N / CW;                                       // whole chunks: N is a multiple of 128
@@ -556,16 +610,17 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
             const int r = (int)(((u64)(2 * kr + 1) * (u64)n_dense) / (u64)(2 * K));
             const int b0 = (int)rank_bucket[kr], p0 = (int)start[b0], p1 = (int)start[b0 + 1];
             const u32 first = half_key(A[min(p0 + n, N - 1)] >> 16);
-            u32 key = kmin + ((u32)b0 << shift);
+            const bool sorted = CROWDED && p1 - p0 >= kHeavy;
+            u32 key = sorted ? half_key(A[r] >> 16) : kmin + ((u32)b0 << shift);
             for (int b = shift - 1; b >= 0; --b) {
                 const u32 cand = key + (1u << b);                    // no more than r - p0 words below cand: the key is cand or above
                 u32 below = 0, v = first;
-                for (int j0 = p0; __any(j0 < p1); j0 += 8) {
+                for (int j0 = p0; __any(!sorted && j0 < p1); j0 += 8) {
                     const int j = j0 + n;
                     if (j0 != p0) v = half_key(A[min(j, N - 1)] >> 16);
                     below += j < p1 && v < cand ? 1u : 0u;
                 }
-                if ((int)group_sum(Plain{below}).v <= r - p0) key = cand;
+                if (!sorted && (int)group_sum(Plain{below}).v <= r - p0) key = cand;
             }
             if (n == 0 && k0 < K) cen_s[k0] = half_bits_to_f32(key_half(key));
         }
@@ -584,10 +639,21 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
             const float t = __fadd_rn(cen, __builtin_bit_cast(float, dpp_u32<kRowShl1>(__builtin_bit_cast(u32, cen), __builtin_bit_cast(u32, cen))));
             const u32 kk = key_below(t);
             const u32 b = (umin(umax(kk, kmin), kmax) - kmin) >> shift;
-            const u32 p0 = kk < kmin ? 0u : start[b], p1 = kk < kmin ? 0u : start[b + 1];
+            u32 p0 = kk < kmin ? 0u : start[b], p1 = kk < kmin ? 0u : start[b + 1];
             // 2 w <= t, with both sides scaled exactly.  It holds for all words in front of the bucket and for none behind it, which a lane
             // may read as well; behind the last word lie kPad that are above every t.
             const float t24 = t * 8388608.0f;
+            if constexpr (CROWDED) {
+                const bool sorted = p1 - p0 >= (u32)kHeavy;          // the words below the boundary end at `at`
+                u32 at = p0, end = sorted ? p1 : p0;
+                while (__any(at < end)) {
+                    const u32 mid = (at + end) / 2;                  // no word of this lane is left: at == end == mid, and both stay
+                    const bool below = weight24(A[mid]) <= t24;
+                    at = below && at < end ? mid + 1 : at;
+                    end = below ? end : mid;
+                }
+                if (sorted) p0 = p1 = at;
+            }
             const u32 j0 = p0 & ~(u32)(CW - 1);
             const u32 c0 = C0[j0 / CW];
             const Mom c1 = C1[j0 / CW];
@@ -622,8 +688,13 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
         if (lane < K) cen_s[lane] = cen;
     };
     if (n_dense > 0) {
-        if (kmax >= 0xD800u || kmin <= 0x27FFu) solve(std::integral_constant<bool, true>{});    // |w| >= 128 somewhere
-        else solve(std::integral_constant<bool, false>{});
+        // One form for rows with and without heavy buckets would make an update of an ordinary 4096x11008 matrix 8 % longer; with the two-word
+        // sums in all rows with heavy buckets, 1024x28672 of 8-bit levels takes 897 us instead of 623.  The ordinary form stands first: behind
+        // the others it took 4 % longer.
+        const bool wide = kmax >= 0xD800u || kmin <= 0x27FFu;        // |w| >= 128 somewhere
+        if (__builtin_expect(!wide && !heavy, 1)) solve(std::false_type{}, std::false_type{});
+        else if (wide) solve(std::true_type{}, std::true_type{});
+        else solve(std::false_type{}, std::true_type{});
     } else if (tid < K) {
         cen_s[tid] = 0.f;
     }
