@@ -262,8 +262,10 @@ __global__ void __launch_bounds__(kPassThreads) quant_count_kernel(int M, int N,
 }
 
 // ---------------------------------------------------------------------------------------------- k-means of one row
-// Exact sum of products s * w * 2^24.  |w| < 128 in the whole row: a product is below 2^47 and a row's sum below 2^63; else the low and
-// the high words of the products are summed apart.
+// Exact sum of products s * w * 2^24.  Narrow rows, -128 < w < 127.9375 (the fp16 number below 128): w * 2^24 fits an int, a product is
+// below 2^47 and a row's sum below 2^63; in wide rows the low and the high words of the products are summed apart.
+constexpr u32 kNarrowEnd = 0x57FF;                                   // fp16 bits of 127.9375
+static_assert(127.9375 * 16777216.0 < 2147483648.0 && 127.9375 * 2 > 2 * 127.875, "an int holds it, and it lies above every boundary of a narrow row");
 template <bool WIDE>
 struct Moment {
     i64 v;
@@ -318,7 +320,9 @@ __device__ __forceinline__ u32 key_below(float t) {
 
 // A word of the row in LDS: fp16 bits << 16 | sensitivity
 __device__ __forceinline__ float weight24(u32 word) { return half_bits_to_f32(word >> 16) * 16777216.0f; }
-constexpr u32 kBeyond = 0x7C000000u;                                 // +infinity with sensitivity 0: above every boundary, adds nothing
+// Behind the row: sensitivity 0, so it adds nothing, and a weight above every boundary of the row.  In narrow rows, whose words are converted
+// to integers, a finite one.
+constexpr u32 kBeyondNarrow = kNarrowEnd << 16, kBeyondWide = 0x7C000000u;   // 127.9375, +infinity
 constexpr int kPad = 16;                                             // words of it behind the row: a round of the iterations ends there at the latest
 // Words from which a bucket is sorted and searched instead of read through.  A round reads 16 words and a bisection step one, in about the
 // same time: at 128 words rows of 8-bit levels, whose fullest buckets hold 137, lost (4096x11008 at 4 bits 751 us, 639 at 256 words, 633
@@ -550,12 +554,13 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
         for (int e = 0; e < 8; ++e)
             if (word[v][e] != 0xFFFFFFFFu)
                 A[start[bucket_of(word[v][e])] + ((e & 1) ? rank[v][e >> 1] >> 16 : rank[v][e >> 1] & 0xFFFFu)] = (key_half(word[v][e] >> 16) << 16) | (word[v][e] & 0xFFFFu);
-    for (int j = n_dense + tid; j < N + kPad; j += T) A[j] = kBeyond;
+    const bool wide = kmax >= (kNarrowEnd | 0x8000u) || kmin <= 0x27FFu;   // keys of 127.9375 and -128
+    for (int j = n_dense + tid; j < N + kPad; j += T) A[j] = wide ? kBeyondWide : kBeyondNarrow;
     __syncthreads();
 
     int it = 0;
-    auto solve = [&](auto wide, auto crowded_row) {
-        constexpr bool WIDE = decltype(wide)::value, CROWDED = decltype(crowded_row)::value;   // may there be heavy buckets?
+    auto solve = [&](auto wide_row, auto crowded_row) {
+        constexpr bool WIDE = decltype(wide_row)::value, CROWDED = decltype(crowded_row)::value;   // may there be heavy buckets?
         constexpr int CW = WIDE ? 2 * S::kChunk : S::kChunk, CT = S::kChunksPerThread;
         typedef Moment<WIDE> Mom;
         const int NC = N / CW;                                       // whole chunks: N is a multiple of 128
@@ -691,7 +696,6 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
         // One form for rows with and without heavy buckets would make an update of an ordinary 4096x11008 matrix 8 % longer; with the two-word
         // sums in all rows with heavy buckets, 1024x28672 of 8-bit levels takes 897 us instead of 623.  The ordinary form stands first: behind
         // the others it took 4 % longer.
-        const bool wide = kmax >= 0xD800u || kmin <= 0x27FFu;        // |w| >= 128 somewhere
         if (__builtin_expect(!wide && !heavy, 1)) solve(std::false_type{}, std::false_type{});
         else if (wide) solve(std::true_type{}, std::true_type{});
         else solve(std::false_type{}, std::true_type{});

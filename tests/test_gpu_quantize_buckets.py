@@ -49,6 +49,23 @@ def test_rows_extracted_entirely():
     compare(M, N, bits, got, ref)
 
 
+@pytest.mark.parametrize("N,bits", [(128, 2), (4096, 3), (11008, 4), (16384, 2), (28672, 3)])
+def test_limit_of_the_one_word_sums(N, bits):
+    """one row on each side of every limit: 127.875 is the largest weight of a row with one-word sums, 127.9375 and -128 are the first of
+    the two-word sums; largest sensitivities, so the sums themselves reach their limits"""
+    M = 9
+    print(f"one-word limit N={N} bits={bits}", flush=True)
+    rng = np.random.default_rng(N)
+    top, first = 127.875, 127.9375
+    sign = np.where(rng.random(N) < 0.5, -1.0, 1.0)
+    w = np.array([np.full(N, top), np.full(N, first), np.full(N, 128.0), np.full(N, -first), np.full(N, -128.0), top * sign, first * sign,
+                  128.0 * sign, np.where(rng.random(N) < 0.3, rng.uniform(-100, 100, N), top * sign)]).astype(np.float16)
+    s = np.full((M, N), 65535, dtype=np.uint16)
+    s[8] = rng.integers(0, 65536, N)
+    w = w.view(np.uint16)
+    compare(M, N, bits, run_gpu(w, s, bits, 0, 0, 0, 12), qo.quantize_layer(w, s, bits, 0, 0, 0, 12))
+
+
 def crowded_weights(kind, M, N, rng):
     """rows with many words of few keys: some buckets hold kHeavy = 256 words and more, next to buckets of a few"""
     z = rng.standard_normal((M, N))
