@@ -50,7 +50,6 @@ __device__ __forceinline__ void wave_fence() {                       // orders t
 // Pair tables of a row group in LDS: entry e of row r lies at byte e * 128 + r * 4 and a second copy 64 bytes further.  Lanes with an even
 // q read the first copy, lanes with an odd q the second, so the 32 lanes the LDS serves together read 32 different banks whatever their
 // indices are.  (One copy: two lanes of a row share its bank, 4.5 cycles per look-up.)
-constexpr u32 kEntryStride = 128;
 template <int BITS>
 __device__ __forceinline__ void entry_offsets(const LaneChunk<BITS>& c, u32 base, u32 (&a)[16]) {
 #pragma unroll
@@ -73,17 +72,11 @@ __device__ __forceinline__ void lookup_window(const LaneChunk<BITS>& c, u32 base
     for (int p = 0; p < 16; ++p) w[p] = *reinterpret_cast<const lds_u32*>(a[p]);
 }
 
-// LDS of one dense wave: the window's activations, one plane of 64 row pairs per column.  With 8 and 16 columns the planes are rotated by
-// up to 24 dwords each and lie 400 bytes apart, else 272.
+// A wave's staging area (sizes: sqllm_batch_split.h).
 template <int BT>
 struct BatchStage {
-    static constexpr bool kRotated = BT == 8 || BT == 16;
-    static constexpr int kPitch = kRotated ? 400 : 272;
-    // indices of the window, row by row; 48 bytes per row, or 64 with the four chunks rotated by row (eight neighbouring lanes then read
-    // chunks of eight different bank groups)
-    static constexpr int index_bytes(int bits) { return bits == 4 ? 1024 : 768; }
-    static constexpr int bytes(int bits) { return index_bytes(bits) + BT * kPitch; }
-    static constexpr int kSparseBytes = 256 + BT * kPitch;           // of a sparse wave: the values of 128 nonzeros in place of indices
+    static constexpr bool kRotated = batch_rotated(BT);
+    static constexpr int kPitch = batch_pitch(BT);
     template <int BITS>
     __device__ static u32 index_piece(int row, int part) {           // LDS offset of 16-byte piece `part` of a row
         return BITS == 4 ? 64u * (u32)row + 16u * (((u32)part + (u32)(row >> 1)) & 3u) : 48u * (u32)row + 16u * (u32)part;
@@ -95,10 +88,9 @@ struct BatchStage {
 };
 
 constexpr int kSparseWindowsPerWave = 6;                             // windows a sparse wave takes before the rest is shared by all waves
-constexpr int kMaxBatchWaves = 12;                                   // three per SIMD: up to 168 registers per lane
 
 template <int BITS, int RG, int BT>
-__global__ void __launch_bounds__(kMaxBatchWaves * kWave) matvec_batch_kernel(MatvecArgs g, int ND) {
+__global__ void __launch_bounds__(kMaxBatchWaves * kWave, batch_waves_per_simd(RG, BT)) matvec_batch_kernel(MatvecArgs g, int ND) {
     constexpr int R = 16 * RG, K = 1 << BITS, E = TableShape<BITS>::kEntries;
     constexpr int kWinCols = 128;
     typedef BatchStage<BT> Stage;
@@ -124,8 +116,8 @@ __global__ void __launch_bounds__(kMaxBatchWaves * kWave) matvec_batch_kernel(Ma
     }
     const size_t row_dwords = (size_t)g.N * BITS / 32;
     // LDS byte address of the wave's own area (uniform): indices or values, then activations
-    const u32 wave_lds = dense_wave ? (u32)(RG * E) * kEntryStride + (u32)wave * (u32)Stage::bytes(BITS)
-                                    : (ND > 0 ? (u32)(RG * E) * kEntryStride : 0u) + (u32)ND * (u32)Stage::bytes(BITS) + (u32)(wave - ND) * (u32)Stage::kSparseBytes;
+    const u32 wave_lds = dense_wave ? (u32)(RG * E) * kEntryStride + (u32)wave * (u32)batch_dense_bytes(BITS, BT)
+                                    : (ND > 0 ? (u32)(RG * E) * kEntryStride : 0u) + (u32)ND * (u32)batch_dense_bytes(BITS, BT) + (u32)(wave - ND) * (u32)batch_sparse_bytes(BT);
     // Indices are fetched in pieces of 16 bytes, BITS to a row and window: piece l of a row group to lane l, row by row, so that neighbouring lanes
     // read neighbouring bytes; they reach the lanes that use them through LDS.  Fetched by those lanes themselves -- neighbouring lanes on
     // different rows -- every lane is a cache access of its own: 144 per load at 3 bits, the vector L1 busy for 65 % of the launch.
@@ -146,7 +138,7 @@ __global__ void __launch_bounds__(kMaxBatchWaves * kWave) matvec_batch_kernel(Ma
         for (int j = 0; j < NP; ++j) c[j] = piece[j][t * BITS];
     };
     const u32 idx_rd = wave_lds + Stage::template index_chunk<BITS>(r, q);
-    const u32 stage_lds = wave_lds + (dense_wave ? (u32)Stage::index_bytes(BITS) : 256u);
+    const u32 stage_lds = wave_lds + (dense_wave ? (u32)batch_index_bytes(BITS) : 256u);
     const u32 tab0 = (u32)r * 4u + 64u * (q & 1);
     auto load_xblock = [&](int t, u32 (&v)[16]) {
         if constexpr (Stage::kRotated) {
@@ -246,6 +238,9 @@ __global__ void __launch_bounds__(kMaxBatchWaves * kWave) matvec_batch_kernel(Ma
     // ---- requested before the tables are built: the first two windows of a dense wave (ND <= nwin)
     u32x4 c0[NP], c1[NP];                                            // indices of windows ahead, as fetched
     LaneChunk<BITS> d[RG];                                           // of the current window, the lane's own
+    // Activations are requested two windows ahead where the registers for them are free, else one.  (One ahead everywhere: 22016x8192, 3 bits,
+    // 8 columns 40.2 against 35.9 us; smaller layers are the same either way.)
+    constexpr bool kFar = !(RG == 2 && BT >= 14);
     u32 xb[16], xv0[16], xv1[16];
     int t = wave;
     const int last_t = dense_wave ? wave + ((nwin - 1 - wave) / ND) * ND : 0;   // this wave's last window
@@ -266,7 +261,7 @@ __global__ void __launch_bounds__(kMaxBatchWaves * kWave) matvec_batch_kernel(Ma
         if (dense_wave) {
             load_xblock(t, xv0);
             load_idx(t, c0);
-            load_xblock(min(t + ND, last_t), xv1);
+            if constexpr (kFar) load_xblock(min(t + ND, last_t), xv1);
             load_idx(min(t + ND, last_t), c1);
         }
         for (int h = tid / R; h < K; ) {
@@ -383,11 +378,11 @@ __global__ void __launch_bounds__(kMaxBatchWaves * kWave) matvec_batch_kernel(Ma
     const int own = ND > 0 ? min(total, NS * kSparseWindowsPerWave) : total;   // windows the sparse waves take alone
     __syncthreads();
     if (dense_wave) {
-        // ---- dense term: windows t, t + ND, ...  Indices and activations are requested two windows ahead.  Past the wave's last window
+        // ---- dense term: windows t, t + ND, ...  Indices are requested two windows ahead, activations two or one.  Past the wave's last window
         //      the requests repeat that window (valid addresses, results unused) instead of branching around loads.
-        auto advance = [&](u32 (&xv)[16], u32x4 (&c)[NP]) {          // window t, which xv and c hold, is put in place; t + 2 ND is requested
+        auto advance = [&](u32 (&xv)[16], u32x4 (&c)[NP]) {          // window t, which xv and c hold, is put in place; the next ones are requested
             stage(xv, c, xb, d);
-            load_xblock(min(t + 2 * ND, last_t), xv);
+            load_xblock(min(t + (kFar ? 2 : 1) * ND, last_t), xv);
             load_idx(min(t + 2 * ND, last_t), c);
         };
         auto window = [&]() {
@@ -406,7 +401,8 @@ __global__ void __launch_bounds__(kMaxBatchWaves * kWave) matvec_batch_kernel(Ma
             advance(xv0, c0);
             window();
             if (t >= nwin) break;
-            advance(xv1, c1);
+            if constexpr (kFar) advance(xv1, c1);
+            else advance(xv0, c1);
             window();
             if (t >= nwin) break;
         }
@@ -439,37 +435,21 @@ __global__ void __launch_bounds__(kMaxBatchWaves * kWave) matvec_batch_kernel(Ma
 }
 
 // ---------------------------------------------------------------------------------------------- launcher
-// Rows and waves per workgroup.  16 rows while that gives every compute unit at most one workgroup, else 32: the activations that a
-// workgroup reads and transposes serve twice the rows (weights from HBM, 0.45 % nonzeros, six and two waves: 5120x5120 at 16 columns 9.3
-// against 10.9 us, 8192x8192 19.1 against 22.2; with fewer rows half the units would idle: 1024x8192 12.2 against 9.5, 4096x11008 20.5
-// against 15.8).
-// Six dense and two sparse waves while there is one workgroup per unit (4096x11008 at 16 columns 15.8 us; four and four 17.7, eight and
-// two 15.6, eight and four 15.9; 8192x8192 19.1 / 19.0 / 20.1 / 19.2); beyond that four and four, so that two workgroups fit a unit
-// (13824x5120 at 5 columns 17.3 us; six and two 18.2, eight and four 19.3; 22016x2048 at 16 columns 17.6 / 18.6 / 19.5).  Without a sparse
-// term eight and four dense waves (8192x8192 14.3 against 15.8 us, 13824x5120 15.5 against 14.2).
-constexpr int kUnits = 256;
+// Rows and waves per workgroup: batch_split.
 template <int BITS, int RG, int BT>
-static hipError_t launch_batch_r(const MatvecArgs& g, hipStream_t s) {
-    constexpr int R = 16 * RG;
-    const int nwin = g.N / 128, groups = (g.M + R - 1) / R;
-    const bool one = groups <= kUnits, sparse = g.nnz > 0;
-    const int ND = g.qidx ? min(nwin, one ? (sparse ? 6 : 8) : 4) : 0;
-    const int NS = ND == 0 ? 8 : (sparse ? (one ? 2 : 4) : 0);
-    const int NW = ND + NS;
-    const size_t stage = (ND ? (size_t)RG * TableShape<BITS>::kEntries * kEntryStride + (size_t)ND * BatchStage<BT>::bytes(BITS) : 0) + (size_t)NS * BatchStage<BT>::kSparseBytes, part = (size_t)NW * R * 64;
-    const size_t lds = stage > part ? stage : part;
-    if (lds > 64 * 1024) {
+static hipError_t launch_batch_r(const MatvecArgs& g, const BatchSplit& b, hipStream_t s) {
+    if (b.lds > 64 * 1024) {
         // the attribute belongs to the current device's copy of the kernel; the call is a host-side table update
-        const hipError_t ea = hipFuncSetAttribute(reinterpret_cast<const void*>(&matvec_batch_kernel<BITS, RG, BT>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        const hipError_t ea = hipFuncSetAttribute(reinterpret_cast<const void*>(&matvec_batch_kernel<BITS, RG, BT>), hipFuncAttributeMaxDynamicSharedMemorySize, kUnitLds);
         if (ea != hipSuccess) return ea;
     }
-    hipLaunchKernelGGL((matvec_batch_kernel<BITS, RG, BT>), dim3(groups), dim3(NW * kWave), lds, s, g, ND);
+    hipLaunchKernelGGL((matvec_batch_kernel<BITS, RG, BT>), dim3(b.blocks), dim3((b.dense_waves + b.sparse_waves) * kWave), b.lds, s, g, b.dense_waves);
     return hipGetLastError();
 }
 template <int BITS, int RG>
-static hipError_t launch_batch_b(const MatvecArgs& g, hipStream_t s) {
+static hipError_t launch_batch_b(const MatvecArgs& g, const BatchSplit& b, hipStream_t s) {
     switch (g.B) {
-#define SQ_B(n) case n: return launch_batch_r<BITS, RG, n>(g, s);
+#define SQ_B(n) case n: return launch_batch_r<BITS, RG, n>(g, b, s);
         SQ_B(2) SQ_B(3) SQ_B(4) SQ_B(5) SQ_B(6) SQ_B(7) SQ_B(8) SQ_B(9) SQ_B(10) SQ_B(11) SQ_B(12) SQ_B(13) SQ_B(14) SQ_B(15) SQ_B(16)
 #undef SQ_B
         default: return hipErrorInvalidValue;
@@ -477,8 +457,8 @@ static hipError_t launch_batch_b(const MatvecArgs& g, hipStream_t s) {
 }
 template <int BITS>
 static hipError_t launch_batch(const MatvecArgs& g, hipStream_t s) {
-    const bool two = (g.M + 15) / 16 > kUnits;
-    return two ? launch_batch_b<BITS, 2>(g, s) : launch_batch_b<BITS, 1>(g, s);
+    const BatchSplit b = batch_split(g.M, g.N, BITS, g.B, g.qidx != nullptr, g.nnz > 0);
+    return b.row_groups == 2 ? launch_batch_b<BITS, 2>(g, b, s) : launch_batch_b<BITS, 1>(g, b, s);
 }
 
 hipError_t launch_matvec_batch(const MatvecArgs& g, hipStream_t s) {

@@ -1,0 +1,42 @@
+"""csrc/sqllm_batch_split.h compiled for the CPU, with signed overflow made fatal."""
+import ctypes
+import functools
+import os
+import subprocess
+import tempfile
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2306_07629_amd", "csrc")
+
+SOURCE = r"""
+#include "sqllm_batch_split.h"
+using namespace sqllm;
+extern "C" {
+int count(int first, int end) { return window_count(first, end); }
+int rest(int p0, int end) { return window_rest(p0, end); }
+uint32_t row_bits(int lo, int hi, int p0, int q) { return window_row_bits(lo, hi, p0, q); }
+void split(int M, int N, int bits, int B, int dense, int sparse, int* out) {
+    const BatchSplit s = batch_split(M, N, bits, B, dense != 0, sparse != 0);
+    out[0] = s.row_groups; out[1] = s.blocks; out[2] = s.dense_waves; out[3] = s.sparse_waves; out[4] = (int)s.lds;
+}
+int waves_per_simd(int row_groups, int B) { return batch_waves_per_simd(row_groups, B); }
+}
+"""
+
+
+@functools.lru_cache(maxsize=None)
+def library():
+    with tempfile.TemporaryDirectory() as d:
+        src, so = os.path.join(d, "split.cpp"), os.path.join(d, "split.so")
+        with open(src, "w") as f:
+            f.write(SOURCE)
+        subprocess.run(["g++", "-std=c++17", "-O1", "-ftrapv", "-Wall", "-Werror", "-shared", "-fPIC", "-I" + CSRC, src, "-o", so], check=True)
+        lib = ctypes.CDLL(so)
+    lib.row_bits.restype = ctypes.c_uint32
+    return lib
+
+
+def batch_split(M, N, bits, B, dense, sparse):
+    """(row groups, blocks, dense waves, sparse waves, bytes of LDS) of the launch"""
+    out = (ctypes.c_int * 5)()
+    library().split(M, N, bits, B, int(dense), int(sparse), out)
+    return tuple(out)

@@ -1,34 +1,16 @@
 """The plain arithmetic of the batch kernel (csrc/sqllm_batch_split.h), compiled for the CPU with signed overflow made fatal: windows of
-nonzeros up to the largest position the interface accepts (nnz < 2^31), against the definition in Python's integers."""
-import ctypes
-import os
-import subprocess
-
+nonzeros up to the largest position the interface accepts (nnz < 2^31), against the definition in Python's integers, and the split of
+rows and waves over the workgroups."""
 import pytest
 
-CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2306_07629_amd", "csrc")
-TOP = 2 ** 31 - 1
+import host_split
 
-SOURCE = r"""
-#include "sqllm_batch_split.h"
-using namespace sqllm;
-extern "C" {
-int count(int first, int end) { return window_count(first, end); }
-int rest(int p0, int end) { return window_rest(p0, end); }
-uint32_t row_bits(int lo, int hi, int p0, int q) { return window_row_bits(lo, hi, p0, q); }
-}
-"""
+TOP = 2 ** 31 - 1
 
 
 @pytest.fixture(scope="module")
-def split(tmp_path_factory):
-    d = tmp_path_factory.mktemp("split")
-    src, so = d / "split.cpp", d / "split.so"
-    src.write_text(SOURCE)
-    subprocess.run(["g++", "-std=c++17", "-O1", "-ftrapv", "-Wall", "-Werror", "-shared", "-fPIC", "-I" + CSRC, str(src), "-o", str(so)], check=True)
-    lib = ctypes.CDLL(str(so))
-    lib.row_bits.restype = ctypes.c_uint32
-    return lib
+def split():
+    return host_split.library()
 
 
 @pytest.mark.parametrize("first,end", [(0, 1), (0, 128), (3, 132), (7, 7), (0, TOP), (TOP - 1, TOP), (TOP - 127, TOP), (TOP - 200, TOP),
@@ -54,3 +36,28 @@ def test_row_bits_name_the_positions_of_the_row(split, base):
                 assert split.row_bits(ptr[r], ptr[r + 1], p0, q) == sum(1 << k for k in range(32) if owner[k] == r), (p0, q, r)
     assert split.row_bits(0, base, base, 0) == 0                     # rows far in front of and far behind the window
     assert split.row_bits(TOP, TOP, 0, 3) == 0
+
+
+UNIT_LDS, UNITS = 160 * 1024, 256
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("B", range(2, 17))
+def test_split_fills_the_units_it_says_it_fills(split, bits, B):
+    for M in (1, 16, 200, 4096, 4097, 8192, 8193, 22016, 10 ** 6, TOP):
+        for N in (128, 384, 640, 1024, 8192, 28672):
+            for dense, sparse in ((1, 1), (1, 0), (0, 1)):
+                rg, blocks, nd, ns, lds = host_split.batch_split(M, N, bits, B, dense, sparse)
+                assert blocks * 16 * rg >= M > (blocks - 1) * 16 * rg
+                assert (nd > 0) == bool(dense) and nd <= N // 128    # a dense wave without a window would read one that is not its own
+                assert (ns > 0) == bool(sparse) and 1 <= nd + ns <= 8
+                assert lds <= UNIT_LDS
+                # four waves per SIMD of 512 registers: two workgroups of eight waves fit a unit's four
+                if rg == 2 and B >= 13:
+                    assert split.waves_per_simd(rg, B) == 4
+                if dense and blocks > UNITS and N >= 1024:
+                    shared = nd == 4
+                    assert not shared or 2 * lds <= UNIT_LDS
+                    assert shared == (bits < 4 or (B <= 5 if sparse else B <= 11 and B != 8)), (bits, B, sparse)
+                    if not shared:                                   # one workgroup keeps the unit busy
+                        assert nd + ns == 8 and nd >= 5

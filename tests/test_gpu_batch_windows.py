@@ -29,6 +29,19 @@ def test_row_counts_where_the_split_changes(M, N, bits, B):
         check(D.matvec(), ref, absdot, ("fused", frac))
 
 
+@pytest.mark.parametrize("M,N,bits,B", [(8209, 384, 4, 5), (8209, 640, 4, 6), (8209, 1152, 4, 7), (8225, 896, 4, 8), (8209, 768, 4, 13), (8225, 1152, 4, 16),
+                                        (8209, 384, 3, 13), (8209, 640, 3, 14), (8225, 1152, 2, 15), (8209, 1024, 3, 16)])
+def test_more_workgroups_than_units(M, N, bits, B):
+    """workgroups that share a unit and workgroups that cannot (4 bits from 6 columns on, from 8 without a sparse term); 13 columns and
+    more request activations one window ahead"""
+    import paper_2306_07629_amd as sq
+    print(f"beyond the units M={M} N={N} bits={bits} B={B}", flush=True)
+    for frac in (0.0, 0.02):
+        L = gen.make_layer(M, N, bits, frac=frac, skew=(0.1, 0.5) if frac else None, B=B, seed=M + N + B)
+        ref, absdot = oracle.layer_matvec(L)
+        check(sq.DeviceLayer(L).matvec(), ref, absdot, ("fused", frac))
+
+
 @pytest.mark.parametrize("B", list(range(2, 17)))
 def test_heavy_rows_fill_many_windows(B):
     """two full rows of 6144 columns (48 windows each) in one workgroup, neighbours empty or with a few nonzeros"""

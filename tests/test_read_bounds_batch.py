@@ -4,6 +4,7 @@ pieces in which a gathered row of x is read), lies inside the array."""
 import numpy as np
 import pytest
 
+import host_split
 from test_read_bounds import SHAPES, rowptr_for
 
 LANES = np.arange(64)
@@ -24,13 +25,9 @@ def row_pieces(B):
 
 
 def batch_kernel_reads(M, N, bits, B, rowptr, cols):
-    two = (M + 15) // 16 > 256
-    RG = 2 if two else 1
+    nwin, nnz = N // 128, int(rowptr[-1])
+    RG, groups, ND, _, _ = host_split.batch_split(M, N, bits, B, True, nnz > 0)   # the launcher's own rule
     R, K = 16 * RG, 1 << bits
-    groups = (M + R - 1) // R
-    nwin, nnz, one = N // 128, int(rowptr[-1]), groups <= 256
-    ND = min(nwin, (6 if nnz else 8) if one else 4)
-    NS = (2 if one else 4) if nnz else 0
     heavy = int(np.argmax(np.diff(rowptr))) // R
     for block in sorted({0, groups - 1, groups // 2, heavy}):
         r0 = block * R
@@ -75,7 +72,7 @@ def test_a_gathered_row_is_read_once_and_no_further(B):
     assert (seen == 1).all()
 
 
-@pytest.mark.parametrize("M,N,bits,B", [s for s in SHAPES if s[3] > 1] + [(4096, 128, 3, 16), (4097, 256, 4, 5), (8193, 384, 3, 13)])
+@pytest.mark.parametrize("M,N,bits,B", [s for s in SHAPES if s[3] > 1] + [(4096, 128, 3, 16), (4097, 256, 4, 5), (8193, 384, 3, 13), (8209, 768, 4, 16)])
 def test_every_load_of_the_batch_kernel_stays_inside_its_array(M, N, bits, B):
     rowptr = rowptr_for(M, N, M + N + bits)
     nnz = int(rowptr[-1])
