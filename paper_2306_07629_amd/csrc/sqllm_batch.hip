@@ -35,9 +35,6 @@ typedef u32 u32x3 __attribute__((ext_vector_type(3)));
 typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
 typedef u32x3 u32x3_a4 __attribute__((aligned(4)));
 typedef u32x2 u32x2_a4 __attribute__((aligned(4)));
-typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
-typedef u32x2 u32x2_a2 __attribute__((aligned(2)));
-typedef u32 u32_a2 __attribute__((aligned(2)));
 typedef __attribute__((address_space(3))) u32 lds_u32;
 typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
 
@@ -240,7 +237,7 @@ __global__ void __launch_bounds__(kMaxBatchWaves * kWave, batch_waves_per_simd(R
     LaneChunk<BITS> d[RG];                                           // of the current window, the lane's own
     // Activations are requested two windows ahead where the registers for them are free, else one.  (One ahead everywhere: 22016x8192, 3 bits,
     // 8 columns 40.2 against 35.9 us; smaller layers are the same either way.)
-    constexpr bool kFar = !(RG == 2 && BT >= 14);
+    constexpr bool kFar = !(RG == 2 && BT >= 13);
     u32 xb[16], xv0[16], xv1[16];
     int t = wave;
     const int last_t = dense_wave ? wave + ((nwin - 1 - wave) / ND) * ND : 0;   // this wave's last window
@@ -327,16 +324,31 @@ __global__ void __launch_bounds__(kMaxBatchWaves * kWave, batch_waves_per_simd(R
             constexpr int H = (BT + 1) / 2;                          // dwords of a row; the last one of an odd batch is half used
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
-                const char* row = xc + e.col[k] * (2u * BT);
-                constexpr int n4 = BT / 8 * 4, n2 = n4 + (BT % 8 >= 4 ? 2 : 0);
+                // An odd batch's rows of odd columns begin in the middle of a dword.  They are read from that dword on: with the half in front,
+                // rows of even columns with the half behind them (the last column is odd: N is even), which rows_to_dwords drops.
+                const u32* row = reinterpret_cast<const u32*>(xc + ((e.col[k] * (2u * BT)) & ~3u));
 #pragma unroll
-                for (int i = 0; i < n4; i += 4) {
-                    const u32x4 v4 = *reinterpret_cast<const u32x4_a2*>(row + 4 * i);
+                for (int i = 0; i + 4 <= H; i += 4) {
+                    const u32x4 v4 = *reinterpret_cast<const u32x4_a4*>(row + i);
                     v[H * k + i] = v4.x; v[H * k + i + 1] = v4.y; v[H * k + i + 2] = v4.z; v[H * k + i + 3] = v4.w;
                 }
-                if constexpr (n2 > n4) { const u32x2 v2 = *reinterpret_cast<const u32x2_a2*>(row + 4 * n4); v[H * k + n4] = v2.x; v[H * k + n4 + 1] = v2.y; }
-                if constexpr (BT % 4 >= 2) v[H * k + n2] = *reinterpret_cast<const u32_a2*>(row + 4 * n2);
-                if constexpr (BT % 2 == 1) v[H * k + H - 1] = *reinterpret_cast<const uint16_t*>(row + 2 * (BT - 1));
+                constexpr int i = H & ~3;
+                if constexpr (H % 4 == 3) { const u32x3 t3 = *reinterpret_cast<const u32x3_a4*>(row + i); v[H * k + i] = t3.x; v[H * k + i + 1] = t3.y; v[H * k + i + 2] = t3.z; }
+                if constexpr (H % 4 == 2) { const u32x2 t2 = *reinterpret_cast<const u32x2_a4*>(row + i); v[H * k + i] = t2.x; v[H * k + i + 1] = t2.y; }
+                if constexpr (H % 4 == 1) v[H * k + i] = row[i];
+            }
+        }
+    };
+    // which of the lane's two rows begin in the middle of a dword, and the rows moved down by that half
+    auto half_starts = [&](const Entries& e) -> u32 { return BT % 2 == 1 ? (e.col[0] & 1u) | ((e.col[1] & 1u) << 1) : 0u; };
+    auto rows_to_dwords = [&](u32 (&v)[16], u32 odd) {
+        if constexpr (BT % 2 == 1) {
+            constexpr int H = (BT + 1) / 2;
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const u32 by = (odd << (4 - k)) & 16u;
+#pragma unroll
+                for (int i = 0; i < H; ++i) v[H * k + i] = funnel_shr(v[H * k + (i + 1 < H ? i + 1 : i)], v[H * k + i], by);
             }
         }
     };
@@ -345,17 +357,20 @@ __global__ void __launch_bounds__(kMaxBatchWaves * kWave, batch_waves_per_simd(R
         if (f >= end) return;                                        // uniform
         const int last_f = f + (end - 1 - f) / stride * stride;
         Entries e0, e1;
-        u32 v[16], vals = 0;
+        u32 v[16], vals = 0, odd = 0;
         load_entries(f, e0);
         load_entries(min(f + stride, last_f), e1);
         gather(e0, v);
+        odd = half_starts(e0);
         vals = e0.val[0] | (e0.val[1] << 16);
         for (; f < end; f += stride) {
             int wg, p0;
             find_window(f, wg, p0);
             *reinterpret_cast<lds_u32*>(wave_lds + 4u * (u32)lane) = vals;
+            rows_to_dwords(v, odd);
             const u32 at = put_x(v, std::true_type{});
             gather(e1, v);                                           // the next window's
+            odd = half_starts(e1);
             vals = e1.val[0] | (e1.val[1] << 16);
             load_entries(min(f + 2 * stride, last_f), e1);
             wave_fence();

@@ -1,6 +1,6 @@
 """Host-side check that the batch kernel never reads past the end of an input array: every address range it touches, re-computed from the
 clamping formulas it uses (rows past M, windows past a wave's last one, surplus lanes of an index load, nonzeros past a row group, the
-pieces in which a gathered row of x is read), lies inside the array."""
+dwords that hold a gathered row of x), lies inside the array."""
 import numpy as np
 import pytest
 
@@ -10,18 +10,11 @@ from test_read_bounds import SHAPES, rowptr_for
 LANES = np.arange(64)
 
 
-def row_pieces(B):
-    """(offset, bytes) of the loads that fetch one row of B halves at any 2-byte alignment"""
-    out, n4 = [], B // 8 * 4
-    n2 = n4 + (2 if B % 8 >= 4 else 0)
-    out += [(4 * i, 16) for i in range(0, n4, 4)]
-    if n2 > n4:
-        out.append((4 * n4, 8))
-    if B % 4 >= 2:
-        out.append((4 * n2, 4))
-    if B % 2:
-        out.append((2 * (B - 1), 2))
-    return out
+def row_reads(col, B):
+    """(first byte, bytes) of the loads that fetch the row of x of a column: whole rows of 8 and 16 columns in pieces of 16 bytes, else from
+    the dword on in which the row begins, in dwords"""
+    first = col * 2 * B & ~3
+    return first, 2 * B if B in (8, 16) else 4 * ((B + 1) // 2)
 
 
 def batch_kernel_reads(M, N, bits, B, rowptr, cols):
@@ -58,18 +51,19 @@ def batch_kernel_reads(M, N, bits, B, rowptr, cols):
                 q = np.minimum(gp[rg] + 128 * f + np.arange(128), ge[rg] - 1)
                 yield "cols", 4 * int(q.min()), 4 * int(q.max()) + 4
                 yield "vals", 2 * int(q.min()), 2 * int(q.max()) + 2
-                c = cols[q].astype(np.int64)
-                for off, n in ([(0, 2 * B)] if B in (8, 16) else row_pieces(B)):
-                    yield "x", int(c.min()) * 2 * B + off, int(c.max()) * 2 * B + off + n
+                for c in sorted({int(v) for v in cols[q]}):
+                    first, n = row_reads(c, B)
+                    yield "x", first, first + n
 
 
 @pytest.mark.parametrize("B", range(2, 17))
-def test_a_gathered_row_is_read_once_and_no_further(B):
-    seen = np.zeros(2 * B, dtype=int)
-    for off, n in row_pieces(B):
-        assert off + n <= 2 * B
-        seen[off:off + n] += 1
-    assert (seen == 1).all()
+def test_a_gathered_row_is_read_whole_and_inside_the_array(B):
+    N = 128
+    for col in range(N):
+        first, n = row_reads(col, B)
+        assert first % 4 == 0 and 0 <= first <= col * 2 * B          # whole row
+        assert col * 2 * B + 2 * B <= first + n <= 2 * N * B         # and no byte past the last row
+        assert n - 2 * B == 2 * (B % 2)                              # at most one foreign half
 
 
 @pytest.mark.parametrize("M,N,bits,B", [s for s in SHAPES if s[3] > 1] + [(4096, 128, 3, 16), (4097, 256, 4, 5), (8193, 384, 3, 13), (8209, 768, 4, 16)])
