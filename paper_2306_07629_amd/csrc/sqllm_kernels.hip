@@ -918,27 +918,52 @@ __global__ void __launch_bounds__(256) csr_rowwise_kernel(MatvecArgs g) {
 // One wave expands up to kExpandUnits x 512 columns of a row: a lane handles eight neighbouring weights per unit, so that a wave reads a
 // contiguous piece of the index stream and writes 1 KB of fp16 (512 bytes of indices) with one instruction.  Same pair tables and field
 // order as the matvec; without a table the entries are the indices 0, 1, 2, ... themselves and the low bytes of the pairs are kept.
-// Every wave owns its table, so nothing waits for a barrier.  Bound by the writes: 13824x5120 at 3 bits 37.3 us (4.5 TB/s in and out; a
-// large copy reaches 5.0), against 54.4 us with 32 weights per lane and 16 dword stores at a stride of 64 bytes.
+// Every wave owns its table, so nothing waits for a barrier.  Bound by the writes: 13824x5120 at 3 bits 33.2 us with indices from HBM and a
+// cold output (5.1 TB/s in and out, the rate of a large copy), 28.7 where the last-level cache holds them; 57 and 52 us with 32 weights per
+// lane and 16 dword stores at a stride of 64 bytes.
 // Eight units of requests in flight per wave; a wider row is split evenly so that no wave gets a short rest.
 constexpr int kExpandUnits = 8, kExpandWaves = 4;
+// Few rows are split further, until there are eight waves per compute unit: 256x4096 2.9 us, with a wave per row 4.0 (512 waves 3.3, 1024
+// and 4096 2.9); 512x4096 3.3 (1024 waves 3.5, 4096 3.5).
+constexpr int kExpandMinWaves = 2048;
 typedef u32x4 u32x4_a2 __attribute__((aligned(2)));                  // the outputs need not be aligned to more than one element
 typedef u32x2 u32x2_a1 __attribute__((aligned(1)));
 
-// the 8 BITS index bits of eight neighbouring weights (group g of the row; above them: other weights' bits)
+// v[k]: the 8 BITS index bits of the eight weights of group (u0 + k) * 64 + lane, for the n units of a wave (above them: other weights' bits).
+// Lanes past the row repeat its last group.  With 2 and 4 bits a unit is 128 or 256 bytes and lies in lines of its own.  With 3 bits it is
+// 192 and every other line holds pieces of two units: fetched per unit, 13824x5120 took 40.0 us from HBM and 36.6 from the last-level cache
+// (41.5 and 27.0 with plain loads in place of non-temporal ones).  So the wave's dwords are fetched 64 at a time and the groups read from
+// LDS: 33.2 and 28.7.
+constexpr int kExpandStage = 3 * kExpandUnits * kWave / 4;          // dwords of eight units at 3 bits
 template <int BITS>
-__device__ __forceinline__ u32 load_group(const char* __restrict__ qrow, int g, int groups, int lane) {
+__device__ __forceinline__ void load_groups(const char* __restrict__ qrow, int u0, int n, int groups, int lane, u32* __restrict__ stage, u32 (&v)[kExpandUnits]) {
     if constexpr (BITS == 3) {
-        // four lanes share three dwords: lane l of the quad fetches dword l (lane 3 dword 2 again) and takes bits [24 l, 24 l + 24)
-        const int l = lane & 3, chunk = min(g >> 2, (groups >> 2) - 1);
-        const u32 d = __builtin_nontemporal_load(reinterpret_cast<const u32*>(qrow) + 3 * chunk + min(l, 2));
-        const u32 lo = (u32)__builtin_amdgcn_mov_dpp((int)d, 0x90, 0xF, 0xF, true);   // quad_perm [0,0,1,2]
-        const u32 hi = (u32)__builtin_amdgcn_mov_dpp((int)d, 0xA4, 0xF, 0xF, true);   // quad_perm [0,1,2,2]
-        return funnel_shr(hi, lo, (24u * (u32)l) & 31u);
-    } else if constexpr (BITS == 4) {
-        return __builtin_nontemporal_load(reinterpret_cast<const u32*>(qrow) + min(g, groups - 1));
+        const u32* q = reinterpret_cast<const u32*>(qrow) + 48 * u0;
+        const int own = min(n * kWave, groups - u0 * kWave), dwords = own / 4 * 3;   // whole chunks of 32 weights: N is a multiple of 128
+        u32 raw[kExpandStage / kWave];
+#pragma unroll
+        for (int j = 0; j < kExpandStage / kWave; ++j)
+            if (64 * j < dwords) raw[j] = __builtin_nontemporal_load(q + min(64 * j + lane, dwords - 1));   // uniform branch
+#pragma unroll
+        for (int j = 0; j < kExpandStage / kWave; ++j)
+            if (64 * j < dwords) stage[64 * j + lane] = raw[j];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+        for (int k = 0; k < kExpandUnits; ++k)
+            if (k < n) {
+                const int g = min(k * kWave + lane, own - 1), d = 3 * g / 4;   // bits 24 g: dword d on; the last group of a chunk ends with dword d
+                v[k] = funnel_shr(stage[min(d + 1, dwords - 1)], stage[d], (24u * (u32)g) & 31u);
+            }
     } else {
-        return __builtin_nontemporal_load(reinterpret_cast<const uint16_t*>(qrow) + min(g, groups - 1));
+#pragma unroll
+        for (int k = 0; k < kExpandUnits; ++k)
+            if (k < n) {                                             // uniform branch
+                const int g = min((u0 + k) * kWave + lane, groups - 1);
+                v[k] = BITS == 4 ? __builtin_nontemporal_load(reinterpret_cast<const u32*>(qrow) + g)
+                                 : (u32)__builtin_nontemporal_load(reinterpret_cast<const uint16_t*>(qrow) + g);
+            }
     }
 }
 
@@ -946,16 +971,15 @@ template <int BITS, bool INDICES>
 __global__ void __launch_bounds__(kExpandWaves * kWave) expand_kernel(int M, int N, int segs, const void* __restrict__ qidx, const uint16_t* __restrict__ lut, void* __restrict__ out) {
     constexpr int K = 1 << BITS, E = TableShape<BITS>::kEntries;
     __shared__ __align__(8) u32 tables[kExpandWaves][E];
+    __shared__ u32 stage[BITS == 3 ? kExpandWaves : 1][BITS == 3 ? kExpandStage : 1];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int id = blockIdx.x * kExpandWaves + wave, row = id / segs, seg = id - row * segs;   // uniform
     if (row >= M) return;
-    const int groups = N / 8, units = (groups + kWave - 1) / kWave, per = (units + segs - 1) / segs;   // per <= kExpandUnits
+    const int groups = N / 8, units = (groups + kWave - 1) / kWave, per = (units + segs - 1) / segs;   // per <= kExpandUnits, and every wave has a unit
     const int u0 = seg * per, n = min(per, units - u0);
     const char* qrow = static_cast<const char*>(qidx) + (size_t)row * groups * BITS;
     u32 v[kExpandUnits];
-#pragma unroll
-    for (int k = 0; k < kExpandUnits; ++k)
-        if (k < n) v[k] = load_group<BITS>(qrow, (u0 + k) * kWave + lane, groups, lane);   // uniform branch
+    load_groups<BITS>(qrow, u0, n, groups, lane, stage[BITS == 3 ? wave : 0], v);
     u32* table = tables[wave];
     {
         const uint16_t* t = INDICES ? nullptr : lut + (size_t)row * K;
@@ -1172,7 +1196,9 @@ hipError_t launch_csr_rowwise(const MatvecArgs& g0, hipStream_t s) {
 
 template <int BITS>
 static void launch_expand(int M, int N, const void* qidx, const void* lut, void* idx_out, void* w_out, hipStream_t s) {
-    const int units = (N + 8 * kWave - 1) / (8 * kWave), segs = (units + kExpandUnits - 1) / kExpandUnits;
+    const int units = (N + 8 * kWave - 1) / (8 * kWave);
+    const int want = max((units + kExpandUnits - 1) / kExpandUnits, (kExpandMinWaves + M - 1) / M);
+    const int per = (units + want - 1) / want, segs = (units + per - 1) / per;   // units per wave, the last one's may be fewer
     const dim3 grid((unsigned)((M * segs + kExpandWaves - 1) / kExpandWaves)), block(kExpandWaves * kWave);
     if (w_out) hipLaunchKernelGGL((expand_kernel<BITS, false>), grid, block, 0, s, M, N, segs, qidx, static_cast<const uint16_t*>(lut), w_out);
     else hipLaunchKernelGGL((expand_kernel<BITS, true>), grid, block, 0, s, M, N, segs, qidx, nullptr, idx_out);

@@ -1,5 +1,5 @@
-"""Expansion to fp16 and to one byte per index where the kernel's split can go wrong: one and several segments per row, a last unit of
-128, 256 or 384 columns, fewer rows than a workgroup has waves, outputs aligned to one element only.  Bit-exact against the oracle."""
+"""Expansion to fp16 and to one byte per index where the kernel's split can go wrong: one and several segments per row (few rows are split
+until there are 2048 waves: from one unit to a whole row per wave), a last unit of 128, 256 or 384 columns, fewer rows than a workgroup has waves, outputs aligned to one element only.  Bit-exact against the oracle."""
 import numpy as np
 import pytest
 
@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("bits", [2, 3, 4])
-@pytest.mark.parametrize("M,N", [(1, 128), (3, 384), (5, 512), (2, 4096), (7, 4224), (3, 8448), (2, 28672)])
+@pytest.mark.parametrize("M,N", [(1, 128), (3, 384), (5, 512), (2, 4096), (7, 4224), (3, 8448), (2, 28672), (300, 3712), (700, 2176), (2049, 4224)])
 def test_expansion_at_the_edges(M, N, bits):
     import torch
     import paper_2306_07629_amd as sq
