@@ -34,13 +34,13 @@
  *   (a hipStream_t passed as void*, NULL = the default stream) and returns.  Device-side data (index
  *   ranges of cols, monotonicity of rowptr) is NOT validated; out-of-range columns are undefined behaviour.
  *   Finiteness is not validated either.  A non-finite activation x[j][t] reaches y[i][t] wherever the
- *   definition multiplies it by a weight (every row, through the dense term); in calls with B >= 3 the sparse
+ *   definition multiplies it by a weight (every row, through the dense term); in calls with B >= 2 the sparse
  *   term is formed by matrix instructions over groups of 16 rows, and a non-finite x[j][t] then also turns
  *   y[i][t] into NaN for the other rows of the group of a row holding a nonzero in column j (0 x Inf).
  *
  * ERRORS  every function returns an sqllm_status.  Arguments are validated on the host first and nothing is enqueued
  *   when validation fails.  An entry point that needs several kernel launches (batches of the one-thread-per-row
- *   kernel beyond 8 columns, more than 65535 rows in the parity exports, the offline pass) can fail in a later
+ *   kernel beyond 8 columns, more than 2^22 rows in the parity exports, the offline pass) can fail in a later
  *   launch with SQLLM_ERR_HIP after earlier ones were enqueued; its outputs are then undefined.  A text for the last
  *   error of the calling thread is available from sqllm_last_error_string().
  *   M == 0 -> SQLLM_OK, nothing enqueued.  N must be positive: N == 0 (an empty sum) is SQLLM_ERR_SHAPE, the caller

@@ -193,3 +193,26 @@ def test_quantize_argument_errors():
     for bad in ((-1, 128, 0.1, 0.1), (4, 128, -0.1, 0.0), (4, 128, 0.6, 0.5)):
         with pytest.raises(sq.SqllmError):
             sq.sqllm_extraction_counts(*bad)
+
+
+class _FakeStream:
+    cuda_stream = 0x1234
+
+
+@pytest.mark.parametrize("raw", [True, False])
+def test_current_stream_with_and_without_torchs_raw_handle(monkeypatch, raw):
+    """the handle of the current stream of the current device, whether or not torch has the function that gives it without an object"""
+    import torch
+    from paper_2306_07629_amd import binding
+    asked = []
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda dev=None: asked.append(dev) or _FakeStream())
+    if raw:
+        monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda dev: asked.append(dev) or 0x1234, raising=False)
+    else:
+        monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(binding, "_torch", None)
+    monkeypatch.setattr(binding, "_raw_stream", None)
+    assert binding._stream(None) == 0x1234 and binding._stream(None) == 0x1234
+    assert asked == [3, 3]
+    assert binding._stream(7) == 7 and binding._stream(_FakeStream()) == 0x1234

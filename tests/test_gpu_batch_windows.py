@@ -68,6 +68,52 @@ def test_heavy_rows_fill_many_windows(B):
     check(D.csr_spmv(), ref, absdot, "sparse alone")
 
 
+# (M, N, bits, windows the sparse waves take alone): two, two, four and three sparse waves of six windows each
+SHARED = [(50, 6144, 3, 12), (4113, 2048, 3, 12), (8209, 2048, 3, 24), (8209, 2048, 4, 18)]
+
+
+@pytest.mark.parametrize("M,N,bits,alone", SHARED)
+@pytest.mark.parametrize("B", [6, 13, 16])
+@pytest.mark.parametrize("group", [0, 1])                            # the row group that holds the heavy rows
+def test_every_shared_window_counts_once(M, N, bits, alone, B, group):
+    """fused calls whose workgroups hold as many windows as the sparse waves take alone, one more, and many more, which all waves share.
+    Tables of zeros, and values and activations of +1 and -1: every sum is a whole number that fp16 holds, and a nonzero lost or counted
+    twice changes it"""
+    import torch
+    import host_split
+    import paper_2306_07629_amd as sq
+    print(f"shared windows M={M} N={N} bits={bits} B={B} group={group}", flush=True)
+    RG, _, ND, NS, _ = host_split.batch_split(M, N, bits, B, True, True)
+    assert ND > 0 and NS * 6 == alone
+    rng = np.random.default_rng(M + B + group)
+    for windows in (alone, alone + 1, alone + 27):
+        block = 16 * RG * (M // (16 * RG) // 2)                      # a workgroup in the middle, and the last one, which may be short
+        counts = rng.integers(0, 4, M)
+        for r0 in (block, M - 1 - (M - 1) % (16 * RG)):
+            heavy, other = (r0 + 16 * group, r0) if r0 + 16 * group < M and group < RG else (r0, r0)
+            counts[r0:min(r0 + 16 * RG, M)] = 0
+            # one window in the other row group (if there is one); in the heavy one rows whose sum is no multiple of 128 columns
+            if other != heavy:
+                counts[other] = 1
+            total = 128 * (windows - (1 if other != heavy else 0)) - 37
+            for k in range(min(16, M - heavy)):
+                counts[heavy + k] = min(total, N)
+                total -= counts[heavy + k]
+        rowptr = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+        cols = np.concatenate([np.sort(rng.choice(N, c, replace=False)) for c in counts]).astype(np.int32)
+        sign = lambda shape: (2 * rng.integers(0, 2, shape) - 1)
+        vals, x = sign(cols.size), sign((N, B))
+        want = np.zeros((M, B), dtype=np.int64)
+        np.add.at(want, np.repeat(np.arange(M), counts), vals[:, None] * x[cols])
+        dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+        y = torch.zeros((M, B), dtype=torch.float16, device="cuda")
+        sq.sqllm_dense_sparse_matvec(M, N, bits, cols.size, B, dev(rng.integers(0, 256, M * N * bits // 8).astype(np.uint8)),
+                                     torch.zeros((M, 1 << bits), dtype=torch.float16, device="cuda"), dev(rowptr), dev(cols),
+                                     dev(vals.astype(np.float16)), dev(x.astype(np.float16)), y)
+        assert np.abs(want).max() <= 2048
+        assert np.array_equal(y.cpu().numpy().astype(np.int64), want), windows
+
+
 @pytest.mark.parametrize("B", [2, 5, 8, 16])
 @pytest.mark.parametrize("M", [64, 5000])                            # 16 and 32 rows per workgroup
 def test_infinite_activation_stays_in_its_tile(M, B):

@@ -63,60 +63,42 @@ def one_column_kernel_reads(M, N, bits, rowptr, R):
                 yield "vals", int(2 * p.min()), int(2 * p.max() + 2)
 
 
-def sixteen_column_kernel_reads(M, N, bits, B, rowptr):
-    RG = 2 if M >= 8192 else 1
-    R = 16 * RG
-    nwin = N // 128
-    NW = min(nwin, 8)
-    K = 1 << bits
+def expansion_reads(M, N, bits):
+    """the index loads of the expansion kernel: per wave, dwords of the pieces of a row (3 bits) or one group of eight weights per lane"""
+    groups, units = N // 8, -(-N // 512)
+    want = max(-(-units // 8), -(-2048 // M))
+    per = -(-units // want)
+    segs = -(-units // per)
+    per = -(-units // segs)                                          # as the kernel re-computes it
     lanes = np.arange(WAVE)
-    r, q = lanes % 16, lanes // 16
-    nnz = int(rowptr[-1])
-    if B in (4, 8, 12, 16):
-        B4 = B // 4
-    elif B == 2:
-        B4 = 5
-    else:
-        B4 = 0
-    BT = 2 if B4 == 5 else 4 * B4
-    for r0 in sorted({0, ((M - 1) // R) * R}):
-        raw_lanes = R * (2 * K) // min(2 * K, 16)
-        unit = min(2 * K, 16)
-        tid = np.arange(raw_lanes)
-        row = np.minimum(r0 + tid * unit // (2 * K), M - 1)
-        off = row * 2 * K + (tid * unit) % (2 * K)
-        yield "lut", int(off.min()), int((off + unit).max())
-        for rg in range(RG):
-            lo = np.minimum(r0 + 16 * rg + r, M)
-            yield "rowptr", int(4 * lo.min()), int(4 * np.minimum(lo + 1, M).max() + 4)
-        for wave in range(NW):
-            last_t = wave + ((nwin - 1 - wave) // NW) * NW
-            for t in sorted({wave, min(wave + NW, last_t), min(wave + 2 * NW, last_t), last_t}):
-                for rg in range(RG):
-                    row = np.minimum(r0 + 16 * rg + r, M - 1)
-                    off = (row * (N * bits // 32) + (4 * t + q) * bits) * 4
-                    yield "qidx", int(off.min()), int((off + 4 * bits).max())
-                wbase = t * 128 * B * 2                            # byte offset of the window in x[N][B]
-                if B4 in (2, 4):
-                    for i in range(B4):
-                        off = wbase + (64 * i + lanes) * 16
-                        yield "x", int(off.min()), int(off.max() + 16)
-                elif B4 > 0:
-                    off = wbase + lanes * 4 * BT
-                    yield "x", int(off.min()), int(off.max() + max(8, 4 * BT))
-                else:
-                    qd = 16 * B
-                    for qq in range(4):
-                        for ii in range(4):
-                            off = wbase + 4 * qq * qd + 4 * np.minimum(64 * ii + lanes, qd - 1)
-                            yield "x", int(off.min()), int(off.max() + 4)
-        if nnz > 0:
-            e4 = 4 * (lanes // 16) + (lanes % 4)
-            for sj in (0, int(rowptr[min(r0 + R, M)]) // 16, (nnz - 1) // 16):
-                pl = np.minimum(16 * sj + e4, nnz - 1)
-                assert (pl >= 0).all()
-                yield "cols", int(4 * pl.min()), int(4 * pl.max() + 4)
-                yield "vals", int(2 * pl.min()), int(2 * pl.max() + 2)
+    for row in sorted({0, M - 1}):
+        base = row * groups * bits
+        for seg in range(segs):
+            u0 = seg * per
+            n = min(per, units - u0)
+            assert 1 <= n <= 8
+            if bits == 3:
+                own = min(n * WAVE, groups - u0 * WAVE)
+                dwords = own // 4 * 3
+                assert own % 4 == 0 and dwords <= 384                # what is staged in LDS
+                for j in range(-(-dwords // 64)):
+                    off = base + 4 * (48 * u0 + np.minimum(64 * j + lanes, dwords - 1))
+                    yield "qidx", int(off.min()), int(off.max()) + 4
+                for k in range(n):                                   # the groups a lane reads from LDS, whole
+                    g = np.minimum(k * WAVE + lanes, own - 1)
+                    d = 3 * g // 4
+                    assert (d < dwords).all() and ((d + 1 < dwords) | (24 * g % 32 + 24 <= 32)).all()
+            else:
+                for k in range(n):
+                    off = base + bits * np.minimum((u0 + k) * WAVE + lanes, groups - 1)
+                    yield "qidx", int(off.min()), int(off.max()) + bits
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("M,N", sorted({s[:2] for s in SHAPES} | {(300, 3712), (700, 2176), (2049, 4224), (256, 4096)}))
+def test_every_load_of_the_expansion_stays_inside_its_array(M, N, bits):
+    for name, lo, hi in expansion_reads(M, N, bits):
+        assert 0 <= lo and hi <= M * N * bits // 8, (name, lo, hi)
 
 
 def plan_sections(M, N, nnz):
@@ -196,7 +178,9 @@ def test_every_load_stays_inside_its_array(M, N, bits, B):
         R = 8 if (N + SLICE - 1) // SLICE >= 8 else 4
         reads = list(one_column_kernel_reads(M, N, bits, rowptr, R)) + list(one_column_kernel_reads(M, N, bits, rowptr, 12 - R))
     else:
-        reads = list(sixteen_column_kernel_reads(M, N, bits, B, rowptr))
+        from test_read_bounds_batch import batch_kernel_reads
+        cols = np.random.default_rng(M).integers(0, N, nnz)
+        reads = list(batch_kernel_reads(M, N, bits, B, rowptr, cols))
     assert len(reads) > 4
     for name, lo, hi in reads:
         assert 0 <= lo and hi <= size[name], (name, lo, hi, size[name])

@@ -51,9 +51,8 @@ def batch_kernel_reads(M, N, bits, B, rowptr, cols):
                 q = np.minimum(gp[rg] + 128 * f + np.arange(128), ge[rg] - 1)
                 yield "cols", 4 * int(q.min()), 4 * int(q.max()) + 4
                 yield "vals", 2 * int(q.min()), 2 * int(q.max()) + 2
-                for c in sorted({int(v) for v in cols[q]}):
-                    first, n = row_reads(c, B)
-                    yield "x", first, first + n
+                first, n = row_reads(cols[q].astype(np.int64), B)
+                yield "x", int(first.min()), int(first.max()) + n
 
 
 @pytest.mark.parametrize("B", range(2, 17))
