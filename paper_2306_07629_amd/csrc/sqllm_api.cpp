@@ -28,7 +28,7 @@ bool misaligned(const void* p, uintptr_t a) { return (reinterpret_cast<uintptr_t
 
 int check_shape(int M, int N, int B) {
     if (M < 0) return fail(SQLLM_ERR_SHAPE, "M = %d is negative", M);
-    // One rule for every width: a lane of the kernels decodes 32 indices and a wave 2048, and the 16-column kernel walks a row in
+    // One rule for every width: a lane of the kernels decodes 32 indices and a wave 2048, and the batch kernel walks a row in
     // windows of 128 columns; 4-bit rows that are whole 16-byte words but not whole 128-column windows (N % 32 == 0 only) are
     // therefore not accepted.  N == 0 is rejected as well: there is no row to read, the caller can clear y itself.
     if (N <= 0 || N % 128 != 0) return fail(SQLLM_ERR_SHAPE, "N = %d must be a positive multiple of 128", N);

@@ -14,9 +14,9 @@
 //     the A operand holds value p in the row of nonzero p (the lanes of the other rows hold zero there).
 //   * Accumulators of the waves are combined through LDS in a fixed order; y is rounded to fp16 once.
 // Bound by what the compute units fetch: every workgroup reads all of x (67 MB through the L2s at 8192x8192 and 16 columns) beside its
-// indices and the gathered rows; LDS and vector ALU are busy for about a third of the launch each.  8192x8192, 3 bits, 16 columns, 0.45 %
-// nonzeros: 15.4 us (21.2 when the sparse term followed the dense one on the same waves and a nonzero's activations were gathered in 8-byte
-// pieces); 13824x5120, 4 bits, 5 columns: 12.4 us (28.7 when batches other than 2, 4, 8, 12 and 16 picked their columns out of LDS with
+// indices and the gathered rows; the LDS is busy for 45 % of the launch, the vector ALU for 35 %.  8192x8192, 3 bits, 16 columns, 0.45 %
+// nonzeros: 15.4 us with the weights in the last-level cache, 18.6 from HBM (21.2 when the sparse term followed the dense one on the same waves and a nonzero's activations were gathered in 8-byte
+// pieces); 13824x5120, 4 bits, 5 columns: 11.9 us, 17.2 from HBM (28.7 when batches other than 2, 4, 8, 12 and 16 picked their columns out of LDS with
 // 16-bit reads, and each of 864 workgroups built its tables through LDS).
 // Lanes of absent columns (r >= B) carry some other column's activations: their products only reach columns that are not stored.
 #include <hip/hip_runtime.h>
@@ -236,7 +236,7 @@ __global__ void __launch_bounds__(kMaxBatchWaves * kWave, batch_waves_per_simd(R
     u32x4 c0[NP], c1[NP];                                            // indices of windows ahead, as fetched
     LaneChunk<BITS> d[RG];                                           // of the current window, the lane's own
     // Activations are requested two windows ahead where the registers for them are free, else one.  (One ahead everywhere: 22016x8192, 3 bits,
-    // 8 columns 40.2 against 35.9 us; smaller layers are the same either way.)
+    // 8 columns 39.6 against 35.1 us; 8192x8192 and smaller are the same either way, but for 12 columns, 17.8 against 18.8.)
     constexpr bool kFar = !(RG == 2 && BT >= 13);
     u32 xb[16], xv0[16], xv1[16];
     int t = wave;

@@ -1171,7 +1171,7 @@ hipError_t launch_matvec_multi(const MultiArgs& m, int bits, int R, hipStream_t 
 }
 
 hipError_t launch_matvec(const MatvecArgs& g, hipStream_t s) {
-    // one column: the vector-ALU kernel; two or more: one launch of the 16-column kernel (every weight is decoded once for all
+    // one column: the vector-ALU kernel; two or more: one launch of the batch kernel (every weight is decoded once for all
     // columns), also without a dense term
     if (g.B == 1 && g.plan && g.qidx && g.nnz > 0 && !g.accumulate)
         return g.bits == 2 ? launch_matvec_planned<2>(g, s) : (g.bits == 3 ? launch_matvec_planned<3>(g, s) : launch_matvec_planned<4>(g, s));

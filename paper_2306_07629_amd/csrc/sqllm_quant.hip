@@ -351,7 +351,7 @@ constexpr int kHeavy = 256;
 // Bound by the latency of the chain boundary -> bucket -> words -> reduction -> division (about 1600 cycles), which the other rows on the
 // unit cover only in part (six at 4096 weights, two at 11008: what their LDS allows).  Against a bitonic sort of the row in LDS and a 64-way
 // search per boundary with reductions over 64 lanes: 4096x4096 at 3 bits 409 -> 101 us (22 updates per row, 1.9 us each over the
-// matrix), 4096x11008 at 4 bits 1164 -> 329 us (32 updates, 5.9 us each).  With a wave per eight boundaries, keys in the words and sums
+// matrix), 4096x11008 at 4 bits 1164 -> 334 us (32 updates, 6.0 us each).  With a wave per eight boundaries, keys in the words and sums
 // exchanged through LDS: 112 and 377 us.
 // Threads T, units of eight weights per thread V, buckets, words per chunk of running sums (twice as many in wide rows), and the waves per
 // SIMD the registers are held down for.
