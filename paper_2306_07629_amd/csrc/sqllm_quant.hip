@@ -363,11 +363,17 @@ struct KmeansShape {
     static constexpr int kChunksPerThread = (kMaxN / CHUNK + T_ - 1) / T_;
     static constexpr size_t sum_bytes(int N) { return (size_t)(N / CHUNK + 1) * 12; }                // also holds (N / (2 CHUNK) + 1) * 20
     static constexpr size_t lds(int N) { return (size_t)(N + kPad) * 4 + sum_bytes(N) + (size_t)(NB + 2) * 2; }
+    // the counters of the heavy buckets, 16 bits for each of a bucket's keys (2^shift, keys have 16 bits), take the place of the sums
+    static constexpr bool counters_fit() {
+        for (int N = 128; N <= kMaxN; N += 128)
+            if (((size_t)((N + kHeavy - 1) / kHeavy) * 2 << (16 - kLogNB)) > sum_bytes(N)) return false;
+        return true;
+    }
 };
 typedef KmeansShape<256, 2, 11, 8, 6> KmeansUpTo4096;                // 26 KB of LDS at 4096 weights: six rows per compute unit
 typedef KmeansShape<512, 3, 12, 8, 4> KmeansUpTo12288;               // 69 KB at 11008: two
 typedef KmeansShape<512, 4, 12, 8, 4> KmeansUpTo16384;
-typedef KmeansShape<1024, 4, 12, 16, 4> KmeansBeyond;                // 145 KB at 28672: one
+typedef KmeansShape<1024, 4, 12, 16, 4> KmeansBeyond;                // 145 KB at 28672: one (two to four registers spilled; 1024x28672 at 4 bits 0.32 ms)
 
 template <int BITS, class S>
 __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(int M, int N, int max_iter, const uint16_t* __restrict__ w, const uint16_t* __restrict__ sens,
@@ -509,6 +515,7 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
     const bool heavy = __builtin_amdgcn_readfirstlane((int)crowded) != 0;   // uniform in the block
     // ---- 4. the words by bucket; those of a heavy bucket by key: a second count, over the 2^shift keys of the bucket, gives their places.
     //         A heavy bucket holds a multiple of kHeavy among its first kHeavy places, which names its counters.
+    static_assert(S::counters_fit(), "");
     if (heavy && shift > 0) {
         u32* sub32 = reinterpret_cast<u32*>(sums);                   // [slots][2^shift] 16-bit counters, then first places
         const uint16_t* sub = reinterpret_cast<const uint16_t*>(sums);
