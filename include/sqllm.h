@@ -105,8 +105,8 @@ int sqllm_dense_sparse_matvec(int M, int N, int bits, long long nnz, int B,
  * once).  The nonzeros of every block of four rows are stored as groups of 16 entries of one row -- column and fp16 value
  * packed into one 32-bit word -- at a position the kernel derives from its workgroup index, with an overflow list for heavy
  * rows.  With a plan the matvec requests its nonzeros at wave start (no row-pointer hop), reads 4 instead of 6 bytes per
- * nonzero (plus the padding of the groups) and sums a row's group with a fixed 16-lane reduction, cheap enough for the dense
- * waves to carry the sparse term.  It pays where the rows' nonzero counts are moderate (a workgroup whose rows hold far more
+ * nonzero (plus the padding of the groups) and adds every product to the lane's own partial sum of its row, cheap enough for
+ * the dense waves to carry the sparse term.  It pays where the rows' nonzero counts are moderate (a workgroup whose rows hold far more
  * than the average goes through the overflow list, a second dependent fetch); a caller may build it per layer or not at all.
  *   sqllm_csr_plan_bytes   size of the plan buffer for (M, N, nnz), a multiple of 256; host pointer `bytes_out`.
  *   sqllm_csr_plan_build   fills `plan` (device, 256-byte aligned, at least that many bytes) from rowptr / cols / vals on

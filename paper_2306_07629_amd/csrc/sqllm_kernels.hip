@@ -29,7 +29,7 @@
 //     atomics are needed and the result does not depend on timing.
 //   * With a plan of the sparse term (a one-time re-layout of the CSR arrays, see PlanView) there is no sparse wave: every
 //     dense wave fetches one 64-entry batch of the workgroup's slot at wave start, gathers its activations once its last
-//     index row has been requested, and sums the four 16-entry row groups of the batch with fixed 16-lane reductions.
+//     index row has been requested, and adds every product to the lane's own partial sum of its row.
 //   * matvec_multi_kernel / matvec_planned_multi_kernel run the workgroups of up to 16 layers in one grid: a workgroup
 //     finds its layer from the first-block table in the kernel arguments and then runs the same per-block code, so every y
 //     is bit for bit that of a launch of its own.
@@ -519,8 +519,9 @@ __device__ __forceinline__ void matvec_block(const MatvecArgs& g, int block, int
 // of R rows serves R / 4 quads, each exactly as a four-row workgroup would (same batches on the same waves in the same order),
 // so the sparse sums -- like the dense ones -- do not depend on R.  Against the
 // CSR arrays this removes the first hop of the dependent chain (row pointers -> columns / values -> gathers), halves the loads
-// per nonzero (column and value share a dword) and replaces the segmented scan by a fixed 16-lane reduction -- cheap enough for
-// the dense waves to carry the sparse term themselves, so a workgroup needs no extra wave.
+// per nonzero (column and value share a dword) and needs no scan: a lane adds its product to one of its R partial sums of the dense
+// term, which are reduced over the wave anyway.  That is cheap enough for the dense waves to carry the sparse term themselves, so a
+// workgroup needs no extra wave.
 struct PlanView {
     const u32* slot_entries;    // [quads][C][64]
     const uint8_t* slot_tags;   // [quads][C][4]  one tag byte per group
@@ -551,25 +552,19 @@ __device__ __forceinline__ PlanView plan_view(const void* plan, int M, long long
     return v;
 }
 
-// sum over each 16-lane row, valid in its lane 15
-__device__ __forceinline__ float row16_sum_to_lane15(float v) {
-    v += dpp_f<kRowShr1>(0.f, v);
-    v += dpp_f<kRowShr2>(0.f, v);
-    v += dpp_f<kRowShr4>(0.f, v);
-    v += dpp_f<kRowShr8>(0.f, v);
-    return v;
-}
-
-// one batch: entry, gathered activation and the tag byte of the lane's group (valid << 7 | (count - 1) << 3 | row) per lane ->
-// the row sums go to the wave's slots
-__device__ __forceinline__ void plan_batch_reduce(u32 entry, u32 xv, u32 tb, int lane, float* __restrict__ slots) {
-    const bool ok = (tb & 0x80u) && (u32)(lane & 15) <= ((tb >> 3) & 15u);
-    float v = ok ? half_bits_to_float((uint16_t)(entry >> 16)) * half_bits_to_float((uint16_t)xv) : 0.f;
-    v = row16_sum_to_lane15(v);
-    // one add per group, in group order (instructions of a wave reach the LDS in order): a fixed order of additions per slot
+// One batch: entry, gathered activation and the tag byte of the lane's group (valid << 7 | (count - 1) << 3 | row) per lane.  Each lane adds
+// its product to its own partial sum of the entry's row, beside what the dense term left there.  Padded lanes add nothing, not a zero
+// product: their column is 0, whose activation may be infinite.  About 17 vector instructions per batch, and none of them waits for the
+// LDS; with a sum over the 16 lanes of a group and an LDS add per group (40 instructions) 8192x8192 took 9.9 us instead of 9.2 (1 % of the
+// rows with 30 % of 0.45 % nonzeros), 4096x4096 at 4 bits 4.65 instead of 4.44, a 65B-shaped MLP pair 42.1 instead of 40.4 and a decode
+// step of four 7B-shaped blocks in groups 122.2 instead of 117.3: a wave's instructions are issued in turn with those of six or seven
+// others, so the workgroups that end last are as late as their chain is long.
+__device__ __forceinline__ void plan_batch_add(u32 entry, u32 xv, u32 tb, int lane, float (&acc)[kPlanRows]) {
+    const int t = (int)tb - 8 * (lane & 15);                         // 128 and above: a valid group that has an entry for the lane
+    const float v = half_bits_to_float((uint16_t)(entry >> 16)) * half_bits_to_float((uint16_t)xv);
+    const u32 row = t >= 128 ? (u32)t & 7u : 8u;
 #pragma unroll
-    for (int gi = 0; gi < 4; ++gi)
-        if (lane == 16 * gi + 15 && (tb & 0x80u)) lds_add(slots + (tb & 7u), v);
+    for (int i = 0; i < kPlanRows; ++i) acc[i] = row == (u32)i ? acc[i] + v : acc[i];
 }
 
 template <int BITS, int R, int D>
@@ -582,8 +577,7 @@ __device__ __forceinline__ void matvec_planned_block(const MatvecArgs& g, int bl
     constexpr int TD = TableShape<BITS>::kTableDwords;
     __shared__ __align__(8) u32 tables[R * TD];
     __shared__ __align__(16) uint16_t raw[R * K];
-    __shared__ float part[kMaxDenseWaves * 4 * R];                   // dense:  [wave][16-lane row][r]
-    __shared__ float spart[kMaxDenseWaves * R];                      // sparse: [wave][r]
+    __shared__ float part[kMaxDenseWaves * 4 * R];                   // [wave][16-lane row][r]
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r0 = block * R;
@@ -591,8 +585,6 @@ __device__ __forceinline__ void matvec_planned_block(const MatvecArgs& g, int bl
     const uint16_t* __restrict__ x = static_cast<const uint16_t*>(g.x);
     const PlanView pv = plan_view(g.plan, g.M, g.nnz, g.plan_c);
     const int n_quads = (g.M + kPlanRows - 1) / kPlanRows;
-    float* myslots = spart + wave * R;
-    if (lane < R) myslots[lane] = 0.f;
 
     // ---- Issue order: (wave 0: fp16 tables), activations, first D rows of the index stream, this wave's slot batches
     constexpr int LPR = TableShape<BITS>::kRowBytes / kRawUnit;
@@ -653,7 +645,7 @@ __device__ __forceinline__ void matvec_planned_block(const MatvecArgs& g, int bl
         build_tables<BITS, R>(tables, raw, lane);
     }
     __syncthreads();
-    float acc[R];
+    float acc[Q][kPlanRows];
     u32 w[16];                                                       // the pairs of the current row; each is replaced by the next row's once its product is formed
     lookup_chunk<BITS>(c[0], tables, w);
     if constexpr (D < R) c[D] = load_chunk_at<BITS>(row_ptr(D), lane_dword);
@@ -698,28 +690,26 @@ __device__ __forceinline__ void matvec_planned_block(const MatvecArgs& g, int bl
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
-            acc[u] = a0 + a1;
+            acc[u / kPlanRows][u % kPlanRows] = a0 + a1;
+            if constexpr (R == 8) asm volatile("" : "+v"(acc[u / kPlanRows][u % kPlanRows]));   // formed here: sunk to its use behind the sparse term, a row's sum keeps its operands alive (125 registers)
         }
         __builtin_amdgcn_sched_barrier(0);
     }
-    row_block_reduce<R>(acc, lane);
-    if (row_block_valid(lane) && (R == 8 || !(lane & 8))) part[(wave * 4 + (lane >> 4)) * R + row_block_class<R>(lane)] = acc[0];
     // ---- sparse term, quad by quad: this wave's slot batch, then its share of the quad's overflow batches (batches wave, wave + W,
     // wave + 2 W, ... in this order whatever UP and R are)
     constexpr int UO = 8;                                            // batches per wave and round in the loop for very heavy rows
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-        float* qslots = myslots + q * kPlanRows;
         const bool have = block * Q + q < n_quads;                   // uniform; the last workgroup of an odd number of quads has one
         const int nb = have ? ov_nb[q] : 0, first = ov_first[q];
-        if (wave < pv.C && have) plan_batch_reduce(ent[q], sx[q], tags[q], lane, qslots);     // uniform
+        if (wave < pv.C && have) plan_batch_add(ent[q], sx[q], tags[q], lane, acc[q]);        // uniform
         if (wave < nb) {                                                                      // uniform
             u32 ox[UP];
 #pragma unroll
             for (int k = 0; k < UP; ++k) ox[k] = x[oe[q][k] & 0x7FFFu];
 #pragma unroll
             for (int k = 0; k < UP; ++k)
-                if (wave + k * W < nb) plan_batch_reduce(oe[q][k], ox[k], ot[q][k], lane, qslots);
+                if (wave + k * W < nb) plan_batch_add(oe[q][k], ox[k], ot[q][k], lane, acc[q]);
         }
         // what a very heavy row leaves after that: UO batches per wave and round, all requested before the first is used (the
         // workgroup that owns such a row ends last, and every round costs it two memory latencies)
@@ -735,13 +725,18 @@ __device__ __forceinline__ void matvec_planned_block(const MatvecArgs& g, int bl
             for (int k = 0; k < UO; ++k) x2[k] = x[e2[k] & 0x7FFFu];
 #pragma unroll
             for (int k = 0; k < UO; ++k)
-                if (ob + k * W < nb) plan_batch_reduce(e2[k], x2[k], t2[k], lane, qslots);
+                if (ob + k * W < nb) plan_batch_add(e2[k], x2[k], t2[k], lane, acc[q]);
         }
     }
+    float sum[R];
+#pragma unroll
+    for (int u = 0; u < R; ++u) sum[u] = acc[u / kPlanRows][u % kPlanRows];
+    row_block_reduce<R>(sum, lane);
+    if (row_block_valid(lane) && (R == 8 || !(lane & 8))) part[(wave * 4 + (lane >> 4)) * R + row_block_class<R>(lane)] = sum[0];
     __syncthreads();
     uint16_t* __restrict__ y = static_cast<uint16_t*>(g.y);
     if (wave == 0) {
-        const float s = block_row_total<R>(part, 4 * W, spart, W, lane);
+        const float s = block_row_total<R>(part, 4 * W, part, 0, lane);
         const int row = lane >> 3;
         if ((lane & 7) == 0 && row < nrows) y[r0 + row] = float_to_half_bits(s);
     }
