@@ -24,9 +24,8 @@
 //     block's rows while the dense waves stream.  The nonzeros of R consecutive rows are one contiguous
 //     range of the CSR arrays; lane l takes nonzeros l, l + 64, ... of that range whatever rows they fall in
 //     (equal work per lane), finds each one's row by comparing against the R + 1 row pointers held in
-//     scalar registers, and the products are combined per row with a segmented scan built from DPP moves.
-//     Only the last lane of each row segment touches the row's LDS accumulator, so no floating-point
-//     atomics are needed and the result does not depend on timing.
+//     scalar registers, and adds the product to the lane's own partial sum of that row; the R partial sums
+//     are reduced over the wave once.  No floating-point atomics, and the result does not depend on timing.
 //   * With a plan of the sparse term (a one-time re-layout of the CSR arrays, see PlanView) there is no sparse wave: every
 //     dense wave fetches one 64-entry batch of the workgroup's slot at wave start, gathers its activations once its last
 //     index row has been requested, and adds every product to the lane's own partial sum of its row.
@@ -47,8 +46,6 @@ namespace sqllm {
 // DPP controls (gfx9 encoding)
 constexpr int kQuadXor1 = 0xB1;        // quad_perm:[1,0,3,2]
 constexpr int kQuadXor2 = 0x4E;        // quad_perm:[2,3,0,1]
-constexpr int kRowShr1 = 0x111, kRowShr2 = 0x112, kRowShr4 = 0x114, kRowShr8 = 0x118;
-constexpr int kWaveShl1 = 0x130;       // lane i reads lane i + 1
 constexpr int kRowRor4 = 0x124, kRowRor8 = 0x128;
 constexpr int kRowMirror = 0x140, kRowHalfMirror = 0x141;
 constexpr int kRowBcast15 = 0x142, kRowBcast31 = 0x143;
@@ -57,11 +54,6 @@ template <int CTRL, int ROW_MASK = 0xF>
 __device__ __forceinline__ float dpp_f(float old, float v) {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, old), __builtin_bit_cast(int, v), CTRL, ROW_MASK, 0xF, false));
 }
-template <int CTRL, int ROW_MASK = 0xF>
-__device__ __forceinline__ int dpp_i(int old, int v) {
-    return __builtin_amdgcn_update_dpp(old, v, CTRL, ROW_MASK, 0xF, false);
-}
-
 // Sum over the 64 lanes without LDS traffic; the total is valid in lane 63.
 __device__ __forceinline__ float wave_sum_to_lane63(float v) {
     v += dpp_f<kQuadXor1>(0.f, v);
@@ -228,12 +220,11 @@ __device__ __forceinline__ int row_block_class(int lane) { return (C == 8 && (la
 // CSR arrays.  It is cut into batches of 64; batch b goes to wave (b mod NW) and lane l of that wave takes
 // nonzero P0 + 64 b + l, whatever row it falls in -- every lane of the block gets the same amount of work
 // and a heavy row is spread over all waves.  A wave handles up to UB batches per round: first all column /
-// value loads, then all activation gathers, then the reduction, so a round costs two memory round trips
-// (which the dense decode of the same wave overlaps).  Products are combined per row inside the wave (plain
-// DPP reduction when a batch lies in one row, segmented DPP scan otherwise) and only the last lane of a row
-// segment adds to the wave's private LDS slot of that row: no floating-point atomics, fixed summation order.
-// (One LDS float add per nonzero instead of the scan was measured: lanes meeting in a slot are served one after the other,
-// 22016x8192 fused 19.4 -> 24.9 us.)
+// value loads, then all activation gathers, then the sums, so a round costs two memory round trips
+// (which the dense decode of the same wave overlaps).  Every lane adds to its own partial sums of the R rows: fixed order, no atomics, no
+// scan.  (A segmented scan over the lanes with one LDS add per row segment before: 22016x8192, 1 % of the rows with 30 % of the nonzeros,
+// 21.1 us against 19.9, 11008x4096 7.6 against 7.2; one LDS float add per nonzero: lanes meeting in a slot are served one after the other,
+// another 5.5 us at 22016x8192.)
 template <int UB>
 struct SparseRegs {
     int c[UB];
@@ -265,67 +256,30 @@ __device__ __forceinline__ void sparse_issue_gathers(const uint16_t* __restrict_
     for (int k = 0; k < UB; ++k) q.xv[k] = x[q.c[k]];
 }
 
-// LDS float add without a returned value: queued in order behind the wave's earlier LDS operations.  Only one
-// wave ever touches a given slot and its lanes address distinct slots, so the summation order is fixed.
-__device__ __forceinline__ void lds_add(float* slot, float v) { (void)__hip_atomic_fetch_add(slot, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
-
 template <int R, int UB>
-__device__ __forceinline__ void sparse_reduce(const SparseRange& sr, const int (&rp)[R + 1], int b0, int NW, int lane, const SparseRegs<UB>& q, float* __restrict__ slots) {
-    int carry_row = -1;                                              // uniform: row whose sum is still in registers
-    float carry = 0.f;
+__device__ __forceinline__ void sparse_accumulate(const SparseRange& sr, const int (&rp)[R + 1], int b0, int NW, int lane, const SparseRegs<UB>& q, float (&acc)[R]) {
 #pragma unroll
     for (int k = 0; k < UB; ++k) {
         const int b = b0 + k * NW;
         if (b < sr.nbatch) {                                         // uniform
-            const int p_first = sr.P0 + b * kWave, p_last = min(p_first + kWave, sr.P1) - 1;
-            const int p = p_first + lane;
-            const bool ok = p <= p_last;
-            float v = ok ? half_bits_to_float(q.vb[k]) * half_bits_to_float(q.xv[k]) : 0.f;
-            int row_first = 0, row_last = 0;                         // rows of the batch's first / last nonzero
+            const int p = sr.P0 + b * kWave + lane;
+            const float v = half_bits_to_float(q.vb[k]) * half_bits_to_float(q.xv[k]);
+            int row = p < sr.P1 ? 0 : R;                             // number of i in 1..R-1 with rp[i] <= p; R: nothing for this lane
 #pragma unroll
-            for (int i = 1; i < R; ++i) { row_first += (p_first >= rp[i]) ? 1 : 0; row_last += (p_last >= rp[i]) ? 1 : 0; }
-            if (row_first == row_last) {
-                // the whole batch lies in one row: plain wave reduction, summed in registers across batches
-                if (carry_row != row_first) {
-                    if (carry_row >= 0 && lane == kWave - 1) lds_add(slots + carry_row, carry);
-                    carry_row = row_first;
-                    carry = 0.f;
-                }
-                carry += wave_sum_to_lane63(v);
-            } else {
-                int row = 0;                                         // number of i in 1..R-1 with rp[i] <= p
+            for (int i = 1; i < R; ++i) row += (p >= rp[i]) ? 1 : 0;
 #pragma unroll
-                for (int i = 1; i < R; ++i) row += (p >= rp[i]) ? 1 : 0;
-                if (!ok) row = R;                                    // idle lanes form their own segment
-                // segmented inclusive scan (rows are non-decreasing with the lane index)
-#define SQ_SEG_STEP(CTRL, MASK)                                                        \
-                {                                                                      \
-                    const int r_up = dpp_i<CTRL, MASK>(-1, row);                       \
-                    const float v_up = dpp_f<CTRL, MASK>(0.f, v);                      \
-                    v += (r_up == row) ? v_up : 0.f;                                   \
-                }
-                SQ_SEG_STEP(kRowShr1, 0xF)
-                SQ_SEG_STEP(kRowShr2, 0xF)
-                SQ_SEG_STEP(kRowShr4, 0xF)
-                SQ_SEG_STEP(kRowShr8, 0xF)
-                SQ_SEG_STEP(kRowBcast15, 0xA)
-                SQ_SEG_STEP(kRowBcast31, 0xC)
-#undef SQ_SEG_STEP
-                const int row_next = dpp_i<kWaveShl1>(-2, row);
-                if (ok && row_next != row) lds_add(slots + row, v);  // last lane of its row segment
-            }
+            for (int i = 0; i < R; ++i) acc[i] = row == i ? acc[i] + v : acc[i];
         }
     }
-    if (carry_row >= 0 && lane == kWave - 1) lds_add(slots + carry_row, carry);
 }
 
 template <int R, int U>
 __device__ __forceinline__ void sparse_round(const MatvecArgs& g, const uint16_t* __restrict__ x, const SparseRange& sr, const int (&rp)[R + 1],
-                                             int b0, int NW, int lane, float* __restrict__ slots) {
+                                             int b0, int NW, int lane, float (&acc)[R]) {
     SparseRegs<U> q;
     sparse_issue_cols_vals<U>(g, sr, b0, NW, lane, q);
     sparse_issue_gathers<U>(x, q);
-    sparse_reduce<R, U>(sr, rp, b0, NW, lane, q, slots);
+    sparse_accumulate<R, U>(sr, rp, b0, NW, lane, q, acc);
 }
 
 // ---------------------------------------------------------------------------------------------- the matvec kernel (one activation column)
@@ -347,15 +301,15 @@ __device__ __forceinline__ void load_row_pointers(const MatvecArgs& g, int r0, i
 
 // The work of one workgroup: rows [R block, R block + R) of layer g, carried by the workgroup's first NW waves
 // (W dense waves, then the sparse wave).
-// Total of one output row over the workgroup's partial sums: `na` values a[i * R + row] followed by `nb` values b[i * R + row].
+// Total of one output row over the workgroup's n partial sums a[i * R + row].
 // Eight lanes per row (lane = 8 row + p) each add every eighth value in order, then the eight are combined by a butterfly whose
-// every lane forms the same sums; the order depends on the counts only, not on R.  Valid in all eight lanes of a row < R.
+// every lane forms the same sums; the order depends on the count only, not on R.  Valid in all eight lanes of a row < R.
 template <int R>
-__device__ __forceinline__ float block_row_total(const float* __restrict__ a, int na, const float* __restrict__ b, int nb, int lane) {
+__device__ __forceinline__ float block_row_total(const float* __restrict__ a, int n, int lane) {
     const int row = lane >> 3, p = lane & 7;
     float s = 0.f;
     if (row < R) {
-        for (int i = p; i < na + nb; i += 8) s += i < na ? a[i * R + row] : b[(i - na) * R + row];
+        for (int i = p; i < n; i += 8) s += a[i * R + row];
     }
     s += dpp_f<kQuadXor1>(0.f, s);
     s += dpp_f<kQuadXor2>(0.f, s);
@@ -372,8 +326,7 @@ __device__ __forceinline__ void matvec_block(const MatvecArgs& g, int block, int
     constexpr int TD = TableShape<BITS>::kTableDwords;
     __shared__ __align__(8) u32 tables[R * TD];
     __shared__ __align__(16) uint16_t raw[R * K];
-    __shared__ float part[kMaxDenseWaves * 4 * R];                   // dense:  [wave][16-lane row][r]
-    __shared__ float spart[(kMaxDenseWaves + 1) * R];                // sparse: [wave][r]
+    __shared__ float part[(kMaxDenseWaves + 1) * 4 * R];             // [wave][16-lane row][r]
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform, and known to be
     const bool dense = g.qidx != nullptr, sparse = g.nnz > 0;
@@ -385,9 +338,8 @@ __device__ __forceinline__ void matvec_block(const MatvecArgs& g, int block, int
     int rp[R + 1];
     SparseRange sr;
     load_row_pointers<R>(g, r0, nrows, sparse, rp, sr);              // consumed late by the dense waves
-    float* myslots = spart + wave * R;
-    if (lane < R) myslots[lane] = 0.f;
     int next_batch = 0;                                              // first batch not yet handled (uniform)
+    float acc[R];
 
     if (wave < W) {
         // ---- dense wave.  Issue order: (wave 0: fp16 tables), activations, first D rows of the index stream.
@@ -438,7 +390,6 @@ __device__ __forceinline__ void matvec_block(const MatvecArgs& g, int block, int
         __syncthreads();
         // software pipeline: the look-ups of row u + 1 are in flight while the products of row u are formed;
         // row u + D of the index stream is requested when row u has been handed to the look-ups
-        float acc[R];
         u32 w[16];
         lookup_chunk<BITS>(c[0], tables, w);
         if constexpr (D < R) c[D] = load_chunk_at<BITS>(row_ptr(D), lane_dword);
@@ -464,15 +415,15 @@ __device__ __forceinline__ void matvec_block(const MatvecArgs& g, int block, int
                     }
                 }
                 acc[u] = a0 + a1;
+                asm volatile("" : "+v"(acc[u]));                     // formed here: sunk to its use behind the sparse term, a row's sum keeps its operands alive
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        // reduce the R row sums jointly over each 16-lane row of the wave
-        row_block_reduce<R>(acc, lane);
-        if (row_block_valid(lane) && (R == 8 || !(lane & 8))) part[(wave * 4 + (lane >> 4)) * R + row_block_class<R>(lane)] = acc[0];
         next_batch = UB;                                             // the sparse wave takes batches 0 .. UB-1
     } else {
         // ---- sparse wave(s)
+#pragma unroll
+        for (int u = 0; u < R; ++u) acc[u] = 0.f;
         if (dense) {
             // columns and values of the first batches are requested BEFORE the dense waves' table barrier: the row pointers arrive
             // together with the fp16 tables, so the second hop of the chain (row pointers -> columns / values -> gathers -> scan)
@@ -482,13 +433,13 @@ __device__ __forceinline__ void matvec_block(const MatvecArgs& g, int block, int
                 sparse_issue_cols_vals<UB>(g, sr, 0, 1, lane, q);
                 __syncthreads();
                 sparse_issue_gathers<UB>(x, q);
-                sparse_reduce<R, UB>(sr, rp, 0, 1, lane, q, myslots);
+                sparse_accumulate<R, UB>(sr, rp, 0, 1, lane, q, acc);
             } else if (sr.nbatch > 0) {
                 SparseRegs<2> q;
                 sparse_issue_cols_vals<2>(g, sr, 0, 1, lane, q);
                 __syncthreads();
                 sparse_issue_gathers<2>(x, q);
-                sparse_reduce<R, 2>(sr, rp, 0, 1, lane, q, myslots);
+                sparse_accumulate<R, 2>(sr, rp, 0, 1, lane, q, acc);
             } else {
                 __syncthreads();
             }
@@ -498,13 +449,16 @@ __device__ __forceinline__ void matvec_block(const MatvecArgs& g, int block, int
     // ---- what is left of the sparse term (everything in a sparse-only launch): batch b goes to wave
     //      (b - next_batch) mod NW, UB batches per wave and round
     for (int b0 = next_batch + wave; b0 < sr.nbatch; b0 += NW * UB)   // uniform
-        sparse_round<R, UB>(g, x, sr, rp, b0, NW, lane, myslots);
+        sparse_round<R, UB>(g, x, sr, rp, b0, NW, lane, acc);
+    // reduce the R row sums jointly over each 16-lane row of the wave
+    row_block_reduce<R>(acc, lane);
+    if (row_block_valid(lane) && (R == 8 || !(lane & 8))) part[(wave * 4 + (lane >> 4)) * R + row_block_class<R>(lane)] = acc[0];
     __syncthreads();
 
     // combine the slice sums and the sparse partial sums in a fixed order, round once
     uint16_t* __restrict__ y = static_cast<uint16_t*>(g.y);
     if (wave == 0) {
-        float s = block_row_total<R>(part, 4 * W, spart, sparse ? NW : 0, lane);
+        float s = block_row_total<R>(part, 4 * NW, lane);
         const int row = lane >> 3;
         if ((lane & 7) == 0 && row < nrows) {
             if (g.accumulate) s += half_bits_to_float(y[r0 + row]);
@@ -736,7 +690,7 @@ __device__ __forceinline__ void matvec_planned_block(const MatvecArgs& g, int bl
     __syncthreads();
     uint16_t* __restrict__ y = static_cast<uint16_t*>(g.y);
     if (wave == 0) {
-        const float s = block_row_total<R>(part, 4 * W, part, 0, lane);
+        const float s = block_row_total<R>(part, 4 * W, lane);
         const int row = lane >> 3;
         if ((lane & 7) == 0 && row < nrows) y[r0 + row] = float_to_half_bits(s);
     }
