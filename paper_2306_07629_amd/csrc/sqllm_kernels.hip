@@ -363,12 +363,10 @@ __device__ __forceinline__ void matvec_block(const MatvecArgs& g, int block, int
         const u32 j0c = live ? j0 : (u32)g.N - kLaneElems;
         u32 xr[16];
         load_x(x, j0c, xr);
-        const size_t row_dwords = (size_t)g.N * BITS / 32;
+        const u32 row_bytes = (u32)g.N / 8u * BITS;
         const u32 lane_dword = (j0c >> 5) * BITS;                    // the lane's 32 indices inside a row of the index stream
-        const u32* __restrict__ qrow0 = static_cast<const u32*>(g.qidx);
-        auto row_ptr = [&](int u) {
-            const u32 row = (u32)__builtin_amdgcn_readfirstlane(min(r0 + u, g.M - 1));   // uniform: the 64-bit product stays on the scalar unit
-            return qrow0 + (size_t)row * row_dwords;
+        auto row_ptr = [&](int u) {                                  // uniform: the scalar unit works it out
+            return reinterpret_cast<const u32*>(static_cast<const char*>(g.qidx) + (size_t)(u32)min(r0 + u, g.M - 1) * row_bytes);
         };
         LaneChunk<BITS> c[R];
 #pragma unroll
@@ -560,12 +558,10 @@ __device__ __forceinline__ void matvec_planned_block(const MatvecArgs& g, int bl
     const u32 j0c = live ? j0 : (u32)g.N - kLaneElems;
     u32 xr[16];
     load_x(x, j0c, xr);
-    const size_t row_dwords = (size_t)g.N * BITS / 32;
+    const u32 row_bytes = (u32)g.N / 8u * BITS;
     const u32 lane_dword = (j0c >> 5) * BITS;                        // the lane's 32 indices inside a row of the index stream
-    const u32* __restrict__ qrow0 = static_cast<const u32*>(g.qidx); // row pointers below are uniform: r0 and M are
-    auto row_ptr = [&](int u) {
-        const u32 row = (u32)__builtin_amdgcn_readfirstlane(min(r0 + u, g.M - 1));   // keeps the 64-bit product on the scalar unit
-        return qrow0 + (size_t)row * row_dwords;
+    auto row_ptr = [&](int u) {                                      // uniform: the scalar unit works it out
+        return reinterpret_cast<const u32*>(static_cast<const char*>(g.qidx) + (size_t)(u32)min(r0 + u, g.M - 1) * row_bytes);
     };
     LaneChunk<BITS> c[R];
 #pragma unroll
@@ -645,7 +641,7 @@ __device__ __forceinline__ void matvec_planned_block(const MatvecArgs& g, int bl
                 }
             }
             acc[u / kPlanRows][u % kPlanRows] = a0 + a1;
-            if constexpr (R == 8) asm volatile("" : "+v"(acc[u / kPlanRows][u % kPlanRows]));   // formed here: sunk to its use behind the sparse term, a row's sum keeps its operands alive (125 registers)
+            asm volatile("" : "+v"(acc[u / kPlanRows][u % kPlanRows]));   // formed here: sunk to its use behind the sparse term, a row's sum keeps its operands alive (125 registers)
         }
         __builtin_amdgcn_sched_barrier(0);
     }
