@@ -311,15 +311,14 @@ struct Moment<true> {
 };
 template <int W> struct U32Vec { typedef u32 type __attribute__((ext_vector_type(W))); };
 template <int W> using u32vec = typename U32Vec<W>::type;
-// Largest key k with 2 w(k) <= t, t between the smallest and the largest fp16 value doubled (the correction steps make it exact whatever
-// the conversion rounds to).
+// Largest key k with 2 w(k) <= t, t between the smallest and the largest fp16 value doubled.  Half of t rounded to zero is that weight unless
+// it lies above (t negative and no fp16 number doubled): then the next one down, whose bits are one higher.  0 * t is added so that -0
+// counts as +0, the higher of the two keys of zero.
 __device__ __forceinline__ u32 key_below(float t) {
     typedef __fp16 fp16x2 __attribute__((ext_vector_type(2)));
-    const fp16x2 h = __builtin_amdgcn_cvt_pkrtz(0.5f * t, 0.f);
-    u32 k = half_key(__builtin_bit_cast(u32, h) & 0xFFFFu);
-    if (t < 2.0f * half_bits_to_f32(key_half(k))) --k;
-    if (!(t < 2.0f * half_bits_to_f32(key_half(k + 1)))) ++k;
-    return k;
+    const float half = __builtin_fmaf(0.5f, t, 0.f);
+    const u32 h = __builtin_bit_cast(u32, __builtin_amdgcn_cvt_pkrtz(half, 0.f));
+    return half_key(h + (half_bits_to_f32(h) > half ? 1u : 0u));
 }
 
 // A word of the row in LDS: fp16 bits << 16 | sensitivity
@@ -328,6 +327,18 @@ __device__ __forceinline__ float weight24(u32 word) { return half_bits_to_f32(wo
 // to integers, a finite one.
 constexpr u32 kBeyondNarrow = kNarrowEnd << 16, kBeyondWide = 0x7C000000u;   // 127.9375, +infinity
 constexpr int kPad = 16;                                             // words of it behind the row: a round of the iterations ends there at the latest
+// float(double(sum * 2^-24) / double(mass)), mass > 0, as one correctly rounded division and one rounding to fp32 give it.  The quotient below
+// is within a unit of the last place of the correctly rounded one (a reciprocal good to 2^-24, one Newton step, one correction), which
+// rounds to another float only next to the middle between two; `near` says so.
+__device__ __forceinline__ float mean_of(double sum, u32 mass, bool& near) {
+    const double d = (double)mass;
+    double r = __builtin_amdgcn_rcp(d);
+    r = __builtin_fma(__builtin_fma(-d, r, 1.0), r, r);
+    double q = sum * r;
+    q = __builtin_fma(__builtin_fma(-d, q, sum), r, q);
+    near = ((u32)__builtin_bit_cast(u64, q) & 0x1FFFFFFFu) - 0x0FFFFFF8u <= 16u;   // the 29 bits that fp32 drops
+    return (float)(q * 5.9604644775390625e-08);
+}
 // Words from which a bucket is sorted and searched instead of read through.  A round reads 16 words and a bisection step one, in about the
 // same time: at 128 words rows of 8-bit levels, whose fullest buckets hold 137, lost (4096x11008 at 4 bits 751 us, 639 at 256 words, 633
 // without); at 512 rows with buckets in between lost (8192x1024 at 2 bits, two values: 362 us, 165 at 256 words).
@@ -348,8 +359,10 @@ constexpr int kHeavy = 256;
 //     the order of their keys, and an update bisects them instead of reading them through (nine tenths zeros, 32 updates: 4096x11008 at 4
 //     bits 0.84 ms, read through 16.3; 1024x28672 0.52 ms, read through 18.7).
 // The decisions and integers are those of a pass over all weights per update, hence the same result.
-// Bound by the latency of the chain boundary -> bucket -> words -> reduction -> division (about 1600 cycles), which the other rows on the
-// unit cover only in part (six at 4096 weights, two at 11008: what their LDS allows).  Against a bitonic sort of the row in LDS and a 64-way
+// Bound by the latency of the chain boundary -> bucket -> words -> reduction -> division (1150 cycles at 4096 weights and 8 entries, 1480 at
+// 11008 and 16), which the other rows on the unit cover only in part (six at 4096 weights, two at 11008: what their LDS allows).  It was 1570
+// and 1920 with the key of a boundary corrected in two steps, the two bucket ends read one after the other under a branch, a test in front of
+// the first round, a full fp64 division behind the test for the end, and no priority over the waves of other rows.  Against a bitonic sort of the row in LDS and a 64-way
 // search per boundary with reductions over 64 lanes: 4096x4096 at 3 bits 409 -> 101 us (22 updates per row, 1.9 us each over the
 // matrix), 4096x11008 at 4 bits 1164 -> 334 us (32 updates, 6.0 us each).  With a wave per eight boundaries, keys in the words and sums
 // exchanged through LDS: 112 and 377 us.
@@ -651,11 +664,13 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
         const Mom all1 = C1[nchunks];
         float cen = cen_s[min(k, K - 1)];
         u32 prev = 0xFFFFFFFFu;
+        __builtin_amdgcn_s_setprio(3);                               // a chain of single instructions beside blocks that have many in flight
         for (;;) {
             const float t = __fadd_rn(cen, __builtin_bit_cast(float, dpp_u32<kRowShl1>(__builtin_bit_cast(u32, cen), __builtin_bit_cast(u32, cen))));
             const u32 kk = key_below(t);
             const u32 b = (umin(umax(kk, kmin), kmax) - kmin) >> shift;
-            u32 p0 = kk < kmin ? 0u : start[b], p1 = kk < kmin ? 0u : start[b + 1];
+            u32 p0 = start[b], p1 = start[b + 1];                    // both reads at once, and no branch around them
+            if (kk < kmin) p0 = p1 = 0;
             // 2 w <= t, with both sides scaled exactly.  It holds for all words in front of the bucket and for none behind it, which a lane
             // may read as well; behind the last word lie kPad that are above every t.
             const float t24 = t * 8388608.0f;
@@ -675,7 +690,8 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
             const Mom c1 = C1[j0 / CW];
             u32 pos = 0, s0 = 0;
             Mom s1 = Mom::zero();
-            for (u32 j = j0 + WPL * sub; __any(j - WPL * sub < p1); j += 16) {
+            u32 j = j0 + WPL * sub;
+            do {                                                     // most updates need one round
                 u32 v[WPL];
                 *reinterpret_cast<u32vec<WPL>*>(v) = *reinterpret_cast<const u32vec<WPL>*>(A + umin(j, N + kPad - WPL));
 #pragma unroll
@@ -687,20 +703,27 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
                     s0 += s;
                     s1 = s1 + Mom::product(w24, v[i] >> 16, s);
                 }
-            }
+                j += 16;
+            } while (__builtin_amdgcn_ballot_w64(j - WPL * sub < p1) != 0);
             pos = strided_sum<COLS>(Plain{pos}).v + j0;
             s0 = strided_sum<COLS>(Plain{s0}).v + c0;
             s1 = strided_sum<COLS>(s1) + c1;
-            if (!__any(boundary && pos != prev) || it == max_iter) break;   // uniform
-            prev = pos;
             if (!boundary) { s0 = all0; s1 = all1; }
             const Plain below0 = Plain{s0}.template moved<kRowShr1>();
             const Mom below1 = s1.template moved<kRowShr1>();
-            const u32 m0 = s0 - (k == 0 ? 0u : below0.v);
-            const Mom m1 = k == 0 ? s1 : s1 - below1;
-            if (m0 > 0) cen = (float)(m1.value() * 5.9604644775390625e-08 / (double)m0);
+            // 16 lanes: nothing moves into lane 0
+            const u32 m0 = s0 - (COLS == 8 && k == 0 ? 0u : below0.v);
+            const Mom m1 = COLS == 8 && k == 0 ? s1 : s1 - below1;
+            bool near;
+            const double sum = m1.value();
+            float next = mean_of(sum, m0, near);
+            if (__builtin_amdgcn_ballot_w64(boundary && pos != prev) == 0 || it == max_iter) break;   // uniform; behind the means, whose chain it does not lengthen
+            if (__builtin_amdgcn_ballot_w64(near && m0 > 0) != 0) next = (float)(sum * 5.9604644775390625e-08 / (double)m0);
+            prev = pos;
+            if (m0 > 0) cen = next;
             ++it;
         }
+        __builtin_amdgcn_s_setprio(0);
         if (lane < K) cen_s[lane] = cen;
     };
     if (n_dense > 0) {
