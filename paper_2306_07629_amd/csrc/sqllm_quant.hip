@@ -373,6 +373,9 @@ struct KmeansShape {
     static constexpr int T = T_, V = V_, kWavesPerSimd = WAVES, kChunk = CHUNK;
     static constexpr int kMaxN = 8 * T_ * V_ < 28672 ? 8 * T_ * V_ : 28672;
     static constexpr int kLogNB = LOG_NB, NB = 1 << LOG_NB;
+    // The CSR entries of a row are written while wave 0 iterates, by the threads behind it: one per 32 columns.  Where those are too few, and
+    // with 1024 threads, where the two registers it takes until then are spilled (1024x28672 341 us against 330), they are written at once.
+    static constexpr int kFirst = T_ <= 512 && kMaxN / 32 <= T_ - 64 ? 64 : 0;
     static constexpr int kChunksPerThread = (kMaxN / CHUNK + T_ - 1) / T_;
     static constexpr size_t sum_bytes(int N) { return (size_t)(N / CHUNK + 1) * 12; }                // also holds (N / (2 CHUNK) + 1) * 20
     static constexpr size_t lds(int N) { return (size_t)(N + kPad) * 4 + sum_bytes(N) + (size_t)(NB + 2) * 2; }
@@ -472,8 +475,18 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
             most = umax(most, r);
         }
     if (most >= kHeavy - 1) crowded = 1;
-    const u32 ext = tid < N / 32 ? emask[tid] : 0u;
+    const u32 ext = tid >= S::kFirst && tid - S::kFirst < N / 32 ? emask[tid - S::kFirst] : 0u;
     __syncthreads();
+    // CSR entries of the row, columns ascending
+    int entry = 0;
+    auto write_entries = [&]() {
+        for (u32 m = ext; m; m &= m - 1) {
+            const int j = 32 * (tid - S::kFirst) + __builtin_ctz(m);
+            cols[entry] = j;
+            vals[entry] = wrow[j];
+            ++entry;
+        }
+    };
     // ---- 3. one scan over the threads for the places of the buckets (low half) and of the CSR entries (high half); both are below 2^15
     int n_dense;
     {
@@ -515,14 +528,8 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
             run = second + (pair[k] >> 16);
         }
         if (tid == 0) start32[NB / 2] = (u32)n_dense;
-        // CSR entries of the row, columns ascending
-        int o = rowptr[row] + (int)(before >> 16);
-        for (u32 m = ext; m; m &= m - 1) {
-            const int j = 32 * tid + __builtin_ctz(m);
-            cols[o] = j;
-            vals[o] = wrow[j];
-            ++o;
-        }
+        entry = rowptr[row] + (int)(before >> 16);
+        if constexpr (S::kFirst == 0) write_entries();
     }
     __syncthreads();
     const bool heavy = __builtin_amdgcn_readfirstlane((int)crowded) != 0;   // uniform in the block
@@ -638,17 +645,29 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
             const int kr = min(k0, K - 1);
             const int r = (int)(((u64)(2 * kr + 1) * (u64)n_dense) / (u64)(2 * K));
             const int b0 = (int)rank_bucket[kr], p0 = (int)start[b0], p1 = (int)start[b0 + 1];
-            const u32 first = half_key(A[min(p0 + n, N - 1)] >> 16);
+            constexpr int HELD = 4;                                  // words of the bucket a lane holds in registers: 32 in all (read again for
+                                                                     // every bit of the key: 2800 instead of 1800 cycles at 4096 columns)
+            u32 held[HELD];
+#pragma unroll
+            for (int i = 0; i < HELD; ++i) {
+                const int j = p0 + n + 8 * i;
+                const u32 key = half_key(A[min(j, N - 1)] >> 16);
+                held[i] = j < p1 ? key : 0xFFFFFFFFu;                // above every candidate
+            }
             const bool sorted = CROWDED && p1 - p0 >= kHeavy;
+            const bool more = __builtin_amdgcn_ballot_w64(!sorted && p1 - p0 > 8 * HELD) != 0;   // uniform
             u32 key = sorted ? half_key(A[r] >> 16) : kmin + ((u32)b0 << shift);
             for (int b = shift - 1; b >= 0; --b) {
                 const u32 cand = key + (1u << b);                    // no more than r - p0 words below cand: the key is cand or above
-                u32 below = 0, v = first;
-                for (int j0 = p0; __any(!sorted && j0 < p1); j0 += 8) {
-                    const int j = j0 + n;
-                    if (j0 != p0) v = half_key(A[min(j, N - 1)] >> 16);
-                    below += j < p1 && v < cand ? 1u : 0u;
-                }
+                u32 below = 0;
+#pragma unroll
+                for (int i = 0; i < HELD; ++i) below += held[i] < cand ? 1u : 0u;
+                if (more)
+                    for (int j0 = p0 + 8 * HELD; __any(!sorted && j0 < p1); j0 += 8) {
+                        const int j = j0 + n;
+                        const u32 v = half_key(A[min(j, N - 1)] >> 16);
+                        below += j < p1 && v < cand ? 1u : 0u;
+                    }
                 if (!sorted && (int)group_sum(Plain{below}).v <= r - p0) key = cand;
             }
             if (n == 0 && k0 < K) cen_s[k0] = half_bits_to_f32(key_half(key));
@@ -736,6 +755,7 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
     } else if (tid < K) {
         cen_s[tid] = 0.f;
     }
+    if (S::kFirst != 0 && wave != 0) write_entries();               // beside the iterations
     // ---- 8. fp16 tables; an index is the number of boundaries between table entries below the weight, as keys
     __syncthreads();
     if (tid < K) {
@@ -744,12 +764,13 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
         u32 k = 0xFFFFu;                                             // the last one: above every key
         if (tid < K - 1) {
             const uint16_t hn = __builtin_bit_cast(uint16_t, (_Float16)cen_s[tid + 1]);
-            const i64 t = half_to_fixed(hb) + half_to_fixed(hn);     // largest key with 2 w 2^24 <= t
+            // largest key whose weight is at most the middle of the two entries, which fp64 holds exactly; +0 where it is zero
+            const double mid = __builtin_fma(0.5, (double)half_bits_to_f32(hb) + (double)half_bits_to_f32(hn), 0.0);
             typedef __fp16 fp16x2 __attribute__((ext_vector_type(2)));
-            const fp16x2 h = __builtin_amdgcn_cvt_pkrtz((float)((double)t * 2.98023223876953125e-08), 0.f);
-            k = half_key(__builtin_bit_cast(u32, h) & 0xFFFFu);
-            if (2 * half_to_fixed(key_half(k)) > t) --k;
-            if (k < 0xFBFFu && 2 * half_to_fixed(key_half(k + 1)) <= t) ++k;
+            const fp16x2 h2 = __builtin_amdgcn_cvt_pkrtz((float)mid, 0.f);
+            const u32 h = __builtin_bit_cast(u32, h2) & 0xFFFFu;     // that weight or the next one up: one step down is a larger magnitude below zero
+            const bool up = (double)half_bits_to_f32(h) > mid;
+            k = half_key(h) - (up ? 1u : 0u);
         }
         bound[tid] = (k << 16) | 0xFFFFu;
         atomicMin(&nearest, ((u32)(hb & 0x7FFFu) << 4) | tid);       // the entry nearest to zero, the first of several
