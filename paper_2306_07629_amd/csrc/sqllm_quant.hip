@@ -359,13 +359,12 @@ constexpr int kHeavy = 256;
 //     the order of their keys, and an update bisects them instead of reading them through (nine tenths zeros, 32 updates: 4096x11008 at 4
 //     bits 0.84 ms, read through 16.3; 1024x28672 0.52 ms, read through 18.7).
 // The decisions and integers are those of a pass over all weights per update, hence the same result.
-// Bound by the latency of the chain boundary -> bucket -> words -> reduction -> division (1150 cycles at 4096 weights and 8 entries, 1480 at
-// 11008 and 16), which the other rows on the unit cover only in part (six at 4096 weights, two at 11008: what their LDS allows).  It was 1570
-// and 1920 with the key of a boundary corrected in two steps, the two bucket ends read one after the other under a branch, a test in front of
-// the first round, a full fp64 division behind the test for the end, and no priority over the waves of other rows.  Against a bitonic sort of the row in LDS and a 64-way
-// search per boundary with reductions over 64 lanes: 4096x4096 at 3 bits 409 -> 101 us (22 updates per row, 1.9 us each over the
-// matrix), 4096x11008 at 4 bits 1164 -> 334 us (32 updates, 6.0 us each).  With a wave per eight boundaries, keys in the words and sums
-// exchanged through LDS: 112 and 377 us.
+// Bound by the latency of the chain boundary -> bucket -> words -> reduction -> division (1150 cycles at 4096 weights and 8 entries, 1130 at
+// 11008 and 16; with 4096 buckets 1480), which the other rows on the unit cover only in
+// part (what their LDS allows: six at 4096 weights, two at 11008).  It was 1570 and 1920 with the key of a boundary corrected in two steps, the two bucket ends read one after the other under a branch, a test
+// in front of the first round, a full fp64 division behind the test for the end, and no priority over the waves of other rows.  Against a
+// bitonic sort of the row in LDS and a 64-way search per boundary with reductions over 64 lanes: 4096x4096 at 3 bits 409 us, now 90
+// (22 updates per row), 4096x11008 at 4 bits 1164, now 258 (32 updates).
 // Threads T, units of eight weights per thread V, buckets, words per chunk of running sums (twice as many in wide rows), and the waves per
 // SIMD the registers are held down for.
 template <int T_, int V_, int LOG_NB, int CHUNK, int WAVES>
@@ -386,10 +385,18 @@ struct KmeansShape {
         return true;
     }
 };
+typedef KmeansShape<128, 1, 11, 8, 6> KmeansUpTo1024;                // 10 KB of LDS at 1024 weights: fourteen rows per compute unit
+typedef KmeansShape<128, 2, 11, 8, 5> KmeansUpTo2048;                // ten rows
 typedef KmeansShape<256, 2, 11, 8, 6> KmeansUpTo4096;                // 26 KB of LDS at 4096 weights: six rows per compute unit
-typedef KmeansShape<512, 3, 12, 8, 4> KmeansUpTo12288;               // 69 KB at 11008: two
+typedef KmeansShape<256, 3, 12, 8, 4> KmeansUpTo6144;                // 36 KB at 5120: four
+typedef KmeansShape<256, 4, 12, 8, 4> KmeansUpTo8192;                // 53 KB at 8192: three (eleven registers spilled, outside the iterations)
+typedef KmeansShape<512, 3, 13, 8, 4> KmeansUpTo11776;               // 77 KB at 11008: two
+typedef KmeansShape<512, 3, 12, 8, 4> KmeansUpTo12288;
 typedef KmeansShape<512, 4, 12, 8, 4> KmeansUpTo16384;
 typedef KmeansShape<1024, 4, 12, 16, 4> KmeansBeyond;                // 145 KB at 28672: one (two to four registers spilled; 1024x28672 at 4 bits 0.32 ms)
+
+constexpr int kMaxN11776 = 11776;
+static_assert(KmeansUpTo11776::lds(kMaxN11776) + 512 <= 80 * 1024, "two rows per compute unit");
 
 template <int BITS, class S>
 __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(int M, int N, int max_iter, const uint16_t* __restrict__ w, const uint16_t* __restrict__ sens,
@@ -846,10 +853,19 @@ template <class S>
 static hipError_t launch_kmeans_bits(const QuantArgs& a, hipStream_t s) {
     return a.bits == 2 ? launch_kmeans<2, S>(a, s) : (a.bits == 3 ? launch_kmeans<3, S>(a, s) : launch_kmeans<4, S>(a, s));
 }
-// Threads per row by the row's LDS footprint: few rows fit a compute unit when they are long, so each gets more waves for the phases that
-// pass over its weights.
+// Threads, registers and buckets by the length of the row, so that as many rows share a compute unit as its LDS allows: while one wave of a
+// row iterates, the others have nothing to do.  us before (256 threads and 2048 buckets up to 4096, 512 and 4096 up to 12288) and with the
+// present shapes: 8192x256 at 3 bits 148 / 120, 8192x1024 181 / 148, 8192x2048 215 / 196, 5120x5120 at 4 bits 383 / 273, 4096x6144 313 / 259,
+// 8192x8192 615 / 557.  11776 columns and below: 8192 buckets instead of 4096 halve the words read per update and still leave room for two
+// rows (4096x11008 at 4 bits: 1480 -> 1130 cycles per update, 428 -> 398 us).  Where all rows are on the chip at once (two to a unit) more
+// threads per row count for more: 300x8192 107 us with 512 threads, 112 with 256.
 static hipError_t launch_kmeans_shape(const QuantArgs& a, hipStream_t s) {
+    if (a.N <= KmeansUpTo1024::kMaxN) return launch_kmeans_bits<KmeansUpTo1024>(a, s);
+    if (a.N <= KmeansUpTo2048::kMaxN) return launch_kmeans_bits<KmeansUpTo2048>(a, s);
     if (a.N <= KmeansUpTo4096::kMaxN) return launch_kmeans_bits<KmeansUpTo4096>(a, s);
+    if (a.N <= KmeansUpTo6144::kMaxN) return launch_kmeans_bits<KmeansUpTo6144>(a, s);
+    if (a.N <= KmeansUpTo8192::kMaxN && a.M > 512) return launch_kmeans_bits<KmeansUpTo8192>(a, s);
+    if (a.N <= kMaxN11776) return launch_kmeans_bits<KmeansUpTo11776>(a, s);
     if (a.N <= KmeansUpTo12288::kMaxN) return launch_kmeans_bits<KmeansUpTo12288>(a, s);
     if (a.N <= KmeansUpTo16384::kMaxN) return launch_kmeans_bits<KmeansUpTo16384>(a, s);
     return launch_kmeans_bits<KmeansBeyond>(a, s);

@@ -1,4 +1,4 @@
-"""The mean of a cluster is formed without a division and checked against the places where that could round differently: means that are
+"""Row lengths and row counts at which the k-means kernel changes its shape, and the means of its clusters.  A mean is formed without a division and checked against the places where that could round differently: means that are
 exact, that lie in the middle between two fp32 numbers or next to it, equal weights of both signs, zeros of both signs."""
 import numpy as np
 import pytest
@@ -26,14 +26,10 @@ def rows(kind, M, N, rng):
     return w.astype(np.float16).view(np.uint16), s.astype(np.uint16)
 
 
-@pytest.mark.parametrize("kind", ["middles", "zeros", "levels", "wide"])
-@pytest.mark.parametrize("N,bits", [(128, 2), (1024, 3), (1152, 4), (4096, 4), (4224, 3)])
-def test_bit_exact_against_the_oracle(kind, N, bits):
+def check(M, N, bits, w, s):
     import torch
     import paper_2306_07629_amd as sq
     import oracle
-    M = 6
-    w, s = rows(kind, M, N, np.random.default_rng(N + bits))
     counts = (M * N // 300, M * N // 300, M * N // 500)
     q = sq.quantize_layer(torch.from_numpy(w.view(np.int16)).cuda(), torch.from_numpy(s.view(np.int16)).cuda(), bits, *counts, max_iter=32)
     ref = qo.quantize_layer(w, s, bits, *counts, 32)
@@ -43,3 +39,17 @@ def test_bit_exact_against_the_oracle(kind, N, bits):
     assert np.array_equal(q.iters.cpu().numpy(), ref["iters"])
     assert np.array_equal(q.lut.cpu().numpy().view(np.uint16), ref["lut"])
     assert np.array_equal(oracle.unpack(M, N, bits, q.qidx.cpu().numpy()), ref["idx"])
+
+
+@pytest.mark.parametrize("kind", ["middles", "zeros", "levels", "wide"])
+@pytest.mark.parametrize("N,bits", [(128, 2), (1024, 3), (1152, 4), (4096, 4), (4224, 3)])
+def test_means_next_to_the_middle_of_two_numbers(kind, N, bits):
+    check(6, N, bits, *rows(kind, 6, N, np.random.default_rng(N + bits)))
+
+
+# last and first row length of every shape; 8192 columns: 512 rows and more than that
+@pytest.mark.parametrize("M,N,bits", [(9, 896, 4), (9, 1024, 2), (9, 1152, 3), (9, 2048, 4), (9, 2176, 3), (5, 6144, 4), (5, 6272, 3),
+                                      (512, 6272, 3), (513, 6272, 4), (513, 8192, 2), (5, 8320, 4), (5, 11776, 4), (5, 11904, 3), (5, 12288, 2)])
+def test_shapes(M, N, bits):
+    import gen
+    check(M, N, bits, gen.make_weights(M, N, N + bits), gen.make_sens(M, N, N + bits))
