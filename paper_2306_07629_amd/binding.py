@@ -1,5 +1,5 @@
-"""ctypes binding of the C ABI in include/sqllm.h.  Argument marshalling only: every step of the matvec
-runs in the HIP kernels of libsqllm.so.  PyTorch tensors are used as owners of device memory and for the
+"""ctypes binding of the C ABI in include/sqllm.h (the matvec call also natively, csrc/sqllm_pycall.c).  Argument marshalling
+only: every step of the matvec runs in the HIP kernels of libsqllm.so.  PyTorch tensors are used as owners of device memory and for the
 current HIP stream, nothing else.  There is no CPU fallback: a missing library raises."""
 from __future__ import annotations
 
@@ -106,9 +106,31 @@ def sqllm_csr_spmv_rowwise(M, N, nnz, B, rowptr, cols, vals, x, y, accumulate=0,
     _check(lib().sqllm_csr_spmv_rowwise(M, N, nnz, B, _ptr(rowptr), _ptr(cols), _ptr(vals), _ptr(x), _ptr(y), int(accumulate), _stream(stream)))
 
 
+def _matvec_ctypes(M, N, bits, nnz, B, qidx, lut, rowptr, cols, vals, plan, x, y, stream):
+    return lib().sqllm_dense_sparse_matvec(M, N, bits, nnz, B, _ptr(qidx), _ptr(lut), _ptr(rowptr), _ptr(cols), _ptr(vals), _ptr(plan),
+                                           _ptr(x), _ptr(y), _stream(stream))
+
+
+def _matvec_first(*args):
+    """The first call: goes through ctypes, then hands over to the native path if torch has a current stream to ask for."""
+    global _matvec
+    status = _matvec_ctypes(*args)
+    if _raw_stream is not None:
+        from . import _pycall
+        _pycall.bind(ctypes.cast(lib().sqllm_dense_sparse_matvec, ctypes.c_void_p).value, _torch.cuda.current_device, _raw_stream)
+        _matvec = _pycall.matvec
+    return status
+
+
+_matvec = _matvec_first
+
+
 def sqllm_dense_sparse_matvec(M, N, bits, nnz, B, qidx, lut, rowptr, cols, vals, x, y, stream=None, plan=None):
-    _check(lib().sqllm_dense_sparse_matvec(M, N, bits, nnz, B, _ptr(qidx), _ptr(lut), _ptr(rowptr), _ptr(cols), _ptr(vals), _ptr(plan),
-                                           _ptr(x), _ptr(y), _stream(stream)))
+    status = _matvec(M, N, bits, nnz, B, qidx, lut, rowptr, cols, vals, plan, x, y, stream)
+    if status is None:                                                # arguments that only ctypes knows how to take, or to refuse
+        status = _matvec_ctypes(M, N, bits, nnz, B, qidx, lut, rowptr, cols, vals, plan, x, y, stream)
+    if status:
+        _check(status)
 
 
 def sqllm_csr_plan_bytes(M, N, nnz) -> int:

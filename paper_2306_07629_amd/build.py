@@ -1,13 +1,15 @@
-"""Build step: compile the HIP sources under csrc/ into libsqllm.so (gfx950 only), in-tree."""
+"""Build step: compile the HIP sources under csrc/ into libsqllm.so (gfx950 only) and the Python call path into _pycall.so, in-tree."""
 from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsqllm.so")
+PYCALL, PYCALL_SOURCE = os.path.join(HERE, "_pycall.so"), os.path.join(CSRC, "sqllm_pycall.c")
 SOURCES = ["sqllm_kernels.hip", "sqllm_batch.hip", "sqllm_quant.hip", "sqllm_api.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -20,7 +22,9 @@ def sources():
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(PYCALL):
+        return True
+    if os.path.getmtime(PYCALL_SOURCE) > os.path.getmtime(PYCALL):
         return True
     t = os.path.getmtime(LIB)
     headers = [os.path.join(CSRC, h) for h in ("sqllm_kernels.h", "sqllm_decode.h", "sqllm_batch_split.h")]
@@ -35,6 +39,9 @@ def build(verbose: bool = False) -> str:
     # hipcc's host pass prints a harmless "unknown target feature" warning for -packed-fp32-ops
     if res.returncode != 0:
         raise RuntimeError("hipcc failed:\n" + res.stdout + res.stderr)
+    res = subprocess.run(["gcc", "-O2", "-Wall", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"], PYCALL_SOURCE, "-o", PYCALL], capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("gcc failed:\n" + res.stdout + res.stderr)
     if verbose:
         print(" ".join(cmd))
     return LIB
