@@ -1,7 +1,7 @@
 /* One call of sqllm_dense_sparse_matvec from Python without ctypes: takes the arguments apart, asks the tensors for their addresses and the
- * runtime for the current stream, and calls the library.  The call of a small layer is bound by the host: through ctypes 256x4096 takes 5.6 us and
- * 4096x4096 at 4 bits 5.8, this way 4.5 and 4.5 (their kernels run for 3.0 and 4.4).  Arguments that are not plain ints, None or objects with data_ptr() are left to
- * the ctypes path (None is returned), which accepts or refuses them as it always has. */
+ * runtime for the current stream, and calls the library.  The call of a small layer is bound by the host: through ctypes 256x4096 takes
+ * 5.6 us and 4096x4096 at 4 bits 5.8, this way 4.5 and 4.5 (their kernels run for 3.0 and 4.4).  Arguments that are not plain ints, None or
+ * objects with data_ptr() are left to the ctypes path (None is returned), which accepts or refuses them as it always has. */
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
