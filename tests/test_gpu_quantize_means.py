@@ -1,5 +1,6 @@
-"""Row lengths and row counts at which the k-means kernel changes its shape, and the means of its clusters.  A mean is formed without a division and checked against the places where that could round differently: means that are
-exact, that lie in the middle between two fp32 numbers or next to it, equal weights of both signs, zeros of both signs."""
+"""Row lengths and row counts at which the k-means kernel changes its shape, and the means of its clusters.  A mean is formed without
+a division and checked against the places where that could round differently: means that are exact, that lie in the middle between two
+fp32 numbers or next to it, equal weights of both signs, zeros of both signs."""
 import numpy as np
 import pytest
 
