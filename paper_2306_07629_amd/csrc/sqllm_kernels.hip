@@ -38,6 +38,7 @@
 #include <string.h>
 #include <type_traits>
 
+#include "sqllm_csr.h"
 #include "sqllm_decode.h"
 #include "sqllm_kernels.h"
 
@@ -236,15 +237,15 @@ struct SparseRange {
     int P0, P1, nbatch;
 };
 
-// Loads of one round are unconditional (indices clamped into [P0, P1), surplus lanes and batches are masked
-// in the reduction), so that all of them are in flight at once.
+// Loads of one round are unconditional (positions clamped to the range's last nonzero, surplus lanes and batches are masked
+// in the sums), so that all of them are in flight at once.
 template <int UB>
 __device__ __forceinline__ void sparse_issue_cols_vals(const MatvecArgs& g, const SparseRange& sr, int b0, int NW, int lane, SparseRegs<UB>& q) {
     const int* __restrict__ cols = g.cols;
     const uint16_t* __restrict__ vals = static_cast<const uint16_t*>(g.vals);
 #pragma unroll
     for (int k = 0; k < UB; ++k) {
-        const int p = min(sr.P0 + (b0 + k * NW) * kWave + lane, sr.P1 - 1);
+        const int p = csr_position(sr.P1, csr_nonzero(sr.P0, b0 + k * NW, lane));
         q.c[k] = cols[p];
         q.vb[k] = vals[p];
     }
@@ -262,11 +263,8 @@ __device__ __forceinline__ void sparse_accumulate(const SparseRange& sr, const i
     for (int k = 0; k < UB; ++k) {
         const int b = b0 + k * NW;
         if (b < sr.nbatch) {                                         // uniform
-            const int p = sr.P0 + b * kWave + lane;
             const float v = half_bits_to_float(q.vb[k]) * half_bits_to_float(q.xv[k]);
-            int row = p < sr.P1 ? 0 : R;                             // number of i in 1..R-1 with rp[i] <= p; R: nothing for this lane
-#pragma unroll
-            for (int i = 1; i < R; ++i) row += (p >= rp[i]) ? 1 : 0;
+            const int row = csr_row<R>(rp, csr_nonzero(sr.P0, b, lane));   // R or more: nothing for this lane
 #pragma unroll
             for (int i = 0; i < R; ++i) acc[i] = row == i ? acc[i] + v : acc[i];
         }
@@ -296,7 +294,7 @@ template <int R>
 __device__ __forceinline__ void load_row_pointers(const MatvecArgs& g, int r0, int nrows, bool sparse, int (&rp)[R + 1], SparseRange& sr) {
 #pragma unroll
     for (int k = 0; k <= R; ++k) rp[k] = sparse ? g.rowptr[r0 + min(k, nrows)] : 0;   // uniform -> scalar loads
-    sr.P0 = rp[0]; sr.P1 = rp[R]; sr.nbatch = (sr.P1 - sr.P0 + kWave - 1) / kWave;
+    sr.P0 = rp[0]; sr.P1 = rp[R]; sr.nbatch = csr_batch_count(sr.P0, sr.P1);
 }
 
 // The work of one workgroup: rows [R block, R block + R) of layer g, carried by the workgroup's first NW waves

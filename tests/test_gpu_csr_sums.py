@@ -33,3 +33,36 @@ def test_every_entry_counts_once_in_its_own_row(N, first):
     D.y.zero_()
     sq.sqllm_dense_sparse_matvec_multi([D.descriptor(), sq.DeviceLayer(gen.hand_layer(idx, lut, 3, rowptr, cols, vals, x)).descriptor()])
     assert np.array_equal(D.y.cpu().numpy().view(np.float16)[:, 0], want)
+
+
+@pytest.mark.parametrize("N", [128, 16384])                              # four and eight rows to a workgroup
+@pytest.mark.parametrize("fused", [False, True])
+def test_nonzeros_up_to_the_largest_position(N, fused):
+    """2^31 - 1 nonzeros (13 GB; entries of one row and column add up): the last workgroup's batches begin less than a round before the end
+    of the 32-bit range, and its last rows end inside a batch.  Small integers, so every sum is exact."""
+    import torch
+    import paper_2306_07629_amd as sq
+    M, nnz = 4096, 2 ** 31 - 1
+    print(f"largest nnz N={N} fused={fused}", flush=True)
+    rowptr = torch.minimum(torch.arange(M + 1, dtype=torch.int64) * 2 ** 19, torch.tensor(nnz))
+    rowptr[M - 8:M] = nnz - torch.tensor([3000, 700, 131, 130, 70, 69, 2, 1])   # the last eight rows hold 2300, 569, 1, 60, 1, 67, 1 and 1
+    cols = torch.full((nnz,), 3, dtype=torch.int32, device="cuda")
+    vals = torch.zeros(nnz, dtype=torch.int16, device="cuda")
+    vals[:2] = 0x3C00
+    vals[nnz - 2900:] = 0x3C00
+    x = torch.zeros((N, 1), dtype=torch.float16, device="cuda")
+    x[3] = 1
+    y = torch.zeros((M, 1), dtype=torch.float16, device="cuda")
+    if fused:
+        qidx = torch.zeros(M * N * 2 // 8, dtype=torch.uint8, device="cuda")
+        lut = torch.zeros((M, 4), dtype=torch.float16, device="cuda")
+        sq.sqllm_dense_sparse_matvec(M, N, 2, nnz, 1, qidx, lut, rowptr.int().cuda(), cols, vals, x, y)
+    else:
+        sq.sqllm_csr_spmv(M, N, nnz, 1, rowptr.int().cuda(), cols, vals, x, y)
+    want = torch.zeros((M, 1))
+    want[0] = 2
+    want[M - 8:, 0] = torch.tensor([2200., 569, 1, 60, 1, 67, 1, 1])
+    got = y.cpu()
+    del cols, vals
+    torch.cuda.empty_cache()
+    assert torch.equal(got, want.half())

@@ -3,10 +3,12 @@
 The kernels avoid divergent bounds checks: tail lanes, tail rows and surplus sparse batches load CLAMPED addresses whose
 results are neutralised later.  A GPU test cannot show that such a load stays inside its array (an over-read of a few bytes
 lands in mapped memory of the allocator's pool and the result is still right), so this test re-computes, from the clamping
-formulas the kernels use (`j0c`, `min(r0 + u, M - 1)`, `min(p, P1 - 1)`, `last_t`, the slots of the activation windows), every
+formulas the kernels use (`j0c`, `min(r0 + u, M - 1)`, `csr_position` -- the kernel's own function, compiled for the CPU --, `last_t`, the slots of the activation windows), every
 address range they touch, for every shape of the GPU test lists, and asserts that it lies inside the array."""
 import numpy as np
 import pytest
+
+import host_split
 
 SLICE, LANE_ELEMS, WAVE = 2048, 32, 64
 
@@ -53,11 +55,11 @@ def one_column_kernel_reads(M, N, bits, rowptr, R):
         rp = [int(rowptr[r0 + min(k, nrows)]) for k in range(R + 1)]
         yield "rowptr", 4 * r0, 4 * (r0 + nrows) + 4
         P0, P1 = rp[0], rp[R]
-        nbatch = (P1 - P0 + WAVE - 1) // WAVE
+        nbatch = host_split.library().batches(P0, P1)
         if nbatch > 0:
             NW, UB = W + 1, 8  # dense waves and the sparse wave
             for b0 in range(0, nbatch + NW * UB, 1):             # every batch slot a round can touch, surplus ones included
-                p = np.minimum(P0 + b0 * WAVE + lanes, P1 - 1)
+                p = host_split.csr_positions(P0, P1, b0)
                 assert (p >= P0).all()
                 yield "cols", int(4 * p.min()), int(4 * p.max() + 4)
                 yield "vals", int(2 * p.min()), int(2 * p.max() + 2)
