@@ -1,5 +1,5 @@
-// Plain arithmetic of the one-column kernel over the CSR arrays: which nonzeros a workgroup's batches hold and whose rows they are.  No HIP in
-// here: the kernel and the tests that run without a GPU use these functions.
+// Plain arithmetic over the CSR arrays, of the one-column kernel -- which nonzeros a workgroup's batches hold and whose rows they are -- and of
+// the offline pass, which writes them.  No HIP in here: the kernels and the tests that run without a GPU use these functions.
 // Positions of nonzeros go up to 2^31 - 2 (nnz < 2^31), and a workgroup may begin so close to that end that its first position plus a few
 // batches exceeds an int.  The batches that a round asks for beyond the last nonzero are a few thousand positions, so an unsigned sum holds all
 // of them; it is clamped and compared as such.
@@ -21,5 +21,9 @@ constexpr int csr_row(const int (&rp)[R + 1], uint32_t p) {
     for (int i = 1; i < R; ++i) row += p >= (uint32_t)rp[i] ? 1 : 0;
     return row;
 }
+
+// May an entry be written at position p?  In front of the end of its row and of the arrays: always, unless the weights have changed since the
+// row's entries were counted.
+constexpr bool csr_has_room(int p, int row_end, int capacity) { return p >= 0 && p < (row_end < capacity ? row_end : capacity); }
 
 }  // namespace sqllm

@@ -19,6 +19,7 @@
 #include <stdint.h>
 #include <type_traits>
 
+#include "sqllm_csr.h"
 #include "sqllm_kernels.h"
 
 namespace sqllm {
@@ -399,7 +400,7 @@ constexpr int kMaxN11776 = 11776;
 static_assert(KmeansUpTo11776::lds(kMaxN11776) + 512 <= 80 * 1024, "two rows per compute unit");
 
 template <int BITS, class S>
-__global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(int M, int N, int max_iter, const uint16_t* __restrict__ w, const uint16_t* __restrict__ sens,
+__global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(int M, int N, int max_iter, int capacity, const uint16_t* __restrict__ w, const uint16_t* __restrict__ sens,
                                                          const u32* __restrict__ ws, const int* __restrict__ rowptr, void* __restrict__ qidx,
                                                          uint16_t* __restrict__ lut, int* __restrict__ cols, uint16_t* __restrict__ vals, int* __restrict__ iters) {
     constexpr int K = 1 << BITS, SETS = K > 8 ? K / 8 : 1;           // eight boundaries per wave
@@ -484,13 +485,17 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
     if (most >= kHeavy - 1) crowded = 1;
     const u32 ext = tid >= S::kFirst && tid - S::kFirst < N / 32 ? emask[tid - S::kFirst] : 0u;
     __syncthreads();
-    // CSR entries of the row, columns ascending
+    // CSR entries of the row, columns ascending.  Where the inputs change under the call there may be more of them than were counted: the
+    // result is wrong then, but nothing is written outside the arrays.
     int entry = 0;
     auto write_entries = [&]() {
+        const int end = rowptr[row + 1];
         for (u32 m = ext; m; m &= m - 1) {
             const int j = 32 * (tid - S::kFirst) + __builtin_ctz(m);
-            cols[entry] = j;
-            vals[entry] = wrow[j];
+            if (csr_has_room(entry, end, capacity)) {
+                cols[entry] = j;
+                vals[entry] = wrow[j];
+            }
             ++entry;
         }
     };
@@ -845,7 +850,7 @@ static hipError_t launch_kmeans(const QuantArgs& a, hipStream_t s) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&quant_kmeans_kernel<BITS, S>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::lds(S::kMaxN));
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((quant_kmeans_kernel<BITS, S>), dim3(a.M), dim3(S::T), S::lds(a.N), s, a.M, a.N, a.max_iter,
-                       static_cast<const uint16_t*>(a.w), static_cast<const uint16_t*>(a.sens), static_cast<const u32*>(a.workspace), a.rowptr, a.qidx,
+                       (int)(a.n_lo + a.n_hi + a.n_sens), static_cast<const uint16_t*>(a.w), static_cast<const uint16_t*>(a.sens), static_cast<const u32*>(a.workspace), a.rowptr, a.qidx,
                        static_cast<uint16_t*>(a.lut), a.cols, static_cast<uint16_t*>(a.vals), a.iters);
     return hipGetLastError();
 }

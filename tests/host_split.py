@@ -32,6 +32,7 @@ void rows4(const int* rp, int b, int* out) {
 void rows8(const int* rp, int b, int* out) {
     for (int lane = 0; lane < kBatchNonzeros; ++lane) out[lane] = csr_row<8>(*reinterpret_cast<const int(*)[9]>(rp), csr_nonzero(rp[0], b, lane));
 }
+int has_room(int p, int row_end, int capacity) { return csr_has_room(p, row_end, capacity); }
 }
 """
 
