@@ -390,7 +390,8 @@ typedef KmeansShape<128, 1, 11, 8, 6> KmeansUpTo1024;                // 10 KB of
 typedef KmeansShape<128, 2, 11, 8, 5> KmeansUpTo2048;                // ten rows
 typedef KmeansShape<256, 2, 11, 8, 6> KmeansUpTo4096;                // 26 KB of LDS at 4096 weights: six rows per compute unit
 typedef KmeansShape<256, 3, 12, 8, 4> KmeansUpTo6144;                // 36 KB at 5120: four
-typedef KmeansShape<256, 4, 12, 8, 4> KmeansUpTo8192;                // 53 KB at 8192: three (eleven registers spilled, outside the iterations)
+typedef KmeansShape<256, 4, 12, 8, 3> KmeansUpTo8192;                // 53 KB at 8192: three, which is three waves per SIMD; registers held down for
+                                                                     // four spilled 11 to 14 (8192 columns, two values 442 us, now 424; Student-t 285, 272)
 typedef KmeansShape<512, 3, 13, 8, 4> KmeansUpTo11776;               // 77 KB at 11008: two
 typedef KmeansShape<512, 3, 12, 8, 4> KmeansUpTo12288;
 typedef KmeansShape<512, 4, 12, 8, 4> KmeansUpTo16384;

@@ -1,4 +1,6 @@
 import os
+import shutil
+import subprocess
 import sys
 
 import pytest
@@ -20,3 +22,15 @@ def pytest_collection_modifyitems(config, items):
 @pytest.fixture(scope="session")
 def golden_dir():
     return os.path.join(ROOT, "tests", "golden")
+
+
+@pytest.fixture(scope="session")
+def assembly(tmp_path_factory):
+    """csrc/sqllm_quant.hip as the compiler emits it for the GPU"""
+    from paper_2306_07629_amd import build
+    assert shutil.which(build.HIPCC), "hipcc is needed to build the library"
+    out = tmp_path_factory.mktemp("asm") / "quant.s"
+    flags = [f for f in build.FLAGS if f not in ("-fPIC", "-shared")]
+    src = [s for s in build.sources() if s.endswith("sqllm_quant.hip")]
+    subprocess.run([build.HIPCC, *flags, "--cuda-device-only", "-S", "-I" + build.CSRC, *src, "-o", str(out)], check=True, capture_output=True)
+    return out.read_text()

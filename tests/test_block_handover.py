@@ -3,24 +3,10 @@ agent-scope stores, then every wave's wait for them, the barrier, and only then 
 reads what the others left.  (The language does not promise that order without a release that would cost 4 % of a call, so a compiler that
 changes it must be noticed here.)"""
 import re
-import shutil
-import subprocess
 
 import pytest
 
-from paper_2306_07629_amd import build
-
 KERNELS = ["quant_hist1_kernel", "quant_hist2_kernel", "quant_count_kernel"]
-
-
-@pytest.fixture(scope="module")
-def assembly(tmp_path_factory):
-    assert shutil.which(build.HIPCC), "hipcc is needed to build the library"
-    out = tmp_path_factory.mktemp("asm") / "quant.s"
-    flags = [f for f in build.FLAGS if f not in ("-fPIC", "-shared")]
-    src = [s for s in build.sources() if s.endswith("sqllm_quant.hip")]
-    subprocess.run([build.HIPCC, *flags, "--cuda-device-only", "-S", "-I" + build.CSRC, *src, "-o", str(out)], check=True, capture_output=True)
-    return out.read_text()
 
 
 def instructions(assembly, kernel):
