@@ -27,7 +27,7 @@ def is_stale() -> bool:
     if os.path.getmtime(PYCALL_SOURCE) > os.path.getmtime(PYCALL):
         return True
     t = os.path.getmtime(LIB)
-    headers = [os.path.join(CSRC, h) for h in ("sqllm_kernels.h", "sqllm_decode.h", "sqllm_batch_split.h", "sqllm_csr.h")]
+    headers = [os.path.join(CSRC, h) for h in ("sqllm_kernels.h", "sqllm_decode.h", "sqllm_batch_split.h", "sqllm_csr.h", "sqllm_buckets.h")]
     deps = sources() + headers + [os.path.join(ROOT, "include", "sqllm.h")]
     return any(os.path.getmtime(d) > t for d in deps)
 

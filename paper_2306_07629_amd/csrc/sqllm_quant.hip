@@ -19,6 +19,7 @@
 #include <stdint.h>
 #include <type_traits>
 
+#include "sqllm_buckets.h"
 #include "sqllm_csr.h"
 #include "sqllm_kernels.h"
 
@@ -377,7 +378,10 @@ struct KmeansShape {
     // with 1024 threads, where the two registers it takes until then are spilled (1024x28672 341 us against 330), they are written at once.
     static constexpr int kFirst = T_ <= 512 && kMaxN / 32 <= T_ - 64 ? 64 : 0;
     static constexpr int kChunksPerThread = (kMaxN / CHUNK + T_ - 1) / T_;
-    static constexpr size_t sum_bytes(int N) { return (size_t)(N / CHUNK + 1) * 12; }                // also holds (N / (2 CHUNK) + 1) * 20
+    static constexpr size_t sum_bytes(int N) { return ((size_t)(N / CHUNK + 1) * 12 + 15) & ~(size_t)15; }   // also holds (N / (2 CHUNK) + 1) * 20; the counters behind it are read four at a time
+    // Counters of neighbouring buckets apart in the banks (spread_word).  With 4096 buckets the levels of a quantised row lie in more banks
+    // anyway: 1024x28672, Student-t 298 us with it, 294 without.
+    static constexpr u32 counter_word(u32 v) { return LOG_NB > 12 ? spread_word(v) : v; }
     static constexpr size_t lds(int N) { return (size_t)(N + kPad) * 4 + sum_bytes(N) + (size_t)(NB + 2) * 2; }
     // the counters of the heavy buckets, 16 bits for each of a bucket's keys (2^shift, keys have 16 bits), take the place of the sums
     static constexpr bool counters_fit() {
@@ -392,7 +396,8 @@ typedef KmeansShape<256, 2, 11, 8, 6> KmeansUpTo4096;                // 26 KB of
 typedef KmeansShape<256, 3, 12, 8, 4> KmeansUpTo6144;                // 36 KB at 5120: four
 typedef KmeansShape<256, 4, 12, 8, 3> KmeansUpTo8192;                // 53 KB at 8192: three, which is three waves per SIMD; registers held down for
                                                                      // four spilled 11 to 14 (8192 columns, two values 442 us, now 424; Student-t 285, 272)
-typedef KmeansShape<512, 3, 13, 8, 4> KmeansUpTo11776;               // 77 KB at 11008: two
+typedef KmeansShape<512, 3, 13, 8, 4> KmeansUpTo11776;               // 77 KB at 11008: two.  16 levels at 3 bits, 4096x11008: 502 us, with the counters
+                                                                     // apart in the banks and four of them per access 475 (4096 buckets 477)
 typedef KmeansShape<512, 3, 12, 8, 4> KmeansUpTo12288;
 typedef KmeansShape<512, 4, 12, 8, 4> KmeansUpTo16384;
 typedef KmeansShape<1024, 4, 12, 16, 4> KmeansBeyond;                // 145 KB at 28672: one (two to four registers spilled; 1024x28672 at 4 bits 0.32 ms)
@@ -436,7 +441,7 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
             const int i = min(tid + T * v, units - 1);
             wv[v] = wr[i]; sv[v] = sr[i];
         }
-        for (int b = tid; b < NB / 2 + 1; b += T) start32[b] = 0;
+        for (int b = tid; b < NB / 8; b += T) reinterpret_cast<u32x4*>(start32)[b] = u32x4{0, 0, 0, 0};
         if (tid == 0) { kmm[0] = 0xFFFFu; kmm[1] = 0; crowded = 0; nearest = 0xFFFFFFFFu; }
         u32 kmin = 0xFFFFu, kmax = 0;
 #pragma unroll
@@ -478,7 +483,7 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
             u32 r = 0;
             if (word[v][e] != 0xFFFFFFFFu) {
                 const u32 b = bucket_of(word[v][e]), sh = 16 * (b & 1);
-                r = (atomicAdd(&start32[b >> 1], 1u << sh) >> sh) & 0xFFFFu;   // a bucket holds fewer than 2^15 words
+                r = (atomicAdd(&start32[S::counter_word(b >> 1)], 1u << sh) >> sh) & 0xFFFFu;   // a bucket holds fewer than 2^15 words
             }
             rank[v][e >> 1] = (e & 1) ? rank[v][e >> 1] | (r << 16) : r;
             most = umax(most, r);
@@ -503,9 +508,14 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
     // ---- 3. one scan over the threads for the places of the buckets (low half) and of the CSR entries (high half); both are below 2^15
     int n_dense;
     {
+        constexpr int VW = NBT / 2 < 4 ? NBT / 2 : 4;                // counters read and written at a time
+        typedef u32vec<VW> vec;
+        const u32 own = (u32)tid * (NBT / 2), counted = S::counter_word(own);
         u32 pair[NBT / 2], mine = 0;
 #pragma unroll
-        for (int k = 0; k < NBT / 2; ++k) { pair[k] = start32[tid * (NBT / 2) + k]; mine += (pair[k] & 0xFFFFu) + (pair[k] >> 16); }
+        for (int k = 0; k < NBT / 2; k += VW) *reinterpret_cast<vec*>(pair + k) = *reinterpret_cast<const vec*>(start32 + counted + k);
+#pragma unroll
+        for (int k = 0; k < NBT / 2; ++k) { mine += (pair[k] & 0xFFFFu) + (pair[k] >> 16); }
         const u32 dense = mine;
         mine |= (u32)__builtin_popcount(ext) << 16;
         const Plain inc = wave_scan(Plain{mine});
@@ -536,10 +546,13 @@ __global__ void __launch_bounds__(S::T, S::kWavesPerSimd) quant_kmeans_kernel(in
         }
 #pragma unroll
         for (int k = 0; k < NBT / 2; ++k) {
-            const u32 second = run + (pair[k] & 0xFFFFu);
-            start32[tid * (NBT / 2) + k] = run | (second << 16);
-            run = second + (pair[k] >> 16);
+            const u32 second = run + (pair[k] & 0xFFFFu), next = second + (pair[k] >> 16);
+            pair[k] = run | (second << 16);
+            run = next;
         }
+        // behind the barrier in front of the totals: all counters have been read
+#pragma unroll
+        for (int k = 0; k < NBT / 2; k += VW) *reinterpret_cast<vec*>(start32 + own + k) = *reinterpret_cast<const vec*>(pair + k);
         if (tid == 0) start32[NB / 2] = (u32)n_dense;
         entry = rowptr[row] + (int)(before >> 16);
         if constexpr (S::kFirst == 0) write_entries();

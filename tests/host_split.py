@@ -1,4 +1,4 @@
-"""csrc/sqllm_batch_split.h and csrc/sqllm_csr.h compiled for the CPU, with signed overflow made fatal."""
+"""csrc/sqllm_batch_split.h, csrc/sqllm_csr.h and csrc/sqllm_buckets.h compiled for the CPU, with signed overflow made fatal."""
 import ctypes
 import functools
 import os
@@ -11,6 +11,7 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 
 SOURCE = r"""
 #include "sqllm_batch_split.h"
+#include "sqllm_buckets.h"
 #include "sqllm_csr.h"
 using namespace sqllm;
 extern "C" {
@@ -32,6 +33,7 @@ void rows4(const int* rp, int b, int* out) {
 void rows8(const int* rp, int b, int* out) {
     for (int lane = 0; lane < kBatchNonzeros; ++lane) out[lane] = csr_row<8>(*reinterpret_cast<const int(*)[9]>(rp), csr_nonzero(rp[0], b, lane));
 }
+uint32_t counter(uint32_t v) { return spread_word(v); }
 int has_room(int p, int row_end, int capacity) { return csr_has_room(p, row_end, capacity); }
 }
 """
@@ -45,7 +47,7 @@ def library():
             f.write(SOURCE)
         subprocess.run(["g++", "-std=c++17", "-O1", "-ftrapv", "-Wall", "-Werror", "-shared", "-fPIC", "-I" + CSRC, src, "-o", so], check=True)
         lib = ctypes.CDLL(so)
-    lib.row_bits.restype = ctypes.c_uint32
+    lib.row_bits.restype = lib.counter.restype = ctypes.c_uint32
     return lib
 
 
