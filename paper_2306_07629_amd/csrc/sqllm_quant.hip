@@ -872,22 +872,18 @@ template <class S>
 static hipError_t launch_kmeans_bits(const QuantArgs& a, hipStream_t s) {
     return a.bits == 2 ? launch_kmeans<2, S>(a, s) : (a.bits == 3 ? launch_kmeans<3, S>(a, s) : launch_kmeans<4, S>(a, s));
 }
-// Threads, registers and buckets by the length of the row, so that as many rows share a compute unit as its LDS allows: while one wave of a
-// row iterates, the others have nothing to do.  us before (256 threads and 2048 buckets up to 4096, 512 and 4096 up to 12288) and with the
-// present shapes: 8192x256 at 3 bits 148 / 120, 8192x1024 181 / 148, 8192x2048 215 / 196, 5120x5120 at 4 bits 383 / 273, 4096x6144 313 / 259,
-// 8192x8192 615 / 557.  11776 columns and below: 8192 buckets instead of 4096 halve the words read per update and still leave room for two
-// rows (4096x11008 at 4 bits: 1480 -> 1130 cycles per update, 428 -> 398 us).  Where all rows are on the chip at once (two to a unit) more
-// threads per row count for more: 300x8192 107 us with 512 threads, 112 with 256.
 static hipError_t launch_kmeans_shape(const QuantArgs& a, hipStream_t s) {
-    if (a.N <= KmeansUpTo1024::kMaxN) return launch_kmeans_bits<KmeansUpTo1024>(a, s);
-    if (a.N <= KmeansUpTo2048::kMaxN) return launch_kmeans_bits<KmeansUpTo2048>(a, s);
-    if (a.N <= KmeansUpTo4096::kMaxN) return launch_kmeans_bits<KmeansUpTo4096>(a, s);
-    if (a.N <= KmeansUpTo6144::kMaxN) return launch_kmeans_bits<KmeansUpTo6144>(a, s);
-    if (a.N <= KmeansUpTo8192::kMaxN && a.M > 512) return launch_kmeans_bits<KmeansUpTo8192>(a, s);
-    if (a.N <= kMaxN11776) return launch_kmeans_bits<KmeansUpTo11776>(a, s);
-    if (a.N <= KmeansUpTo12288::kMaxN) return launch_kmeans_bits<KmeansUpTo12288>(a, s);
-    if (a.N <= KmeansUpTo16384::kMaxN) return launch_kmeans_bits<KmeansUpTo16384>(a, s);
-    return launch_kmeans_bits<KmeansBeyond>(a, s);
+    switch (kmeans_columns(a.M, a.N)) {
+        case 1024: return launch_kmeans_bits<KmeansUpTo1024>(a, s);
+        case 2048: return launch_kmeans_bits<KmeansUpTo2048>(a, s);
+        case 4096: return launch_kmeans_bits<KmeansUpTo4096>(a, s);
+        case 6144: return launch_kmeans_bits<KmeansUpTo6144>(a, s);
+        case 8192: return launch_kmeans_bits<KmeansUpTo8192>(a, s);
+        case 11776: return launch_kmeans_bits<KmeansUpTo11776>(a, s);
+        case 12288: return launch_kmeans_bits<KmeansUpTo12288>(a, s);
+        case 16384: return launch_kmeans_bits<KmeansUpTo16384>(a, s);
+        default: return launch_kmeans_bits<KmeansBeyond>(a, s);
+    }
 }
 
 hipError_t launch_quantize(const QuantArgs& a, hipStream_t s) {

@@ -34,6 +34,7 @@ void rows8(const int* rp, int b, int* out) {
     for (int lane = 0; lane < kBatchNonzeros; ++lane) out[lane] = csr_row<8>(*reinterpret_cast<const int(*)[9]>(rp), csr_nonzero(rp[0], b, lane));
 }
 uint32_t counter(uint32_t v) { return spread_word(v); }
+int kmeans_shape(int M, int N) { return kmeans_columns(M, N); }
 int has_room(int p, int row_end, int capacity) { return csr_has_room(p, row_end, capacity); }
 }
 """
