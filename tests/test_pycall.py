@@ -1,12 +1,13 @@
 """The native call path of sqllm_dense_sparse_matvec takes and refuses the arguments that the ctypes path takes and refuses.  No GPU: every
 call here fails validation on the host, or is not for the native path."""
 import ctypes
+import os
 
 import numpy as np
 import pytest
 
 import paper_2306_07629_amd as sq
-from paper_2306_07629_amd import binding
+from paper_2306_07629_amd import binding, build
 
 GOOD = dict(M=4, N=128, bits=3, nnz=0, B=1, qidx=4096, lut=4096, rowptr=None, cols=None, vals=None, plan=None, x=4096, y=4096, stream=0)
 
@@ -25,6 +26,8 @@ class Stream:
 
 @pytest.fixture(scope="module")
 def native():
+    if build.pycall_is_stale():
+        build.build_pycall()
     from paper_2306_07629_amd import _pycall
     asked = []
     _pycall.bind(ctypes.cast(sq.lib().sqllm_dense_sparse_matvec, ctypes.c_void_p).value, lambda: 3, lambda dev: asked.append(dev) or 0)
@@ -74,6 +77,26 @@ def test_errors_of_data_ptr_arrive(native):
         native[0](*{**GOOD, "x": Gone()}.values())
     with pytest.raises(AttributeError):
         native[0](*{**GOOD, "x": object()}.values())
+
+
+def test_a_library_without_the_module_is_not_stale(monkeypatch):
+    sq.lib()
+    monkeypatch.setattr(build, "PYCALL", "/nonexistent/_pycall.so")
+    assert build.pycall_is_stale() and not build.is_stale()
+
+
+def test_the_library_is_built_without_a_c_compiler(monkeypatch, capfd):
+    monkeypatch.setattr(build, "HIPCC", "true")                          # stands for a compiler that succeeds
+    monkeypatch.setattr(build, "CC", "/nonexistent/gcc")
+    before = os.path.getmtime(build.PYCALL) if os.path.exists(build.PYCALL) else None
+    assert build.build() == build.LIB
+    assert "was not built" in capfd.readouterr().err
+    assert before is None or os.path.getmtime(build.PYCALL) == before    # what was there stays
+
+
+def test_the_module_is_named_for_its_interpreter():
+    import importlib.machinery
+    assert os.path.basename(build.PYCALL) == "_pycall" + importlib.machinery.EXTENSION_SUFFIXES[0]
 
 
 def test_binding_raises_with_the_status():
