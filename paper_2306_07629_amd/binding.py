@@ -81,15 +81,19 @@ def _ptr(t):
 _torch = _raw_stream = None
 
 
+def _find_streams():
+    global _torch, _raw_stream
+    import torch
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda dev: torch.cuda.current_stream(dev).cuda_stream)
+    _torch = torch
+
+
 def _stream(stream):
     """Raw handle of `stream` (None: the current stream of the current device).  The handle is asked for directly: building a Stream
     object for it took 3.0 of the 8.8 us that a single-layer call costs the host, this way takes 0.4."""
-    global _torch, _raw_stream
     if stream is None:
         if _torch is None:
-            import torch
-            _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda dev: torch.cuda.current_stream(dev).cuda_stream)
-            _torch = torch
+            _find_streams()
         return _raw_stream(_torch.cuda.current_device())
     return stream if isinstance(stream, int) else stream.cuda_stream
 
@@ -111,15 +115,27 @@ def _matvec_ctypes(M, N, bits, nnz, B, qidx, lut, rowptr, cols, vals, plan, x, y
                                            _ptr(x), _ptr(y), _stream(stream))
 
 
-def _matvec_first(*args):
-    """The first call: goes through ctypes, then hands over to the native path if torch has a current stream to ask for."""
-    global _matvec
-    status = _matvec_ctypes(*args)
-    if _raw_stream is not None:
+def _native_matvec():
+    """The native form of the call; None where its module cannot be built or imported (said once): ctypes does the same."""
+    address = ctypes.cast(lib().sqllm_dense_sparse_matvec, ctypes.c_void_p).value
+    try:
+        if _build.pycall_is_stale():
+            _build.build_pycall()
         from . import _pycall
-        _pycall.bind(ctypes.cast(lib().sqllm_dense_sparse_matvec, ctypes.c_void_p).value, _torch.cuda.current_device, _raw_stream)
-        _matvec = _pycall.matvec
-    return status
+    except (ImportError, OSError, RuntimeError) as e:
+        print(f"paper_2306_07629_amd: no native call path, calls go through ctypes: {e}", file=sys.stderr, flush=True)
+        return None
+    if _torch is None:
+        _find_streams()
+    _pycall.bind(address, _torch.cuda.current_device, _raw_stream)
+    return _pycall.matvec
+
+
+def _matvec_first(*args):
+    """The first call chooses the path of all later ones."""
+    global _matvec
+    _matvec = _native_matvec() or _matvec_ctypes
+    return _matvec(*args)
 
 
 _matvec = _matvec_first

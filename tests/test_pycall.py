@@ -2,6 +2,7 @@
 call here fails validation on the host, or is not for the native path."""
 import ctypes
 import os
+import sys
 
 import numpy as np
 import pytest
@@ -77,6 +78,45 @@ def test_errors_of_data_ptr_arrive(native):
         native[0](*{**GOOD, "x": Gone()}.values())
     with pytest.raises(AttributeError):
         native[0](*{**GOOD, "x": object()}.values())
+
+
+@pytest.fixture
+def fresh(monkeypatch):
+    """a process that has not called yet"""
+    monkeypatch.setattr(binding, "_matvec", binding._matvec_first)
+    return monkeypatch
+
+
+def call(**change):
+    a = {**GOOD, **change}
+    return sq.sqllm_dense_sparse_matvec(a["M"], a["N"], a["bits"], a["nnz"], a["B"], a["qidx"], a["lut"], a["rowptr"], a["cols"], a["vals"],
+                                        a["x"], a["y"], stream=a["stream"], plan=a["plan"])
+
+
+def test_public_call_takes_the_native_path_whatever_the_stream(native, fresh):
+    from paper_2306_07629_amd import _pycall
+    with pytest.raises(sq.SqllmError) as e:
+        call(bits=7, stream=0)                                           # a program that always passes its stream
+    assert e.value.status == 2 and binding._matvec is _pycall.matvec
+    with pytest.raises(sq.SqllmError) as e:                              # left to ctypes by the native path
+        call(bits=np.int64(3), B=99)
+    assert e.value.status == 6
+
+
+@pytest.mark.parametrize("cause", ["no compiler", "no module"])
+def test_without_the_module_calls_go_through_ctypes(native, fresh, capfd, cause):
+    import paper_2306_07629_amd as package
+    if cause == "no compiler":
+        fresh.setattr(build, "PYCALL", "/nonexistent/_pycall.so")
+        fresh.setattr(build, "CC", "/nonexistent/gcc")
+    else:
+        fresh.delattr(package, "_pycall")
+        fresh.setitem(sys.modules, "paper_2306_07629_amd._pycall", None)   # import raises ImportError
+    for _ in range(2):
+        with pytest.raises(sq.SqllmError) as e:
+            call(bits=7)
+        assert e.value.status == 2 and binding._matvec is binding._matvec_ctypes
+    assert capfd.readouterr().err.count("through ctypes") == 1
 
 
 def test_a_library_without_the_module_is_not_stale(monkeypatch):
