@@ -18,8 +18,9 @@
 //     a wave-wide look-up occupies the LDS for ~4 cycles (64 entries) / ~7 cycles (256 entries, bank
 //     conflicts), against ~7.3 for a ds_bpermute-based register table.  The field extraction is a shift + mask
 //     (a funnel shift where a 3-bit pair straddles two dwords; a byte select for b = 4).
-//   * Per row the 64 lane sums are reduced with DPP adds (no LDS traffic), the slice sums of the W waves
-//     are combined through LDS in a fixed order, the CSR term is added, and y is rounded to fp16 once.
+//   * The products of the sparse term join the lane sums of the dense term.  Per row the 64 lane sums are
+//     reduced with DPP adds (no LDS traffic), the sums of the waves are combined through LDS in a fixed
+//     order, and y is rounded to fp16 once.
 //   * Sparse wave (balanced CSR, cf. Sec. 4.3): one extra wave per workgroup handles the nonzeros of the
 //     block's rows while the dense waves stream.  The nonzeros of R consecutive rows are one contiguous
 //     range of the CSR arrays; lane l takes nonzeros l, l + 64, ... of that range whatever rows they fall in
@@ -297,8 +298,6 @@ __device__ __forceinline__ void load_row_pointers(const MatvecArgs& g, int r0, i
     sr.P0 = rp[0]; sr.P1 = rp[R]; sr.nbatch = csr_batch_count(sr.P0, sr.P1);
 }
 
-// The work of one workgroup: rows [R block, R block + R) of layer g, carried by the workgroup's first NW waves
-// (W dense waves, then the sparse wave).
 // Total of one output row over the workgroup's n partial sums a[i * R + row].
 // Eight lanes per row (lane = 8 row + p) each add every eighth value in order, then the eight are combined by a butterfly whose
 // every lane forms the same sums; the order depends on the count only, not on R.  Valid in all eight lanes of a row < R.
@@ -315,6 +314,8 @@ __device__ __forceinline__ float block_row_total(const float* __restrict__ a, in
     return s;
 }
 
+// The work of one workgroup: rows [R block, R block + R) of layer g, carried by the workgroup's first NW waves
+// (W dense waves, then the sparse wave).
 template <int BITS, int R, int D>
 __device__ __forceinline__ void matvec_block(const MatvecArgs& g, int block, int NW) {
     static_assert(D >= 2 && D <= R && (R == 4 || R == 8), "prefetch depth, rows per workgroup");
@@ -422,7 +423,7 @@ __device__ __forceinline__ void matvec_block(const MatvecArgs& g, int block, int
         for (int u = 0; u < R; ++u) acc[u] = 0.f;
         if (dense) {
             // columns and values of the first batches are requested BEFORE the dense waves' table barrier: the row pointers arrive
-            // together with the fp16 tables, so the second hop of the chain (row pointers -> columns / values -> gathers -> scan)
+            // together with the fp16 tables, so the second hop of the chain (row pointers -> columns / values -> gathers -> sums)
             // runs while the tables are built instead of after (22016x8192 fused 21.3 -> 20.5 us)
             if (sr.nbatch > 2) {
                 SparseRegs<UB> q;
@@ -451,7 +452,7 @@ __device__ __forceinline__ void matvec_block(const MatvecArgs& g, int block, int
     if (row_block_valid(lane) && (R == 8 || !(lane & 8))) part[(wave * 4 + (lane >> 4)) * R + row_block_class<R>(lane)] = acc[0];
     __syncthreads();
 
-    // combine the slice sums and the sparse partial sums in a fixed order, round once
+    // combine the sums of the waves in a fixed order, round once
     uint16_t* __restrict__ y = static_cast<uint16_t*>(g.y);
     if (wave == 0) {
         float s = block_row_total<R>(part, 4 * NW, lane);
@@ -1011,10 +1012,12 @@ static hipError_t launch_matvec_r(const MatvecArgs& g, hipStream_t s) {
     return hipGetLastError();
 }
 
-// One activation column.  Rows per workgroup, measured (fused, 0.45 % sparse): 4 rows win on 22016x8192 (19.3 against 19.4 us),
-// 8192x8192 (11.0 against 13.4) and 11008x4096 (8.8 against 9.8); rows of eight or more slices -- 8192x22016 with its 11 waves per
-// workgroup, of which a compute unit holds only two -- want 8 rows (25.1 against 27.3 us): the fixed cost of a workgroup (tables,
-// barriers, the final combination) is then spread over twice the stream.
+// One activation column.  Rows per workgroup, measured at 3 bits with weights from HBM (us with 4 rows / with 8; dense, then with 0.45 %
+// nonzeros from the CSR arrays, then from a plan): 4096x4096 4.4 / 5.1, 4.9 / 5.5, 4.6 / 5.2; 11008x4096 6.6 / 7.1, 7.4 / 8.3, 7.5 / 8.0;
+// 8192x8192 8.6 / 8.8, 9.6 / 9.8, 9.8 / 9.4; 22016x8192 18.2 / 19.5, 20.6 / 19.9, 20.0 / 19.1; 8192x16384 14.8 / 14.4, 19.2 / 18.4, 17.9 / 17.4;
+// 8192x22016 22.9 / 20.5, 25.3 / 23.4, 25.3 / 22.6; 4096x28672 16.2 / 13.3, 17.4 / 15.9, 19.8 / 16.8.  Rows of eight or more slices -- 8192x22016 with
+// its 11 waves per workgroup, of which a compute unit holds only two -- want 8 rows: the fixed cost of a workgroup (tables, barriers, the
+// final combination) is then spread over twice the stream.  Below that 4 rows are the better choice for narrow rows and without nonzeros.
 template <int BITS>
 static hipError_t launch_matvec_one(const MatvecArgs& g, hipStream_t s) {
     return g.qidx && multi_rows_per_workgroup(g.N) == 8 ? launch_matvec_r<BITS, 8, 2>(g, s) : launch_matvec_r<BITS, 4, 2>(g, s);

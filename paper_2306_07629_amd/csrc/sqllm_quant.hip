@@ -342,8 +342,9 @@ __device__ __forceinline__ float mean_of(double sum, u32 mass, bool& near) {
     return (float)(q * 5.9604644775390625e-08);
 }
 // Words from which a bucket is sorted and searched instead of read through.  A round reads 16 words and a bisection step one, in about the
-// same time: at 128 words rows of 8-bit levels, whose fullest buckets hold 137, lost (4096x11008 at 4 bits 751 us, 639 at 256 words, 633
-// without); at 512 rows with buckets in between lost (8192x1024 at 2 bits, two values: 362 us, 165 at 256 words).
+// same time.  At 128 words rows of 8-bit levels, whose fullest buckets hold 137, lose (4096x11008 at 4 bits 639 us, 515 at 256 words;
+// 4096x11776 at 2 bits 443, 320), though some rows of 16 levels gain (451, 512); at 512 rows with buckets in between lose (8192x1024 at 2
+// bits, two values 215, 130; 4096x8320 at 3 bits, 16 levels 469, 401).
 constexpr int kHeavy = 256;
 
 // One block of T threads per row.  In one dimension the clusters of Lloyd's method are intervals of the sorted weights, so an update
@@ -359,16 +360,17 @@ constexpr int kHeavy = 256;
 //     between two updates;
 //   * pruned, constant or already quantised rows have few keys and many words of each.  Buckets of kHeavy words or more are therefore put in
 //     the order of their keys, and an update bisects them instead of reading them through (nine tenths zeros, 32 updates: 4096x11008 at 4
-//     bits 0.84 ms, read through 16.3; 1024x28672 0.52 ms, read through 18.7).
+//     bits 0.81 ms, read through 16.3; 1024x28672 0.50 ms, read through 18.7).
 // The decisions and integers are those of a pass over all weights per update, hence the same result.
 // Bound by the latency of the chain boundary -> bucket -> words -> reduction -> division (1150 cycles at 4096 weights and 8 entries, 1130 at
-// 11008 and 16; with 4096 buckets 1480), which the other rows on the unit cover only in
-// part (what their LDS allows: six at 4096 weights, two at 11008).  It was 1570 and 1920 with the key of a boundary corrected in two steps, the two bucket ends read one after the other under a branch, a test
-// in front of the first round, a full fp64 division behind the test for the end, and no priority over the waves of other rows.  Against a
-// bitonic sort of the row in LDS and a 64-way search per boundary with reductions over 64 lanes: 4096x4096 at 3 bits 409 us, now 90
+// 11008 and 16; with 4096 buckets 1480), which the other rows on the unit cover only in part (what their LDS allows: six at 4096 weights, two
+// at 11008).  It was 1570 and 1920 with the key of a boundary corrected in two steps, the two bucket ends read one after the other under a
+// branch, a test in front of the first round, a full fp64 division behind the test for the end, and no priority over the waves of other rows.
+// Against a bitonic sort of the row in LDS and a 64-way search per boundary with reductions over 64 lanes: 4096x4096 at 3 bits 409 us, now 89
 // (22 updates per row), 4096x11008 at 4 bits 1164, now 258 (32 updates).
 // Threads T, units of eight weights per thread V, buckets, words per chunk of running sums (twice as many in wide rows), and the waves per
-// SIMD the registers are held down for.
+// SIMD the registers are held down for.  All shapes but the narrowest keep scalar registers in lanes of vector registers: 17 to 19 of them with
+// two units per thread, 47 to 79 with three and four.
 template <int T_, int V_, int LOG_NB, int CHUNK, int WAVES>
 struct KmeansShape {
     static constexpr int T = T_, V = V_, kWavesPerSimd = WAVES, kChunk = CHUNK;
@@ -400,7 +402,7 @@ typedef KmeansShape<512, 3, 13, 8, 4> KmeansUpTo11776;               // 77 KB at
                                                                      // apart in the banks and four of them per access 475 (4096 buckets 477)
 typedef KmeansShape<512, 3, 12, 8, 4> KmeansUpTo12288;
 typedef KmeansShape<512, 4, 12, 8, 4> KmeansUpTo16384;
-typedef KmeansShape<1024, 4, 12, 16, 4> KmeansBeyond;                // 145 KB at 28672: one (two to four registers spilled; 1024x28672 at 4 bits 0.32 ms)
+typedef KmeansShape<1024, 4, 12, 16, 4> KmeansBeyond;                // 145 KB at 28672: one (four registers spilled; 1024x28672 at 4 bits 0.29 ms)
 
 constexpr int kMaxN11776 = 11776;
 static_assert(KmeansUpTo11776::lds(kMaxN11776) + 512 <= 80 * 1024, "two rows per compute unit");
